@@ -901,139 +901,64 @@ extern "C" int dlma_correlators(dlma_gauge_t h, int t_src, int nev, const void* 
     if (!V_all || !C_out || (ndist > 0 && !phi_dist) || (nnoise > 0 && (!phi || !phibar)))
         return fail(DLMA_EINVAL, "NULL pointer");
     hipStream_t s = S(stream);
-    const long V = g->V;
-    const long fs = V * 12;  // complex numbers per spinor field
-    const int nd = 4 * ndist, nn = 4 * nnoise;
-    // fields: dist solutions, then phi, then phibar
-    std::vector<const double2*> fields;
-    for (int i = 0; i < nd; ++i) fields.push_back((const double2*)phi_dist + i * fs);
-    for (int i = 0; i < nn; ++i) fields.push_back((const double2*)phi + i * fs);
-    for (int i = 0; i < nn; ++i) fields.push_back((const double2*)phibar + i * fs);
-    const int nf = (int)fields.size();
-    // Gram pairs: dist (phi_{l,s'}, phi_{l,s}); noise (phi_{r,s'}, phi_{r,s}) and (phibar_{r,s'}, phi_{r,s})
-    std::vector<const double2*> pa, pb;
-    for (int l = 0; l < ndist; ++l)
-        for (int sp = 0; sp < 4; ++sp)
-            for (int sq = 0; sq < 4; ++sq) { pa.push_back(fields[l * 4 + sp]); pb.push_back(fields[l * 4 + sq]); }
-    for (int r = 0; r < nnoise; ++r)
-        for (int y = 0; y < 2; ++y)
-            for (int sp = 0; sp < 4; ++sp)
-                for (int sq = 0; sq < 4; ++sq) {
-                    pa.push_back(fields[nd + (y ? nn : 0) + r * 4 + sp]);
-                    pb.push_back(fields[nd + r * 4 + sq]);
-                }
-    const int np = (int)pa.size();
-    Buf dF, dA, dB, dP, dG;
-    DLMA_TRY(dF.allocate(sizeof(void*) * std::max(1, nf)));
-    DLMA_TRY(dA.allocate(sizeof(void*) * std::max(1, np)));
-    DLMA_TRY(dB.allocate(sizeof(void*) * std::max(1, np)));
-    DLMA_TRY(dP.allocate(sizeof(double2) * (size_t)nf * T * nev * 4));
-    DLMA_TRY(dG.allocate(sizeof(double2) * (size_t)np * T * 16));
-    DLMA_HIP(hipMemcpyAsync(dF.p, fields.data(), sizeof(void*) * nf, hipMemcpyHostToDevice, s));
-    DLMA_HIP(hipMemcpyAsync(dA.p, pa.data(), sizeof(void*) * np, hipMemcpyHostToDevice, s));
-    DLMA_HIP(hipMemcpyAsync(dB.p, pb.data(), sizeof(void*) * np, hipMemcpyHostToDevice, s));
-    DLMA_HIP(launch_tproj((const double2*)V_all, (const double2* const*)dF.p, nf, g->geo, nev, dP.as<double2>(), s));
-    DLMA_HIP(launch_spin_gram((const double2* const*)dA.p, (const double2* const*)dB.p, np, g->geo, dG.as<double2>(), s));
-    std::vector<cplx> P((size_t)nf * T * nev * 4), G((size_t)np * T * 16);
-    DLMA_HIP(hipMemcpyAsync(P.data(), dP.p, sizeof(double2) * P.size(), hipMemcpyDeviceToHost, s));
-    DLMA_HIP(hipMemcpyAsync(G.data(), dG.p, sizeof(double2) * G.size(), hipMemcpyDeviceToHost, s));
-    DLMA_HIP(hipStreamSynchronize(s));
-
-    // Host assembly of the few numbers per timeslice from the GPU projections and Grams.
-    auto Pf = [&](int f, int t, int k, int sp) { return P[(((size_t)f * T + t) * nev + k) * 4 + sp]; };
-    auto Gp = [&](int p, int t, int s1, int s2) { return G[((size_t)p * T + t) * 16 + s1 * 4 + s2]; };
+    const long fs = g->V * 12;  // complex numbers per spinor field
+    const long L3 = (long)g->dims[1] * g->dims[2] * g->dims[3];
+    const int ud = (ndist + 1) / 2, un = nnoise;  // units of the contraction kernel
+    const int ksd = contract_ks(g->geo, T, ud), ksn = contract_ks(g->geo, T, un);
+    const size_t taud = (size_t)ndist * T * nev * 16, taun = (size_t)2 * nnoise * T * nev * 16;
+    const size_t np = (size_t)T * proj_gram_parts() * 256;
+    // spin weights: the piece <A_{s'}, M B_s> N_{s s'} takes entry (s', a), (s, b) of a Gram
     std::vector<Gam> ga = gammas();
     const Gam g5 = ga[4];
-    std::fill(C_out, C_out + (size_t)DLMA_NGAMMA * DLMA_NPARTS * T * 2, 0.0);
+    std::vector<cplx> W(DLMA_NGAMMA * 256, 0.0);
     for (int gi = 0; gi < DLMA_NGAMMA; ++gi) {
         std::vector<Gam> Gs;
         if (gi == 0) Gs.push_back(g5);
         else Gs = {ga[1], ga[2], ga[3]};
-        std::vector<cplx> acc((size_t)DLMA_NPARTS * T, 0.0);
         for (const Gam& Gm : Gs) {
-            Gam M = gmul(g5, Gm), N = gmul(Gm, g5);
-            for (int d = 0; d < T; ++d) {
-                int t = (t_src + d) % T;
-                // <A, M B>_t from a Gram, <A, M P_t B>_t from projections
-                auto mg = [&](int p) {
-                    cplx v = 0;
-                    for (int a = 0; a < 4; ++a)
+            const Gam M = gmul(g5, Gm), N = gmul(Gm, g5);
+            for (int sq = 0; sq < 4; ++sq)
+                for (int a = 0; a < 4; ++a)
+                    for (int sp = 0; sp < 4; ++sp)
                         for (int b = 0; b < 4; ++b)
-                            if (M.m[a][b] != 0.0) v += M.m[a][b] * Gp(p, t, a, b);
-                    return v;
-                };
-                auto mp = [&](int fa, int fb) {
-                    cplx v = 0;
-                    for (int k = 0; k < nev; ++k)
-                        for (int a = 0; a < 4; ++a)
-                            for (int b = 0; b < 4; ++b)
-                                if (M.m[a][b] != 0.0) v += M.m[a][b] * std::conj(Pf(fa, t, k, a)) * Pf(fb, t, k, b);
-                    return v;
-                };
-                // noise estimators
-                if (nnoise > 0) {
-                    cplx qq = 0, pq = 0, qp = 0, pp = 0, one = 0;
-                    for (int r = 0; r < nnoise; ++r)
-                        for (int s1 = 0; s1 < 4; ++s1)       // s: source spin of phi_{r,s}
-                            for (int s2 = 0; s2 < 4; ++s2) {  // s': spin of phiY_{r,s'}
-                                cplx nc = N.m[s1][s2];
-                                if (nc == 0.0) continue;
-                                int p1 = ndist * 16 + (r * 2 + 0) * 16 + s2 * 4 + s1;  // (phi_{r,s'}, phi_{r,s})
-                                int pQ = ndist * 16 + (r * 2 + 1) * 16 + s2 * 4 + s1;  // (phibar_{r,s'}, phi_{r,s})
-                                int fB = nd + r * 4 + s1;
-                                int fA1 = nd + r * 4 + s2, fAQ = nd + nn + r * 4 + s2;
-                                cplx g1 = mg(p1), gQ = mg(pQ);
-                                cplx P1 = mp(fA1, fB), PQ = mp(fAQ, fB);
-                                // Y = 1: phi; Y = Q: phibar; Y = P: phi - phibar.  X = P: projected; Q = 1 - P
-                                cplx y1x1 = g1, y1xp = P1, yqx1 = gQ, yqxp = PQ;
-                                cplx ypx1 = g1 - gQ, ypxp = P1 - PQ;
-                                qq += nc * (yqx1 - yqxp);
-                                pq += nc * yqxp;
-                                qp += nc * (ypx1 - ypxp);
-                                pp += nc * ypxp;
-                                one += nc * y1x1;
-                                (void)y1xp;
-                            }
-                    acc[0 * T + d] += qq / nvec;
-                    acc[1 * T + d] += pq / nvec;
-                    acc[2 * T + d] += qp / nvec;
-                    acc[3 * T + d] += pp / nvec;
-                    acc[4 * T + d] += one / nvec;
-                }
-                // exact C_dist from the perambulator tau_{(k s),(l s')} = P[l*4+s'][t][k][s]
-                cplx cd = 0;
-                for (int k = 0; k < nev; ++k)
-                    for (int l = 0; l < ndist; ++l)
-                        for (int s1 = 0; s1 < 4; ++s1)
-                            for (int s2 = 0; s2 < 4; ++s2) {
-                                if (M.m[s1][s2] == 0.0) continue;
-                                for (int s3 = 0; s3 < 4; ++s3)
-                                    for (int s4 = 0; s4 < 4; ++s4) {
-                                        if (N.m[s3][s4] == 0.0) continue;
-                                        cd += M.m[s1][s2] * Pf(l * 4 + s3, t, k, s2) * N.m[s3][s4] * std::conj(Pf(l * 4 + s4, t, k, s1));
-                                    }
-                            }
-                acc[5 * T + d] += cd;
-                // exact C_QP from the distillation solutions
-                cplx cq = 0;
-                for (int l = 0; l < ndist; ++l)
-                    for (int s1 = 0; s1 < 4; ++s1)
-                        for (int s2 = 0; s2 < 4; ++s2) {
-                            cplx nc = N.m[s1][s2];
-                            if (nc == 0.0) continue;
-                            int p = l * 16 + s2 * 4 + s1;  // (phi_{l,s'}, phi_{l,s})
-                            cq += nc * (mg(p) - mp(l * 4 + s2, l * 4 + s1));
-                        }
-                acc[6 * T + d] += cq;
-            }
+                            W[(size_t)gi * 256 + (sq * 4 + a) * 16 + sp * 4 + b] += N.m[sp][sq] * M.m[a][b] / (double)Gs.size();
         }
-        for (int part = 0; part < DLMA_NPARTS; ++part)
-            for (int d = 0; d < T; ++d) {
-                cplx v = acc[(size_t)part * T + d] / (double)Gs.size();
-                C_out[(((size_t)gi * DLMA_NPARTS + part) * T + d) * 2 + 0] = v.real();
-                C_out[(((size_t)gi * DLMA_NPARTS + part) * T + d) * 2 + 1] = v.imag();
-            }
     }
+    // work buffers in one allocation: tau and its partials, Gram and projected partials, weights, result
+    size_t off = 0;
+    auto take = [&](size_t n) { const size_t o = off; off += n; return o; };
+    const size_t o_td = take(taud), o_tdp = take(ksd > 1 ? taud * ksd : 0), o_gd = take((size_t)T * ksd * ud * 256);
+    const size_t o_tn = take(taun), o_tnp = take(ksn > 1 ? taun * ksn : 0), o_gn = take((size_t)T * ksn * un * 512);
+    const size_t o_pd = take(np), o_pn = take(np), o_pq = take(np), o_w = take(W.size());
+    const size_t o_c = take((size_t)DLMA_NGAMMA * DLMA_NPARTS * T);
+    Buf ws;
+    DLMA_TRY(ws.allocate(sizeof(double2) * off));
+    double2* w = ws.as<double2>();
+    DLMA_HIP(hipMemcpyAsync(w + o_w, W.data(), sizeof(cplx) * W.size(), hipMemcpyHostToDevice, s));
+    ContractArgs ca = {};
+    ca.Vall = (const double2*)V_all;
+    ca.L3 = L3; ca.fs = fs; ca.nt = T; ca.nev = nev;
+    if (ndist > 0) {
+        ca.f0 = (const double2*)phi_dist; ca.ng = ndist; ca.ks = ksd;
+        ca.taup = w + o_tdp; ca.gramp = w + o_gd;
+        DLMA_HIP(launch_contract(ca, false, true, w + o_td, s));
+        DLMA_HIP(launch_proj_gram(w + o_td, T, nev, ndist, 0, 0, 1, w + o_pd, s));
+    }
+    if (nnoise > 0) {
+        ca.f0 = (const double2*)phi; ca.f1 = (const double2*)phibar; ca.ng = nnoise; ca.ks = ksn;
+        ca.taup = w + o_tnp; ca.gramp = w + o_gn;
+        DLMA_HIP(launch_contract(ca, true, true, w + o_tn, s));
+        DLMA_HIP(launch_proj_gram(w + o_tn, T, nev, nnoise, 0, 0, 2, w + o_pn, s));
+        DLMA_HIP(launch_proj_gram(w + o_tn, T, nev, nnoise, 1, 0, 2, w + o_pq, s));
+    }
+    CorrPiecesArgs pc = {};
+    pc.gd = w + o_gd; pc.pd = w + o_pd; pc.gn = w + o_gn; pc.pn = w + o_pn; pc.pq = w + o_pq;
+    pc.W = w + o_w; pc.C = w + o_c;
+    pc.inv_nvec = 1.0 / nvec; pc.T = T; pc.t_src = t_src;
+    pc.nud = ksd * ud; pc.nun = ksn * un;
+    DLMA_HIP(launch_corr_pieces(pc, s));
+    DLMA_HIP(hipMemcpyAsync(C_out, w + o_c, sizeof(double2) * DLMA_NGAMMA * DLMA_NPARTS * T, hipMemcpyDeviceToHost, s));
+    DLMA_HIP(hipStreamSynchronize(s));
     return DLMA_OK;
 }
 
@@ -1063,7 +988,6 @@ extern "C" int dlma_correlators_grad(dlma_gauge_t h, int t_src, int nev, const v
     hipStream_t s = S(stream);
     const long L3 = (long)g->dims[1] * g->dims[2] * g->dims[3];
     const long fs = g->V * 12;
-    const int nd = 4 * ndist, nn = 4 * nnoise, nf = nd + 2 * nn;
     const double nvec = nnoise > 0 ? (double)(nnoise / ndil) : 1.0;
 
     // weight matrices per timeslice: noise [T][32][32] over (phi_s, phibar_s) x spin, dist [T][16][16]
@@ -1129,66 +1053,48 @@ extern "C" int dlma_correlators_grad(dlma_gauge_t h, int t_src, int nev, const v
         }
     }
     int nact = 0;
+    std::vector<int> tlist;
     for (int t = 0; t < T; ++t)
-        if (tact[t] >= 0) tact[t] = nact++;
-    // projections of every input field on the modes of every timeslice: P[f][t][k][s]
-    std::vector<const double2*> fields;
-    for (int i = 0; i < nd; ++i) fields.push_back((const double2*)phi_dist + i * fs);
-    for (int i = 0; i < nn; ++i) fields.push_back((const double2*)phi + i * fs);
-    for (int i = 0; i < nn; ++i) fields.push_back((const double2*)phibar + i * fs);
-    Buf dF, dP, dW1n, dW1d, dTn, dTd, dTact;
-    std::vector<cplx> P;
+        if (tact[t] >= 0) {
+            tact[t] = nact++;
+            tlist.push_back(t);
+        }
+    // tau' = WP(t) V(t)^dag F for every group and weighted timeslice, on the device
+    Buf dW1n, dW1d, dWPn, dWPd, dTn, dTd, dTact, dtau, dtaup;
+    DLMA_TRY(dTact.allocate(sizeof(int) * 2 * T));
+    DLMA_HIP(hipMemcpyAsync(dTact.p, tact.data(), sizeof(int) * T, hipMemcpyHostToDevice, s));
+    const int ksd = contract_ks(g->geo, nact, (ndist + 1) / 2), ksn = contract_ks(g->geo, nact, nnoise);
+    const size_t taud = (size_t)ndist * nact * nev * 16, taun = (size_t)nnoise * nact * nev * 32;
+    DLMA_TRY(dTn.allocate(sizeof(double2) * taun));
+    DLMA_TRY(dTd.allocate(sizeof(double2) * taud));
     if (nact > 0) {
-        DLMA_TRY(dF.allocate(sizeof(void*) * nf));
-        DLMA_TRY(dP.allocate(sizeof(double2) * (size_t)nf * T * nev * 4));
-        DLMA_HIP(hipMemcpyAsync(dF.p, fields.data(), sizeof(void*) * nf, hipMemcpyHostToDevice, s));
-        DLMA_HIP(launch_tproj((const double2*)V_all, (const double2* const*)dF.p, nf, g->geo, nev, dP.as<double2>(), s));
-        P.resize((size_t)nf * T * nev * 4);
-        DLMA_HIP(hipMemcpyAsync(P.data(), dP.p, sizeof(double2) * P.size(), hipMemcpyDeviceToHost, s));
-        DLMA_HIP(hipStreamSynchronize(s));
-    }
-    // tau' = WP(t) tau for every group and weighted timeslice
-    std::vector<cplx> taun((size_t)std::max(1, nnoise) * std::max(1, nact) * nev * 32, 0.0);
-    std::vector<cplx> taud((size_t)std::max(1, ndist) * std::max(1, nact) * nev * 16, 0.0);
-    auto Pf = [&](int f, int t, int k, int sp) { return P[(((size_t)f * T + t) * nev + k) * 4 + sp]; };
-    for (int t = 0; t < T; ++t) {
-        const int ta = tact[t];
-        if (ta < 0) continue;
-        for (int r = 0; r < nnoise; ++r)
-            for (int k = 0; k < nev; ++k)
-                for (int row = 0; row < 32; ++row) {
-                    cplx v = 0;
-                    for (int col = 0; col < 32; ++col) {
-                        const cplx wv = WPn[((size_t)t * 32 + row) * 32 + col];
-                        if (wv == 0.0) continue;
-                        const int j = col >> 2, b = col & 3;
-                        const int f = j < 4 ? nd + r * 4 + j : nd + nn + r * 4 + (j - 4);
-                        v += wv * Pf(f, t, k, b);
-                    }
-                    taun[(((size_t)r * nact + ta) * nev + k) * 32 + row] = v;
-                }
-        for (int l = 0; l < ndist; ++l)
-            for (int k = 0; k < nev; ++k)
-                for (int row = 0; row < 16; ++row) {
-                    cplx v = 0;
-                    for (int col = 0; col < 16; ++col) {
-                        const cplx wv = WPd[((size_t)t * 16 + row) * 16 + col];
-                        if (wv == 0.0) continue;
-                        v += wv * Pf(l * 4 + (col >> 2), t, k, col & 3);
-                    }
-                    taud[(((size_t)l * nact + ta) * nev + k) * 16 + row] = v;
-                }
+        int* dtl = dTact.as<int>() + T;
+        DLMA_HIP(hipMemcpyAsync(dtl, tlist.data(), sizeof(int) * nact, hipMemcpyHostToDevice, s));
+        DLMA_TRY(dtau.allocate(sizeof(double2) * std::max(taud, taun)));
+        DLMA_TRY(dtaup.allocate(sizeof(double2) * std::max(taud * ksd, taun * ksn)));
+        ContractArgs ca = {};
+        ca.Vall = (const double2*)V_all;
+        ca.L3 = L3; ca.fs = fs; ca.tlist = dtl; ca.nt = nact; ca.nev = nev;
+        ca.taup = dtaup.as<double2>();
+        if (ndist > 0) {
+            DLMA_TRY(dWPd.allocate(sizeof(double2) * WPd.size()));
+            DLMA_HIP(hipMemcpyAsync(dWPd.p, WPd.data(), sizeof(double2) * WPd.size(), hipMemcpyHostToDevice, s));
+            ca.f0 = (const double2*)phi_dist; ca.ng = ndist; ca.ks = ksd;
+            DLMA_HIP(launch_contract(ca, false, false, dtau.as<double2>(), s));
+            DLMA_HIP(launch_tau_weights(dtau.as<double2>(), dWPd.as<double2>(), dtl, nact, nev, ndist, false, dTd.as<double2>(), s));
+        }
+        if (nnoise > 0) {
+            DLMA_TRY(dWPn.allocate(sizeof(double2) * WPn.size()));
+            DLMA_HIP(hipMemcpyAsync(dWPn.p, WPn.data(), sizeof(double2) * WPn.size(), hipMemcpyHostToDevice, s));
+            ca.f0 = (const double2*)phi; ca.f1 = (const double2*)phibar; ca.ng = nnoise; ca.ks = ksn;
+            DLMA_HIP(launch_contract(ca, true, false, dtau.as<double2>(), s));
+            DLMA_HIP(launch_tau_weights(dtau.as<double2>(), dWPn.as<double2>(), dtl, nact, nev, nnoise, true, dTn.as<double2>(), s));
+        }
     }
     DLMA_TRY(dW1n.allocate(sizeof(double2) * W1n.size()));
     DLMA_TRY(dW1d.allocate(sizeof(double2) * W1d.size()));
-    DLMA_TRY(dTn.allocate(sizeof(double2) * taun.size()));
-    DLMA_TRY(dTd.allocate(sizeof(double2) * taud.size()));
-    DLMA_TRY(dTact.allocate(sizeof(int) * T));
     DLMA_HIP(hipMemcpyAsync(dW1n.p, W1n.data(), sizeof(double2) * W1n.size(), hipMemcpyHostToDevice, s));
     DLMA_HIP(hipMemcpyAsync(dW1d.p, W1d.data(), sizeof(double2) * W1d.size(), hipMemcpyHostToDevice, s));
-    DLMA_HIP(hipMemcpyAsync(dTn.p, taun.data(), sizeof(double2) * taun.size(), hipMemcpyHostToDevice, s));
-    DLMA_HIP(hipMemcpyAsync(dTd.p, taud.data(), sizeof(double2) * taud.size(), hipMemcpyHostToDevice, s));
-    DLMA_HIP(hipMemcpyAsync(dTact.p, tact.data(), sizeof(int) * T, hipMemcpyHostToDevice, s));
     CorrGradArgs a = {};
     a.Vall = (const double2*)V_all;
     a.dist = (const double2*)phi_dist; a.phi = (const double2*)phi; a.phibar = (const double2*)phibar;

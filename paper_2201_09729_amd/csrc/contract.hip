@@ -1,96 +1,293 @@
-// Timeslice contractions behind the correlators (paper eq. 2-4):
-//   tproj:     P[f][t][k][s] = sum_{m,c} conj(V_k(t)(m,c)) phi_f(t,m,s,c)
-//              (projections of solutions on the Laplacian modes; for the
-//              distillation solutions this is the perambulator)
-//   spin_gram: G[p][t][s1][s2] = sum_{m,c} conj(A_p(t,m,s1,c)) B_p(t,m,s2,c)
-//              (spin-resolved timeslice inner products of solution pairs)
+// Timeslice contractions behind the correlators (paper eq. 2-4).  With the four
+// spin-diluted solutions of a source group as columns i = (label s', spin a) of 3 L^3
+// rows (site, colour) on a timeslice, everything the correlators need is
+//   tau[k][i]  = sum_rows conj(v_k) F_i            (projections on the Laplacian modes;
+//                                                   for distillation the perambulator)
+//   gram[i][j] = sum_groups sum_rows conj(A_i) B_j  (spin-resolved inner products)
+//   proj[i][j] = sum_groups sum_k conj(tauA[k][i]) tauB[k][j]
+// for (A, B) = (dist, dist), (phi, phi), (phibar, phi); the pieces are fixed linear
+// combinations of the 16 x 16 sums, formed by k_corr_pieces.
 // Spinor fields are canonical complex128 [T][Z][Y][X][4][3]; V is [T][nev][L^3][3].
 #include "laplace.h"
 
 namespace dlma {
 
-__device__ __forceinline__ double2 cjm(double2 a, double2 b) { return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x); }
+// ---------------------------------------------------------------- projections and Grams
+//
+// One wave takes two column sets (two distillation groups, or the phi and phibar of a
+// noise group) on one chunk of sites of a timeslice, and up to 32 modes, on FP64 matrix
+// instructions (v_mfma_f64_16x16x4: operand lane l holds row or column l % 16 at
+// k = l / 16, result register i of lane l is row 4 i + l / 16 of column l % 16).  Lane
+// (q, m) = (l / 16, l % 16) loads the three colours of site x + q of column m (or of
+// mode m): 48 contiguous bytes, four sites of four spins contiguous across the wave.
+// The same registers are the A and the B operand of the Gram, so nothing is shuffled and
+// every field is read once for both results.  Two column sets per wave halve the reads
+// of V (L2 hits: the waves of a block take consecutive groups of one chunk, and each
+// XCD walks a contiguous range of chunks).
+// Bound: the matrix cores (64 cycles per instruction, 8 flop per complex product).  At
+// 16^3 x 32 with 32 modes, 128 distillation and 32 noise solutions the projections and
+// Grams took 23.8 ms as one block per field and four modes, every field read nev / 4
+// times for tau and 8 times for the Grams, and the sums over groups and spins 43 ms on
+// the host (67.2 ms per call); now 1.89 ms per call, 41 TFLOP/s of a 64 TFLOP/s FP64
+// matrix product.
+typedef double d4 __attribute__((ext_vector_type(4)));
 
-// one block per (k-group of 4, t, f)
-__global__ void __launch_bounds__(256) k_tproj(const double2* __restrict__ Vall, const double2* const* __restrict__ fields,
-                                               long L3, int nev, int T, double2* __restrict__ P) {
-    __shared__ double lds[4];
-    int k0 = blockIdx.x * 4, t = blockIdx.y, f = blockIdx.z;
-    const double2* phi = fields[f] + (long)t * L3 * 12;
-    const double2* Vt = Vall + (long)t * nev * L3 * 3;
-    double2 acc[4][4];
-    for (int a = 0; a < 4; ++a)
-        for (int b = 0; b < 4; ++b) acc[a][b] = make_double2(0, 0);
-    for (long m = threadIdx.x; m < L3; m += 256) {
-        double2 ps[12];
-        for (int i = 0; i < 12; ++i) ps[i] = phi[m * 12 + i];
-        for (int kk = 0; kk < 4; ++kk) {
-            if (k0 + kk >= nev) break;
-            const double2* v = Vt + ((long)(k0 + kk) * L3 + m) * 3;
-            double2 v0 = v[0], v1 = v[1], v2 = v[2];
-            for (int sp = 0; sp < 4; ++sp) {
-                double2 a = cjm(v0, ps[sp * 3]), b = cjm(v1, ps[sp * 3 + 1]), c = cjm(v2, ps[sp * 3 + 2]);
-                acc[kk][sp].x += a.x + b.x + c.x;
-                acc[kk][sp].y += a.y + b.y + c.y;
+__device__ __forceinline__ d4 mma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// Result tile (re, im) of one wave into [16][16] complex numbers, rows limited to nrow
+__device__ __forceinline__ void store_tile(double2* o, int lane, int nrow, const d4& re, const d4& im) {
+    const int q = lane >> 4, m = lane & 15;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (4 * i + q < nrow) o[(4 * i + q) * 16 + m] = make_double2(re[i], im[i]);
+}
+
+template <bool NOISE, bool GRAM, int MT>
+__global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
+    // block -> (unit group fastest, site chunk, timeslice), contiguous per XCD
+    const int per = gridDim.x >> 3;
+    const int lb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    const int nub = (a.nunit + 3) / 4;
+    const int ub = lb % nub, r = lb / nub;
+    const int kc = r % a.ks, ti = r / a.ks;
+    const int unit = ub * 4 + (int)(threadIdx.x >> 6);
+    if (ti >= a.nt || unit >= a.nunit) return;  // whole waves
+    const int t = a.tlist ? a.tlist[ti] : ti;
+    const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
+    const long L3 = a.L3;
+    const long x0 = kc * a.chunk, x1 = x0 + a.chunk < L3 ? x0 + a.chunk : L3;
+    // column sets: groups 2 unit, 2 unit + 1 (the second repeats the first past the end), or phi and phibar
+    const int g0 = NOISE ? unit : 2 * unit;
+    const bool two = NOISE || g0 + 1 < a.ng;
+    const long col = ((long)t * L3 + x0 + q) * 12 + (m & 3) * 3;
+    const double2* p0 = a.f0 + ((long)g0 * 4 + (m >> 2)) * a.fs + col;
+    const double2* p1 = NOISE ? a.f1 + ((long)g0 * 4 + (m >> 2)) * a.fs + col
+                              : a.f0 + ((long)(two ? g0 + 1 : g0) * 4 + (m >> 2)) * a.fs + col;
+    const double2* pv[MT];
+#pragma unroll
+    for (int b = 0; b < MT; ++b) {
+        const int k = a.k0 + 16 * b + m;  // modes past the last repeat it; their rows are not stored
+        pv[b] = a.Vall + (((long)t * a.nev + (k < a.nev ? k : a.nev - 1)) * L3 + x0 + q) * 3;
+    }
+    const d4 z = {0.0, 0.0, 0.0, 0.0};
+    d4 tr[2][MT], tm[2][MT], g00r = z, g00x = z, g10r = z, g10i = z;
+#pragma unroll
+    for (int b = 0; b < MT; ++b) { tr[0][b] = z; tr[1][b] = z; tm[0][b] = z; tm[1][b] = z; }
+    for (long x = x0; x < x1; x += 4) {
+        double2 f0[3], f1[3], v[MT][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) { f0[c] = p0[c]; f1[c] = p1[c]; }
+#pragma unroll
+        for (int b = 0; b < MT; ++b)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[b][c] = pv[b][c];
+        p0 += 48;
+        p1 += 48;
+#pragma unroll
+        for (int b = 0; b < MT; ++b) pv[b] += 12;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+            for (int b = 0; b < MT; ++b) {
+                const double vr = v[b][c].x, vi = v[b][c].y, nvi = -vi;
+                tr[0][b] = mma64(vr, f0[c].x, tr[0][b]);
+                tm[0][b] = mma64(vr, f0[c].y, tm[0][b]);
+                tr[1][b] = mma64(vr, f1[c].x, tr[1][b]);
+                tm[1][b] = mma64(vr, f1[c].y, tm[1][b]);
+                tr[0][b] = mma64(vi, f0[c].y, tr[0][b]);
+                tm[0][b] = mma64(nvi, f0[c].x, tm[0][b]);
+                tr[1][b] = mma64(vi, f1[c].y, tr[1][b]);
+                tm[1][b] = mma64(nvi, f1[c].x, tm[1][b]);
+            }
+            if (GRAM) {
+                // (A, A): the imaginary part is X - X^T with X = Re(A)^T Im(A)
+                g00r = mma64(f0[c].x, f0[c].x, g00r);
+                g00x = mma64(f0[c].x, f0[c].y, g00x);
+                g00r = mma64(f0[c].y, f0[c].y, g00r);
+                if (NOISE) {
+                    g10r = mma64(f1[c].x, f0[c].x, g10r);
+                    g10i = mma64(f1[c].x, f0[c].y, g10i);
+                    g10r = mma64(f1[c].y, f0[c].y, g10r);
+                    g10i = mma64(-f1[c].y, f0[c].x, g10i);
+                } else if (two) {
+                    g00r = mma64(f1[c].x, f1[c].x, g00r);
+                    g00x = mma64(f1[c].x, f1[c].y, g00x);
+                    g00r = mma64(f1[c].y, f1[c].y, g00r);
+                }
             }
         }
     }
-    for (int kk = 0; kk < 4; ++kk) {
-        if (k0 + kk >= nev) break;  // uniform
-        for (int sp = 0; sp < 4; ++sp) {
-            double re = block_sum<256>(acc[kk][sp].x, lds);
-            double im = block_sum<256>(acc[kk][sp].y, lds);
-            if (threadIdx.x == 0) P[(((long)f * T + t) * nev + k0 + kk) * 4 + sp] = make_double2(re, im);
+    const int nset = NOISE ? 2 * a.ng : a.ng;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+        if (s == 0 || two)
+#pragma unroll
+            for (int b = 0; b < MT; ++b) {
+                const int k = a.k0 + 16 * b;
+                const int set = NOISE ? 2 * g0 + s : g0 + s;
+                if (k < a.nev)
+                    store_tile(a.taup + ((((long)kc * nset + set) * a.nt + ti) * a.nev + k) * 16, lane, a.nev - k, tr[s][b], tm[s][b]);
+            }
+    if (GRAM) {
+        constexpr int NG = NOISE ? 2 : 1;
+        double2* o = a.gramp + (((long)ti * a.ks + kc) * a.nunit + unit) * NG * 256;
+        store_tile(o, lane, 16, g00r, g00x);
+        if (NOISE) store_tile(o + 256, lane, 16, g10r, g10i);
+    }
+}
+
+// Site chunks per (unit, timeslice): about 4096 waves in all (eight per SIMD slot pair),
+// at least 16 steps of four sites each
+static int contract_chunks(long L3, long waves) {
+    const long want = (4096 + waves - 1) / waves, most = L3 / 64 > 1 ? L3 / 64 : 1;
+    return (int)(want < 1 ? 1 : (want > most ? most : want));
+}
+
+int contract_ks(const Geo& g, int nt, int units) {
+    return contract_chunks((long)g.Z * g.Y * g.X, (long)std::max(1, nt) * std::max(1, units));
+}
+
+template <bool NOISE> static hipError_t launch_contract_t(ContractArgs a, bool gram, hipStream_t s) {
+    const long nb = (long)a.nt * a.ks * ((a.nunit + 3) / 4);
+    const dim3 grid((unsigned)((nb + 7) / 8 * 8)), block(256);
+    for (a.k0 = 0; a.k0 < a.nev; a.k0 += 32) {
+        const bool one = a.nev - a.k0 <= 16, gr = gram && a.k0 == 0;
+        if (gr && one) hipLaunchKernelGGL((k_contract<NOISE, true, 1>), grid, block, 0, s, a);
+        else if (gr) hipLaunchKernelGGL((k_contract<NOISE, true, 2>), grid, block, 0, s, a);
+        else if (one) hipLaunchKernelGGL((k_contract<NOISE, false, 1>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_contract<NOISE, false, 2>), grid, block, 0, s, a);
+    }
+    return hipGetLastError();
+}
+
+// tau[i] = sum of its ks partials, in order
+__global__ void k_sum_parts(const double2* __restrict__ p, long n, int ks, double2* __restrict__ o) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    double2 v = p[i];
+    for (int k = 1; k < ks; ++k) {
+        const double2 w = p[i + k * n];
+        v.x += w.x;
+        v.y += w.y;
+    }
+    o[i] = v;
+}
+
+hipError_t launch_contract(const ContractArgs& a0, bool noise, bool gram, double2* tau, hipStream_t s) {
+    if (a0.ng <= 0 || a0.nt <= 0) return hipSuccess;
+    ContractArgs a = a0;
+    a.nunit = noise ? a.ng : (a.ng + 1) / 2;
+    a.chunk = ((a.L3 + a.ks - 1) / a.ks + 3) / 4 * 4;  // L3 is a multiple of 8
+    if (a.ks == 1) a.taup = tau;
+    const hipError_t e = noise ? launch_contract_t<true>(a, gram, s) : launch_contract_t<false>(a, gram, s);
+    if (e != hipSuccess || a.ks == 1) return e;
+    const long n = (long)(noise ? 2 : 1) * a.ng * a.nt * a.nev * 16;
+    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.taup, n, a.ks, tau);
+    return hipGetLastError();
+}
+
+// proj[i][j] partials: wave w of block (., timeslice) adds groups w, w + nw, ... of
+// conj(tauA[k][i]) tauB[k][j] over the modes, four modes per matrix instruction (rows
+// past the last mode enter as zero).  A and B are sets oa + st g, ob + st g of tau.
+__global__ void __launch_bounds__(256) k_proj_gram(const double2* __restrict__ tau, int nt, int nev, int ng, int oa, int ob, int st,
+                                                   double2* __restrict__ part) {
+    const int ti = blockIdx.y, nw = gridDim.x * 4, w = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+    const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
+    d4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
+    for (int g = w; g < ng; g += nw) {
+        const double2* A = tau + ((long)(oa + st * g) * nt + ti) * nev * 16 + m;
+        const double2* B = tau + ((long)(ob + st * g) * nt + ti) * nev * 16 + m;
+        for (int k0 = 0; k0 < nev; k0 += 4) {
+            const bool ok = k0 + q < nev;
+            const double2 x = ok ? A[(long)(k0 + q) * 16] : make_double2(0.0, 0.0);
+            const double2 y = ok ? B[(long)(k0 + q) * 16] : make_double2(0.0, 0.0);
+            re = mma64(x.x, y.x, re);
+            im = mma64(x.x, y.y, im);
+            re = mma64(x.y, y.y, re);
+            im = mma64(-x.y, y.x, im);
+        }
+    }
+    store_tile(part + ((long)ti * nw + w) * 256, lane, 16, re, im);
+}
+
+constexpr int PROJ_BLOCKS = 4;  // k_proj_gram blocks per timeslice (16 partials)
+
+// C[gamma][part][delta] from the partial sums of the three Grams and their projected
+// forms, block delta: thread e = (i, j) of four slices adds its entry over the partials,
+// W[gamma][e] holds the piece's spin weights sum_Gamma N[s][s'] M[a][b] / (Gammas).
+__global__ void __launch_bounds__(1024) k_corr_pieces(CorrPiecesArgs a) {
+    __shared__ double2 sm[4][256];
+    __shared__ double lds[16];
+    const int d = blockIdx.x, T = a.T, t = (a.t_src + d) % T;
+    const int e = (int)threadIdx.x & 255, sl = (int)threadIdx.x >> 8;
+    const int eT = (e & 15) * 16 + (e >> 4);
+    // F: 0 dist, 1 (phi, phi), 2 (phibar, phi); [0] whole, [1] projected
+    double2 F[3][2];
+    auto sum = [&](const double2* p, int n, long stride, int ent) {
+        __syncthreads();  // the previous sum has been read
+        double2 v = make_double2(0.0, 0.0);
+        for (int k = sl; k < n; k += 4) {
+            const double2 w = p[k * stride + ent];
+            v.x += w.x;
+            v.y += w.y;
+        }
+        sm[sl][ent] = v;
+        __syncthreads();
+        double2 s = sm[0][ent];
+        for (int k = 1; k < 4; ++k) {
+            s.x += sm[k][ent].x;
+            s.y += sm[k][ent].y;
+        }
+        return s;
+    };
+    auto hermitian = [&](double2 v) {  // (re, X) -> (re, X - X^T)
+        __syncthreads();
+        if (sl == 0) sm[0][e] = v;
+        __syncthreads();
+        return make_double2(v.x, v.y - sm[0][eT].y);
+    };
+    const double2 z = make_double2(0.0, 0.0);
+    for (int k = 0; k < 3; ++k) F[k][0] = F[k][1] = z;
+    const int np = PROJ_BLOCKS * 4;
+    if (a.nud > 0) {
+        F[0][0] = hermitian(sum(a.gd + (long)t * a.nud * 256, a.nud, 256, e));
+        F[0][1] = sum(a.pd + (long)t * np * 256, np, 256, e);
+    }
+    if (a.nun > 0) {
+        F[1][0] = hermitian(sum(a.gn + (long)t * a.nun * 512, a.nun, 512, e));
+        F[2][0] = sum(a.gn + (long)t * a.nun * 512 + 256, a.nun, 512, e);
+        F[1][1] = sum(a.pn + (long)t * np * 256, np, 256, e);
+        F[2][1] = sum(a.pq + (long)t * np * 256, np, 256, e);
+    }
+    auto sub = [](double2 x, double2 y) { return make_double2(x.x - y.x, x.y - y.y); };
+    const double2 piece[DLMA_NPARTS] = {sub(F[2][0], F[2][1]), F[2][1], sub(sub(F[1][0], F[2][0]), sub(F[1][1], F[2][1])),
+                                        sub(F[1][1], F[2][1]), F[1][0], F[0][1], sub(F[0][0], F[0][1])};
+    for (int gi = 0; gi < DLMA_NGAMMA; ++gi) {
+        const double2 w = a.W[gi * 256 + e];
+        const bool on = sl == 0 && (w.x != 0.0 || w.y != 0.0);
+        for (int p = 0; p < DLMA_NPARTS; ++p) {
+            const double2 c = piece[p];
+            const double re = block_sum<1024>(on ? w.x * c.x - w.y * c.y : 0.0, lds);
+            const double im = block_sum<1024>(on ? w.x * c.y + w.y * c.x : 0.0, lds);
+            if (threadIdx.x == 0) {
+                const double s = p < 5 ? a.inv_nvec : 1.0;
+                a.C[((long)gi * DLMA_NPARTS + p) * T + d] = make_double2(re * s, im * s);
+            }
         }
     }
 }
 
-hipError_t launch_tproj(const double2* Vall, const double2* const* fields, int nf, const Geo& g, int nev, double2* P,
-                        hipStream_t s) {
-    long L3 = (long)g.Z * g.Y * g.X;
-    if (nf <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tproj, dim3((nev + 3) / 4, g.T, nf), dim3(256), 0, s, Vall, fields, L3, nev, g.T, P);
+int proj_gram_parts() { return PROJ_BLOCKS * 4; }
+
+hipError_t launch_proj_gram(const double2* tau, int nt, int nev, int ng, int oa, int ob, int st, double2* part, hipStream_t s) {
+    hipLaunchKernelGGL(k_proj_gram, dim3(PROJ_BLOCKS, nt), dim3(256), 0, s, tau, nt, nev, ng, oa, ob, st, part);
     return hipGetLastError();
 }
 
-// one block per (t, pair)
-__global__ void __launch_bounds__(256) k_spin_gram(const double2* const* __restrict__ A, const double2* const* __restrict__ B,
-                                                   long L3, int T, double2* __restrict__ G) {
-    __shared__ double lds[4];
-    int t = blockIdx.x, p = blockIdx.y;
-    const double2* a = A[p] + (long)t * L3 * 12;
-    const double2* b = B[p] + (long)t * L3 * 12;
-    double2 acc[16];
-    for (int i = 0; i < 16; ++i) acc[i] = make_double2(0, 0);
-    for (long m = threadIdx.x; m < L3; m += 256) {
-        double2 av[12], bv[12];
-        for (int i = 0; i < 12; ++i) { av[i] = a[m * 12 + i]; bv[i] = b[m * 12 + i]; }
-        for (int s1 = 0; s1 < 4; ++s1)
-            for (int s2 = 0; s2 < 4; ++s2)
-                for (int c = 0; c < 3; ++c) {
-                    double2 q = cjm(av[s1 * 3 + c], bv[s2 * 3 + c]);
-                    acc[s1 * 4 + s2].x += q.x;
-                    acc[s1 * 4 + s2].y += q.y;
-                }
-    }
-    for (int i = 0; i < 16; ++i) {
-        double re = block_sum<256>(acc[i].x, lds);
-        double im = block_sum<256>(acc[i].y, lds);
-        if (threadIdx.x == 0) G[((long)p * T + t) * 16 + i] = make_double2(re, im);
-    }
-}
-
-hipError_t launch_spin_gram(const double2* const* A, const double2* const* B, int npair, const Geo& g, double2* G,
-                            hipStream_t s) {
-    long L3 = (long)g.Z * g.Y * g.X;
-    if (npair <= 0) return hipSuccess;
-    for (int p0 = 0; p0 < npair; p0 += 65535) {
-        int np = npair - p0 < 65535 ? npair - p0 : 65535;
-        hipLaunchKernelGGL(k_spin_gram, dim3(g.T, np), dim3(256), 0, s, A + p0, B + p0, L3, g.T, G + (long)p0 * g.T * 16);
-    }
+hipError_t launch_corr_pieces(const CorrPiecesArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_corr_pieces, dim3(a.T), dim3(1024), 0, s, a);
     return hipGetLastError();
 }
-
 
 // ---------------------------------------------------------------- backward of the contractions
 //
@@ -100,85 +297,144 @@ hipError_t launch_spin_gram(const double2* const* A, const double2* const* B, in
 //   grad(t, x) = W1(t) F(t, x) + WP(t) (box(t) F)(t, x),
 // with F the group's input fields stacked with their spin components, W1 and WP spin
 // matrices that combine the loss weights, Gamma, g5 and the normalisations (the same
-// for every group), and box(t) F = sum_k v_k(t) tau_k, tau = V(t)^dag F.  The host
-// folds WP into tau' = WP tau; this kernel forms W1 F + sum_k v_k tau'_k for one
-// output chunk (four output fields of one group) at 256 rows (site, colour) of one
-// timeslice per block.  W1 rows and tau' of the chunk are staged in LDS.
-__global__ void __launch_bounds__(256) k_corr_grad(CorrGradArgs a) {
-    __shared__ double2 w1s[16 * 32];  // W1 rows of the chunk's 16 outputs, over <= 32 inputs
-    __shared__ double2 tps[64 * 16];  // tau'[k][16 outputs] for 64 modes at a time
-    const int t = blockIdx.y, z = blockIdx.z;
-    const bool noise = z < 2 * a.nnoise;
-    const int grp = noise ? z >> 1 : z - 2 * a.nnoise;
-    const int half = noise ? (z & 1) : 0;
-    const int nin = noise ? 32 : 16;  // input (field, spin) columns of a group
-    const int ta = a.tact[t];         // uniform: the block's timeslice carries weights or not
-    const long L3 = a.L3;
-    const long row = (long)blockIdx.x * 256 + threadIdx.x;
-    const bool valid = row < L3 * 3;
-    const long x = valid ? row / 3 : 0;
-    const int c = (int)(valid ? row - x * 3 : 0);
-    const long site = ((long)t * L3 + x) * 12 + c;  // offset of (spin 0, colour c) in a field
-    double2 acc[16];
+// for every group), and box(t) F = sum_k v_k(t) tau_k, tau = V(t)^dag F.  k_tau_weights
+// folds WP into tau' = WP tau; k_corr_grad forms W1 F + sum_k v_k tau'_k.
+
+// tau'[grp][ta][k][row] = sum_col WP(t)[row][col] tau_col[k], the columns of a group being
+// its sets' 16 columns in turn (noise: phi then phibar).  One thread per (k, row).
+template <int N>
+__global__ void __launch_bounds__(256) k_tau_weights(const double2* __restrict__ tau, const double2* __restrict__ WP,
+                                                     const int* __restrict__ tlist, int nact, int nev, double2* __restrict__ o) {
+    const int row = (int)threadIdx.x % N, k = blockIdx.x * (256 / N) + (int)threadIdx.x / N;
+    const int ta = blockIdx.y, grp = blockIdx.z;
+    if (k >= nev) return;
+    const double2* W = WP + ((long)tlist[ta] * N + row) * N;
+    double2 v = make_double2(0.0, 0.0);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = make_double2(0.0, 0.0);
-    if (ta >= 0) {
-        const double2* W1 = noise ? a.W1n + ((long)t * 32 + half * 16) * 32 : a.W1d + (long)t * 16 * 16;
-        for (int i = threadIdx.x; i < 16 * nin; i += 256) w1s[i] = W1[i];
-        __syncthreads();
-        if (valid) {
-            for (int j = 0; j < nin / 4; ++j) {
-                const double2* f = noise ? (j < 4 ? a.phi + ((long)grp * 4 + j) * a.fs : a.phibar + ((long)grp * 4 + j - 4) * a.fs)
-                                         : a.dist + ((long)grp * 4 + j) * a.fs;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const double2 v = f[site + b * 3];
-                    const int col = j * 4 + b;
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        const double2 w = w1s[q * nin + col];
-                        acc[q].x += w.x * v.x - w.y * v.y;
-                        acc[q].y += w.x * v.y + w.y * v.x;
-                    }
-                }
-            }
-        }
-        const double2* tp = noise ? a.taun + (((long)grp * a.nact + ta) * a.nev) * 32 + half * 16
-                                  : a.taud + (((long)grp * a.nact + ta) * a.nev) * 16;
-        const int tstride = noise ? 32 : 16;
-        const double2* vk = a.Vall + (long)t * a.nev * L3 * 3 + (valid ? row : 0);
-        for (int k0 = 0; k0 < a.nev; k0 += 64) {
-            const int nk = a.nev - k0 < 64 ? a.nev - k0 : 64;
-            __syncthreads();  // the previous chunk (or W1) has been read by every thread
-            for (int i = threadIdx.x; i < nk * 16; i += 256) tps[i] = tp[(long)(k0 + (i >> 4)) * tstride + (i & 15)];
-            __syncthreads();
-            if (valid) {
-                for (int k = 0; k < nk; ++k) {
-                    const double2 v = vk[(long)(k0 + k) * L3 * 3];
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        const double2 w = tps[k * 16 + q];
-                        acc[q].x += w.x * v.x - w.y * v.y;
-                        acc[q].y += w.x * v.y + w.y * v.x;
-                    }
-                }
-            }
+    for (int s = 0; s < N / 16; ++s) {
+        const double2* p = tau + ((((long)grp * (N / 16) + s) * nact + ta) * nev + k) * 16;
+        for (int c = 0; c < 16; ++c) {
+            const double2 w = W[s * 16 + c], x = p[c];
+            if (w.x == 0.0 && w.y == 0.0) continue;  // no weight: the column does not enter
+            v.x += w.x * x.x - w.y * x.y;
+            v.y += w.x * x.y + w.y * x.x;
         }
     }
-    if (!valid) return;
+    o[(((long)grp * nact + ta) * nev + k) * N + row] = v;
+}
+
+hipError_t launch_tau_weights(const double2* tau, const double2* WP, const int* tlist, int nact, int nev, int ngrp, bool noise,
+                              double2* o, hipStream_t s) {
+    if (ngrp <= 0 || nact <= 0) return hipSuccess;
+    const int per = noise ? 8 : 16;
+    const dim3 grid((nev + per - 1) / per, nact, ngrp);
+    if (noise) hipLaunchKernelGGL(k_tau_weights<32>, grid, dim3(256), 0, s, tau, WP, tlist, nact, nev, o);
+    else hipLaunchKernelGGL(k_tau_weights<16>, grid, dim3(256), 0, s, tau, WP, tlist, nact, nev, o);
+    return hipGetLastError();
+}
+
+// Gradient fields of one unit (two distillation groups, or phi and phibar of a noise
+// group) on 32 rows (site, colour) of a timeslice per wave: a matrix product over the
+// group's (field, spin) inputs, then over the modes, on FP64 matrix instructions.  Rows
+// are the A operand (of V: 256 contiguous bytes per mode), the 16 outputs (field, spin)
+// of each of the unit's two halves the columns, so V is read once for both halves.
+// Bound: the matrix cores and the field streams alike.  At 12^3 x 24 with 21 modes,
+// 13 distillation and 6 noise groups forward and backward together took 20.9 ms (tau and
+// tau' on the host, a VALU kernel here), 2.50 ms with the projections above, 1.89 ms so.
+template <bool NOISE>
+__global__ void __launch_bounds__(256) k_corr_grad(CorrGradArgs a) {
+    constexpr int NIN = NOISE ? 32 : 16;
+    const int t = blockIdx.y, unit = blockIdx.z;
+    const int g0 = NOISE ? unit : 2 * unit;
+    const bool two = NOISE || g0 + 1 < a.ndist;
+    const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
+    const long L3 = a.L3, nrow = L3 * 3;
+    const long r0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
+    if (r0 >= nrow) return;  // whole waves
+    const int ta = a.tact[t];  // uniform: the timeslice carries weights or not
+    d4 re[2][2], im[2][2];  // [half][row tile]
+    const d4 z = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        double2* o = noise ? (half == 0 ? a.gphi : a.gphibar) + ((long)grp * 4 + i) * a.fs : a.gdist + ((long)grp * 4 + i) * a.fs;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) o[site + s * 3] = acc[i * 4 + s];
+        for (int b = 0; b < 2; ++b) re[h][b] = im[h][b] = z;
+    const long tofs = (long)t * L3 * 12;
+    if (ta >= 0) {
+        // operand rows of this lane (past the last row: the last one, not stored)
+        long row[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const long r = r0 + 16 * b + m;
+            row[b] = r < nrow ? r : nrow - 1;
+        }
+        auto mac = [&](int h, int b, double2 x, double2 w) {
+            re[h][b] = mma64(x.x, w.x, re[h][b]);
+            im[h][b] = mma64(x.x, w.y, im[h][b]);
+            re[h][b] = mma64(-x.y, w.y, re[h][b]);
+            im[h][b] = mma64(x.y, w.x, im[h][b]);
+        };
+        // W1 F: inputs (field j, spin q)
+        const double2* W = (NOISE ? a.W1n : a.W1d) + (long)t * NIN * NIN + (long)m * NIN + q;
+        const long f0 = tofs + row[0] / 3 * 12 + row[0] % 3 + q * 3, f1 = tofs + row[1] / 3 * 12 + row[1] % 3 + q * 3;
+#pragma unroll
+        for (int j = 0; j < NIN / 4; ++j) {
+            if (NOISE) {
+                const double2* f = (j < 4 ? a.phi : a.phibar) + ((long)g0 * 4 + (j & 3)) * a.fs;
+                const double2 x0 = f[f0], x1 = f[f1], w0 = W[j * 4], w1 = W[16 * NIN + j * 4];
+                mac(0, 0, x0, w0);
+                mac(0, 1, x1, w0);
+                mac(1, 0, x0, w1);
+                mac(1, 1, x1, w1);
+            } else {
+                const double2 w = W[j * 4];
+                const double2* f = a.dist + ((long)g0 * 4 + j) * a.fs;
+                mac(0, 0, f[f0], w);
+                mac(0, 1, f[f1], w);
+                if (two) {
+                    f += 4 * a.fs;
+                    mac(1, 0, f[f0], w);
+                    mac(1, 1, f[f1], w);
+                }
+            }
+        }
+        // V tau': four modes at a time (past the last: zero)
+        const double2* v = a.Vall + ((long)t * a.nev + q) * nrow;
+        const long ts = (long)a.nact * a.nev * 16;
+        const double2* tp = NOISE ? a.taun + (((long)g0 * a.nact + ta) * a.nev + q) * 32 + m
+                                  : a.taud + (((long)g0 * a.nact + ta) * a.nev + q) * 16 + m;
+        for (int k = 0; k < a.nev; k += 4) {
+            const bool ok = k + q < a.nev;
+            const double2 zz = make_double2(0.0, 0.0);
+            const double2 x0 = ok ? v[(long)k * nrow + row[0]] : zz, x1 = ok ? v[(long)k * nrow + row[1]] : zz;
+            const double2 w0 = ok ? tp[(long)k * NIN] : zz;
+            const double2 w1 = ok && two ? (NOISE ? tp[(long)k * NIN + 16] : tp[(long)k * NIN + ts]) : zz;
+            mac(0, 0, x0, w0);
+            mac(0, 1, x1, w0);
+            mac(1, 0, x0, w1);
+            mac(1, 1, x1, w1);
+        }
+    }
+    // result register i of this lane: row 4 i + q, output m = (field, spin)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h == 1 && !two) break;
+        double2* o = (NOISE ? (h == 0 ? a.gphi : a.gphibar) + ((long)g0 * 4 + (m >> 2)) * a.fs
+                            : a.gdist + ((long)(g0 + h) * 4 + (m >> 2)) * a.fs) + tofs + (m & 3) * 3;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const long r = r0 + 16 * b + 4 * i + q;
+                if (r < nrow) o[r / 3 * 12 + r % 3] = make_double2(re[h][b][i], im[h][b][i]);
+            }
     }
 }
 
 hipError_t launch_corr_grad(const CorrGradArgs& a, int T, hipStream_t s) {
-    const int nchunk = 2 * a.nnoise + a.ndist;  // grid z: the callers keep it below 65536
-    if (nchunk <= 0) return hipSuccess;
-    if (nchunk > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_corr_grad, dim3((unsigned)((a.L3 * 3 + 255) / 256), T, nchunk), dim3(256), 0, s, a);
+    if (2L * a.nnoise + a.ndist > 65535) return hipErrorInvalidValue;  // the callers keep the grids below this
+    const unsigned nb = (unsigned)((a.L3 * 3 + 127) / 128);
+    if (a.ndist > 0) hipLaunchKernelGGL(k_corr_grad<false>, dim3(nb, T, (a.ndist + 1) / 2), dim3(256), 0, s, a);
+    if (a.nnoise > 0) hipLaunchKernelGGL(k_corr_grad<true>, dim3(nb, T, a.nnoise), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 // Launchers of the Laplacian, Lanczos, projector and contraction kernels.
 #pragma once
+#include "../../include/dlma.h"
 #include "kernels.h"
 
 namespace dlma {
@@ -50,8 +51,36 @@ hipError_t launch_project(const double2* Vt, const double2* in, double2* out, co
                           double2* coef, hipStream_t s);
 
 // contractions
-hipError_t launch_tproj(const double2* Vall, const double2* const* fields, int nf, const Geo& g, int nev, double2* P,
-                        hipStream_t s);
+// Column sets of 16 (label, spin) columns per source group: the groups of f0, or with
+// noise the phi (f0) and phibar (f1) of each group in turn (sets 2 g, 2 g + 1).
+struct ContractArgs {
+    const double2 *Vall, *f0, *f1;
+    long L3, fs;       // sites of a timeslice, complex numbers of a field
+    const int* tlist;  // the nt timeslices, nullptr = 0 .. nt - 1
+    int nt, nev, ng, ks;
+    double2* taup;     // partials [ks][set][nt][nev][16] (unused with ks = 1)
+    double2* gramp;    // [nt][ks][unit][noise ? 2 : 1][16][16]: (re, X) of (f0, f0), then (f1, f0)
+    int nunit, k0;     // set by the launcher
+    long chunk;
+};
+int contract_ks(const Geo& g, int nt, int units);
+// tau[set][nt][nev][16], and with gram the Gram partials of nunit = noise ? ng : (ng + 1) / 2 units
+hipError_t launch_contract(const ContractArgs& a, bool noise, bool gram, double2* tau, hipStream_t s);
+// part[nt][proj_gram_parts()][16][16] of sum_g sum_k conj(tau[oa + st g]) tau[ob + st g]
+int proj_gram_parts();
+hipError_t launch_proj_gram(const double2* tau, int nt, int nev, int ng, int oa, int ob, int st, double2* part, hipStream_t s);
+struct CorrPiecesArgs {
+    const double2 *gd, *pd;         // dist: Gram partials [T][nud], projected partials
+    const double2 *gn, *pn, *pq;    // noise: Gram partials [T][nun][2], projected (phi, phi) and (phibar, phi)
+    const double2* W;               // [DLMA_NGAMMA][16][16] spin weights
+    double2* C;                     // [DLMA_NGAMMA][DLMA_NPARTS][T]
+    double inv_nvec;
+    int T, t_src, nud, nun;
+};
+hipError_t launch_corr_pieces(const CorrPiecesArgs& a, hipStream_t s);
+// tau' = WP tau for ngrp groups of N = noise ? 32 : 16 columns, WP [T][N][N]
+hipError_t launch_tau_weights(const double2* tau, const double2* WP, const int* tlist, int nact, int nev, int ngrp, bool noise,
+                              double2* o, hipStream_t s);
 // backward of the correlator contractions (see contract.hip)
 struct CorrGradArgs {
     const double2* Vall;                       // [T][nev][L3][3]
@@ -66,7 +95,5 @@ struct CorrGradArgs {
     int nev, ndist, nnoise, nact;
 };
 hipError_t launch_corr_grad(const CorrGradArgs& a, int T, hipStream_t s);
-hipError_t launch_spin_gram(const double2* const* A, const double2* const* B, int npair, const Geo& g, double2* G,
-                            hipStream_t s);
 
 }  // namespace dlma
