@@ -818,8 +818,8 @@ extern "C" int dlma_dot(const void* a, const void* b, long n, double* out, void*
     if (n < 0) return fail(DLMA_EINVAL, "n < 0");
     hipStream_t s = S(stream);
     Buf r;
-    DLMA_TRY(r.allocate(sizeof(double2)));
-    DLMA_HIP(launch_dots((const double2*)a, 0, 0, (const double2*)b, 0, n, r.as<double2>(), 1, 1, 1, s));
+    DLMA_TRY(r.allocate(sizeof(double2) * (1 + dot_parts(n))));
+    DLMA_HIP(launch_dot((const double2*)a, (const double2*)b, n, r.as<double2>() + 1, r.as<double2>(), s));
     double2 h;
     DLMA_HIP(hipMemcpyAsync(&h, r.p, sizeof(double2), hipMemcpyDeviceToHost, s));
     DLMA_HIP(hipStreamSynchronize(s));

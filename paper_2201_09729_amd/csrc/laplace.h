@@ -16,8 +16,9 @@ hipError_t launch_cheb_step(const double2* U64, const Geo& g, int t0, const doub
                             double2* out, long tso, int nt, double c1, double c2, hipStream_t s, const double2* qd = nullptr,
                             long tsqd = 0, double* part = nullptr);
 hipError_t launch_rayleigh(const double2* y, const double2* ay, long n, int nvec, double* lam, double* res, hipStream_t s);
-hipError_t launch_dots(const double2* a, long tsa, long isa, const double2* b, long tsb, long n, double2* out, int ostride,
-                       int ni, int nt, hipStream_t s);
+// <a, b> over n complex numbers; part: dot_parts(n) numbers
+int dot_parts(long n);
+hipError_t launch_dot(const double2* a, const double2* b, long n, double2* part, double2* out, hipStream_t s);
 // Lanczos step with split reductions: alpha from the stencil's partials (nap per
 // timeslice), Gram-Schmidt dots in GS_NCH element chunks, |w|^2 partials from the last
 // subtraction (gs_sub_blocks(n) per timeslice) consumed by the normalisation.  prev =
