@@ -29,14 +29,23 @@ static int check_dims(const int* dims) {
     return DLMA_OK;
 }
 
-static int invert_clover(Gauge* g, hipStream_t s) {
+// A_oo^-1 from A_oo; *bits (host, may be NULL) also receives the 8 bytes at `worst` (device),
+// read with the inversion's error flag after one synchronisation
+static int invert_clover(Gauge* g, hipStream_t s, const void* worst = nullptr, unsigned long long* bits = nullptr) {
     Buf err;
     DLMA_TRY(err.allocate(sizeof(int)));
     DLMA_HIP(hipMemsetAsync(err.p, 0, sizeof(int), s));
     DLMA_HIP(launch_clover_invert(g->Cl64[1].as<double2>(), g->Ci64.as<double2>(), g->Vh, err.as<int>(), s));
     int h = 0;
+    if (bits) DLMA_HIP(hipMemcpyAsync(bits, worst, sizeof(*bits), hipMemcpyDeviceToHost, s));
     DLMA_HIP(hipMemcpyAsync(&h, err.p, sizeof(int), hipMemcpyDeviceToHost, s));
     DLMA_HIP(hipStreamSynchronize(s));
+    if (bits) {
+        double m;
+        std::memcpy(&m, bits, sizeof(m));
+        if (!(m <= 1e-10))
+            return fail(DLMA_EINVAL, "links are not unitary to 1e-10 (max |U U^dag - 1| = " + std::to_string(m) + ")");
+    }
     if (h) return fail(DLMA_EINVAL, "clover block not positive definite (kappa/csw out of range for this field)");
     for (int p = 1; p < 4; ++p) g->lo_ready[p] = false;
     return DLMA_OK;
@@ -58,30 +67,21 @@ extern "C" int dlma_load_gauge(const int dims[4], const void* U_dev, double kapp
     g->csw = csw;
     auto bad = [&](int rc) { delete g; return rc; };
     const double2* Uc = (const double2*)U_dev;
-    // unitarity and finiteness of every link
-    {
-        long nlink = g->V * 4;
-        int nblk = ceil_div(nlink, 256);
-        Buf bm;
-        if (int rc = bm.allocate(sizeof(double) * nblk)) return bad(rc);
-        if (launch_unitarity(Uc, nlink, bm.as<double>(), nblk, s) != hipSuccess) return bad(fail(DLMA_EHIP, "unitarity kernel launch failed"));
-        std::vector<double> h(nblk);
-        if (hipMemcpyAsync(h.data(), bm.p, sizeof(double) * nblk, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return bad(fail(DLMA_EHIP, "reading the unitarity check failed"));
-        double m = 0;
-        for (double v : h) m = std::max(m, v);
-        if (!(m <= 1e-10)) return bad(fail(DLMA_EINVAL, "links are not unitary to 1e-10 (max |U U^dag - 1| = " + std::to_string(m) + ")"));
-    }
+    Buf worst;
+    if (int rc = worst.allocate(sizeof(unsigned long long))) return bad(rc);
     if (int rc = g->U64.allocate(sizeof(double2) * 2L * 4 * 9 * g->Vh)) return bad(rc);
     if (int rc = g->Cl64[0].allocate(sizeof(double2) * 2L * 18 * g->Vh)) return bad(rc);
     if (int rc = g->Cl64[1].allocate(sizeof(double2) * 2L * 18 * g->Vh)) return bad(rc);
     if (int rc = g->Ci64.allocate(sizeof(double2) * 2L * 18 * g->Vh)) return bad(rc);
-    if (launch_pack_links(Uc, g->U64.as<double2>(), g->geo, s) != hipSuccess) return bad(fail(DLMA_EHIP, "link packing failed"));
+    // packing, with the unitarity and finiteness of every link
+    if (hipMemsetAsync(worst.p, 0, sizeof(unsigned long long), s) != hipSuccess ||
+        launch_ingest(Uc, g->U64.as<double2>(), g->geo, worst.as<unsigned long long>(), s) != hipSuccess)
+        return bad(fail(DLMA_EHIP, "link packing failed"));
     double m0 = 1.0 / (2.0 * kappa) - 4.0;
-    if (launch_clover_build(Uc, g->geo, m0, csw, g->Cl64[0].as<double2>(), g->Cl64[1].as<double2>(), s) != hipSuccess)
+    if (launch_clover_build(g->U64.as<double2>(), g->geo, m0, csw, g->Cl64[0].as<double2>(), g->Cl64[1].as<double2>(), s) != hipSuccess)
         return bad(fail(DLMA_EHIP, "clover construction failed"));
-    if (int rc = invert_clover(g, s)) return bad(rc);
+    unsigned long long bits = 0;
+    if (int rc = invert_clover(g, s, worst.p, &bits)) return bad(rc);
     *out = (dlma_gauge_t)g;
     return DLMA_OK;
 }

@@ -13,13 +13,6 @@ HD C64 cconj(C64 a) { return {a.r, -a.i}; }
 
 struct M3 { C64 m[9]; };
 
-HD M3 ldU(const double2* U, long site, int mu) {
-    M3 o;
-    const double2* p = U + (site * 4 + mu) * 9;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) { double2 v = p[k]; o.m[k] = {v.x, v.y}; }
-    return o;
-}
 HD M3 dagm(const M3& a) {
     M3 o;
 #pragma unroll
@@ -56,155 +49,183 @@ HD int ext(const Geo& g, int mu) { return mu == 0 ? g.T : (mu == 1 ? g.X : (mu =
 HD long site_of(const Geo& g, Coord c) {
     return (((long)c.c[0] * g.Z + c.c[3]) * g.Y + c.c[2]) * g.X + c.c[1];
 }
-HD Coord shift(const Geo& g, Coord c, int mu, int d) {
-    int L = ext(g, mu);
-    c.c[mu] = (c.c[mu] + d + L) % L;
-    return c;
-}
 
-// ---------------------------------------------------------------- gauge packing
+// ---------------------------------------------------------------- gauge ingest
 
-__global__ void k_pack_links(const double2* __restrict__ Ucan, double2* __restrict__ U64, Geo g) {
-    long V = 2L * g.Vh;
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= V * 4) return;
-    long s = i >> 2;
-    int mu = (int)(i & 3);
-    Coord c = coord_of(g, s);
-    int par = (c.c[0] + c.c[1] + c.c[2] + c.c[3]) & 1;
-    long cb = s >> 1;  // ((t*Z+z)*Y+y)*Xh + x/2 since X is even
-    for (int k = 0; k < 9; ++k) U64[((size_t)(par * 4 + mu) * 9 + k) * g.Vh + cb] = Ucan[(s * 4 + mu) * 9 + k];
-}
-
-hipError_t launch_pack_links(const double2* Ucan, double2* U64, const Geo& g, hipStream_t s) {
-    long n = 2L * g.Vh * 4;
-    hipLaunchKernelGGL(k_pack_links, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, Ucan, U64, g);
-    return hipGetLastError();
-}
-
-// per block: max over its links of max_ij |(U U^dag - 1)_ij| (NaN propagates as +inf)
-__global__ void k_unitarity(const double2* __restrict__ Ucan, long nlink, double* __restrict__ blockmax) {
-    __shared__ double sm[256];
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+// Packs the links of 64 consecutive sites per block into the even-odd planes and takes
+// the maximum of max_ij |(U U^dag - 1)_ij| over them (NaN counts as +inf).  The canonical
+// links pass through LDS as one contiguous 36 KB span; lane l of wave mu then holds the
+// site of parity l / 32 in pair l % 32, so every plane is written in runs of 32 sites.
+// One read and one write of the links: bound by HBM.  As two kernels with a thread per
+// link the pair took 215 us at 24^3 x 48 (0.76 GB); 172 us so.
+constexpr int INGEST_SITES = 64, INGEST_STRIDE = 37;  // padded: the links of a site, 36 numbers
+__global__ void __launch_bounds__(256) k_ingest(const double2* __restrict__ Ucan, double2* __restrict__ U64, Geo g,
+                                                unsigned long long* __restrict__ worst) {
+    __shared__ double2 buf[INGEST_SITES * INGEST_STRIDE];
+    const long V = 2L * g.Vh, s0 = (long)blockIdx.x * INGEST_SITES;
+    const int ns = (int)(V - s0 < INGEST_SITES ? V - s0 : INGEST_SITES);  // even
+    for (int e = threadIdx.x; e < ns * 36; e += 256) buf[e / 36 * INGEST_STRIDE + e % 36] = Ucan[s0 * 36 + e];
+    __syncthreads();
+    const int mu = (int)threadIdx.x >> 6, l = (int)threadIdx.x & 63, p = l & 31, par = l >> 5;
     double m = 0.0;
-    if (i < nlink) {
+    if (2 * p < ns) {
+        const Coord c = coord_of(g, s0 + 2 * p);
+        const int site = 2 * p + (((c.c[0] + c.c[1] + c.c[2] + c.c[3]) & 1) ^ par);
         M3 u;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) { double2 v = Ucan[i * 9 + k]; u.m[k] = {v.x, v.y}; }
-        M3 p = mulm(u, dagm(u));
+        for (int k = 0; k < 9; ++k) {
+            const double2 v = buf[site * INGEST_STRIDE + mu * 9 + k];
+            u.m[k] = {v.x, v.y};
+            U64[((size_t)(par * 4 + mu) * 9 + k) * g.Vh + (s0 >> 1) + p] = v;
+        }
+        const M3 w = mulm(u, dagm(u));
+#pragma unroll
         for (int a = 0; a < 3; ++a)
+#pragma unroll
             for (int b = 0; b < 3; ++b) {
-                double re = p.m[a * 3 + b].r - (a == b ? 1.0 : 0.0), im = p.m[a * 3 + b].i;
-                double e = fabs(re) + fabs(im);
+                double e = fabs(w.m[a * 3 + b].r - (a == b ? 1.0 : 0.0)) + fabs(w.m[a * 3 + b].i);
                 if (!(e == e) || isinf(e)) e = INFINITY;
                 m = fmax(m, e);
             }
     }
-    sm[threadIdx.x] = m;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) sm[threadIdx.x] = fmax(sm[threadIdx.x], sm[threadIdx.x + st]);
-        __syncthreads();
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    // non-negative doubles order like their bits; almost every wave finds a larger value there
+    if (l == 0) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(m);
+        if (b > *(volatile unsigned long long*)worst) atomicMax(worst, b);
     }
-    if (threadIdx.x == 0) blockmax[blockIdx.x] = sm[0];
 }
 
-hipError_t launch_unitarity(const double2* Ucan, long nlink, double* blockmax, int nblk, hipStream_t s) {
-    hipLaunchKernelGGL(k_unitarity, dim3(nblk), dim3(256), 0, s, Ucan, nlink, blockmax);
+hipError_t launch_ingest(const double2* Ucan, double2* U64, const Geo& g, unsigned long long* worst, hipStream_t s) {
+    const long V = 2L * g.Vh;
+    hipLaunchKernelGGL(k_ingest, dim3((unsigned)((V + INGEST_SITES - 1) / INGEST_SITES)), dim3(256), 0, s, Ucan, U64, g, worst);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- clover
 
-// Four-leaf clover Q_{mu nu}(x): the four plaquettes of the (mu,nu) plane touching x,
-// each traversed counter-clockwise from x.
-HD M3 leaves(const double2* U, const Geo& g, Coord x, int mu, int nu) {
-    long sx = site_of(g, x);
-    Coord xpm = shift(g, x, mu, 1), xpn = shift(g, x, nu, 1);
-    Coord xmm = shift(g, x, mu, -1), xmn = shift(g, x, nu, -1);
-    Coord xmm_pn = shift(g, xmm, nu, 1), xmm_mn = shift(g, xmm, nu, -1), xmn_pm = shift(g, xmn, mu, 1);
-    long s_pm = site_of(g, xpm), s_pn = site_of(g, xpn), s_mm = site_of(g, xmm), s_mn = site_of(g, xmn);
-    long s_mmpn = site_of(g, xmm_pn), s_mmmn = site_of(g, xmm_mn), s_mnpm = site_of(g, xmn_pm);
-    M3 Q;
-    M3 t = mulm(mulm(ldU(U, sx, mu), ldU(U, s_pm, nu)), mulm(dagm(ldU(U, s_pn, mu)), dagm(ldU(U, sx, nu))));
-    Q = t;
-    t = mulm(mulm(ldU(U, sx, nu), dagm(ldU(U, s_mmpn, mu))), mulm(dagm(ldU(U, s_mm, nu)), ldU(U, s_mm, mu)));
-    for (int k = 0; k < 9; ++k) Q.m[k] = cadd(Q.m[k], t.m[k]);
-    t = mulm(mulm(dagm(ldU(U, s_mm, mu)), dagm(ldU(U, s_mmmn, nu))), mulm(ldU(U, s_mmmn, mu), ldU(U, s_mn, nu)));
-    for (int k = 0; k < 9; ++k) Q.m[k] = cadd(Q.m[k], t.m[k]);
-    t = mulm(mulm(dagm(ldU(U, s_mn, nu)), ldU(U, s_mn, mu)), mulm(ldU(U, s_mnpm, nu), dagm(ldU(U, sx, mu))));
-    for (int k = 0; k < 9; ++k) Q.m[k] = cadd(Q.m[k], t.m[k]);
-    return Q;
-}
-
 // A(x) in the chiral basis splits into two 6x6 blocks (spins 0,1 and spins 2,3):
 //   block = (4+m0) 1 + csw (i/2) [[B3, B1 - i B2], [B1 + i B2, -B3]]  (2x2 in spin, 3x3 in colour)
 // upper: B1 = F01 - F23, B2 = F02 + F13, B3 = F03 - F12
 // lower: B1 = -F01 - F23, B2 = -F02 + F13, B3 = -F03 - F12
-// (from sigma_0k = diag(sk, -sk) and sigma_jk = -eps_jkl diag(sl, sl) in this basis).
-HD void clover_site(const double2* U, const Geo& g, double m0, double csw, double2* C0, double2* C1, long s) {
-    Coord x = coord_of(g, s);
-    M3 F[6];
-    int p = 0;
-    for (int mu = 0; mu < 4; ++mu)
-        for (int nu = mu + 1; nu < 4; ++nu, ++p) {
-            M3 Q = leaves(U, g, x, mu, nu);
-            for (int a = 0; a < 3; ++a)
-                for (int b = 0; b < 3; ++b) {
-                    C64 q = Q.m[a * 3 + b], qt = cconj(Q.m[b * 3 + a]);
-                    F[p].m[a * 3 + b] = {(q.r - qt.r) / 8.0, (q.i - qt.i) / 8.0};
-                }
+// (from sigma_0k = diag(sk, -sk) and sigma_jk = -eps_jkl diag(sl, sl) in this basis), with
+// F = (Q - Q^dag)/8 of the four-leaf clover Q: the four plaquettes of the (mu, nu) plane
+// touching x, each traversed counter-clockwise from x.
+//
+// A block covers 64 checkerboard sites of one parity; wave p takes plane p (01, 02, 03, 12,
+// 13, 23), so the plane is uniform and a thread holds one Q in registers; the F of the six
+// planes meet in LDS and each wave writes 6 of the 36 packed pairs.  The links come from
+// the packed planes (consecutive sites on consecutive lanes).  Bound: L2 reads of the 12
+// links per plane (1.7 KB per site and plane) and FP64 products about equally.  One
+// thread per site with its six F in scratch, reading the canonical links, took 2504 us at
+// 24^3 x 48; 698 us so (224 registers, one block of six waves per CU; forced to 168
+// registers it spills and takes 864 to 932 us).
+constexpr int CLOVER_SITES = 64;
+
+__device__ __forceinline__ M3 link_at(const double2* __restrict__ U64, const Geo& g, const Coord& c, int mu) {
+    const int par = (c.c[0] + c.c[1] + c.c[2] + c.c[3]) & 1;
+    const double2* b = U64 + (size_t)(par * 4 + mu) * 9 * g.Vh + (site_of(g, c) >> 1);
+    M3 o;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const double2 v = b[(size_t)k * g.Vh];
+        o.m[k] = {v.x, v.y};
+    }
+    return o;
+}
+
+// c moved by one in direction mu (periodic), without indexing the coordinates by a variable
+__device__ __forceinline__ Coord step(const Geo& g, Coord c, int mu, int d) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int L = ext(g, k), v = c.c[k] + d, w = v < 0 ? L - 1 : (v == L ? 0 : v);
+        c.c[k] = k == mu ? w : c.c[k];
+    }
+    return c;
+}
+
+__global__ void __launch_bounds__(6 * CLOVER_SITES)
+k_clover_build(const double2* __restrict__ U64, Geo g, double m0, double csw, double2* __restrict__ C0, double2* __restrict__ C1) {
+    __shared__ double2 F[6][9][CLOVER_SITES];
+    const int par = blockIdx.y, lane = (int)threadIdx.x & 63, p = wave_uniform((int)threadIdx.x >> 6);
+    const int cb = (int)blockIdx.x * CLOVER_SITES + lane;
+    const bool ok = cb < g.Vh;
+    if (ok) {
+        const int mu = p < 3 ? 0 : (p < 5 ? 1 : 2), nu = p < 3 ? p + 1 : (p < 5 ? p - 1 : 3);
+        Coord x;
+        {
+            const uint32_t r1 = mdiv(cb, g.mXh), r2 = mdiv(r1, g.mY), t = mdiv(r2, g.mZ);
+            const int xh = cb - (int)r1 * g.Xh;
+            x.c[2] = (int)r1 - (int)r2 * g.Y;
+            x.c[3] = (int)r2 - (int)t * g.Z;
+            x.c[0] = (int)t;
+            x.c[1] = 2 * xh + ((x.c[0] + x.c[2] + x.c[3] + par) & 1);
         }
-    // planes: 0:01 1:02 2:03 3:12 4:13 5:23
-    int par = (x.c[0] + x.c[1] + x.c[2] + x.c[3]) & 1;
-    long cb = s >> 1;
+        const Coord xm = step(g, x, mu, -1), xn = step(g, x, nu, -1), xmn = step(g, xm, nu, -1);
+        M3 Q;
+        {
+            const Coord a = step(g, x, mu, 1), b = step(g, x, nu, 1);
+            Q = mulm(mulm(link_at(U64, g, x, mu), link_at(U64, g, a, nu)),
+                     mulm(dagm(link_at(U64, g, b, mu)), dagm(link_at(U64, g, x, nu))));
+        }
+        auto add = [&](const M3& t) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) Q.m[k] = cadd(Q.m[k], t.m[k]);
+        };
+        add(mulm(mulm(link_at(U64, g, x, nu), dagm(link_at(U64, g, step(g, xm, nu, 1), mu))),
+                 mulm(dagm(link_at(U64, g, xm, nu)), link_at(U64, g, xm, mu))));
+        add(mulm(mulm(dagm(link_at(U64, g, xm, mu)), dagm(link_at(U64, g, xmn, nu))),
+                 mulm(link_at(U64, g, xmn, mu), link_at(U64, g, xn, nu))));
+        add(mulm(mulm(dagm(link_at(U64, g, xn, nu)), link_at(U64, g, xn, mu)),
+                 mulm(link_at(U64, g, step(g, xn, mu, 1), nu), dagm(link_at(U64, g, x, mu)))));
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const C64 q = Q.m[a * 3 + b], qt = cconj(Q.m[b * 3 + a]);
+                F[p][a * 3 + b][lane] = make_double2((q.r - qt.r) / 8.0, (q.i - qt.i) / 8.0);
+            }
+    }
+    __syncthreads();
+    if (!ok) return;
     double2* C = par ? C1 : C0;
-    for (int blk = 0; blk < 2; ++blk) {
-        double sg = blk == 0 ? 1.0 : -1.0;
-        C64 B[3][9];
-        for (int k = 0; k < 9; ++k) {
-            B[0][k] = {sg * F[0].m[k].r - F[5].m[k].r, sg * F[0].m[k].i - F[5].m[k].i};
-            B[1][k] = {sg * F[1].m[k].r + F[4].m[k].r, sg * F[1].m[k].i + F[4].m[k].i};
-            B[2][k] = {sg * F[2].m[k].r - F[3].m[k].r, sg * F[2].m[k].i - F[3].m[k].i};
+    // B1, B2, B3 of block blk at colour entry k
+    auto field = [&](int blk, int j, int k) {
+        const double sg = blk == 0 ? 1.0 : -1.0, s2 = j == 1 ? 1.0 : -1.0;
+        const double2 u = F[j][k][lane], v = F[5 - j][k][lane];
+        return C64{sg * u.x + s2 * v.x, sg * u.y + s2 * v.y};
+    };
+    // entry (i, j) of a block, i = spin * 3 + colour: csw (i/2) v + diagonal
+    auto entry = [&](int blk, int i, int j) {
+        const int s1 = i / 3, s2 = j / 3, k = (i - 3 * s1) * 3 + (j - 3 * s2);
+        C64 v;
+        if (s1 == s2) {
+            v = field(blk, 2, k);
+            if (s1 == 1) v = {-v.r, -v.i};
+        } else {  // lower triangle: s1 = 1, s2 = 0
+            const C64 b1 = field(blk, 0, k), b2 = field(blk, 1, k);
+            v = {b1.r - b2.i, b1.i + b2.r};
         }
-        // full 6x6: index i = s*3 + a
-        C64 H[36];
-        for (int s1 = 0; s1 < 2; ++s1)
-            for (int s2 = 0; s2 < 2; ++s2)
-                for (int a = 0; a < 3; ++a)
-                    for (int b = 0; b < 3; ++b) {
-                        int k = a * 3 + b;
-                        C64 v;
-                        if (s1 == 0 && s2 == 0) v = B[2][k];
-                        else if (s1 == 1 && s2 == 1) v = {-B[2][k].r, -B[2][k].i};
-                        else if (s1 == 0) v = {B[0][k].r + B[1][k].i, B[0][k].i - B[1][k].r};  // B1 - i B2
-                        else v = {B[0][k].r - B[1][k].i, B[0][k].i + B[1][k].r};               // B1 + i B2
-                        // csw (i/2) v
-                        C64 w = {-0.5 * csw * v.i, 0.5 * csw * v.r};
-                        if (s1 == s2 && a == b) w.r += 4.0 + m0;
-                        H[(s1 * 3 + a) * 6 + s2 * 3 + b] = w;
-                    }
-        double2* o = C + (size_t)blk * 18 * g.Vh + cb;
-        o[0 * (size_t)g.Vh] = make_double2(H[0].r, H[7].r);
-        o[1 * (size_t)g.Vh] = make_double2(H[14].r, H[21].r);
-        o[2 * (size_t)g.Vh] = make_double2(H[28].r, H[35].r);
-        int q = 3;
-        for (int i = 1; i < 6; ++i)
-            for (int j = 0; j < i; ++j, ++q) o[(size_t)q * g.Vh] = make_double2(H[i * 6 + j].r, H[i * 6 + j].i);
+        return make_double2(-0.5 * csw * v.i + (i == j ? 4.0 + m0 : 0.0), 0.5 * csw * v.r);
+    };
+    for (int o = p * 6; o < p * 6 + 6; ++o) {  // uniform over the wave
+        const int blk = o / 18, e = o - 18 * blk;
+        double2 w;
+        if (e < 3) {
+            w = make_double2(entry(blk, 2 * e, 2 * e).x, entry(blk, 2 * e + 1, 2 * e + 1).x);
+        } else {
+            int i = 1, f = e - 3;  // e - 3 counts the entries (i, j < i) row by row
+            while (f >= i) f -= i++;
+            w = entry(blk, i, f);
+        }
+        C[((size_t)blk * 18 + e) * g.Vh + cb] = w;
     }
 }
 
-__global__ void k_clover_build(const double2* __restrict__ U, Geo g, double m0, double csw,
-                               double2* __restrict__ C0, double2* __restrict__ C1) {
-    long V = 2L * g.Vh;
-    long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    clover_site(U, g, m0, csw, C0, C1, s);
-}
-
-hipError_t launch_clover_build(const double2* Ucan, const Geo& g, double m0, double csw, double2* C0, double2* C1, hipStream_t s) {
-    long n = 2L * g.Vh;
-    hipLaunchKernelGGL(k_clover_build, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, Ucan, g, m0, csw, C0, C1);
+hipError_t launch_clover_build(const double2* U64, const Geo& g, double m0, double csw, double2* C0, double2* C1, hipStream_t s) {
+    hipLaunchKernelGGL(k_clover_build, dim3((unsigned)((g.Vh + CLOVER_SITES - 1) / CLOVER_SITES), 2), dim3(6 * CLOVER_SITES), 0, s,
+                       U64, g, m0, csw, C0, C1);
     return hipGetLastError();
 }
 

@@ -113,9 +113,9 @@ constexpr int hop_window_max_bytes(int nb) { return nb <= 2 ? 20 * 1024 : 40 * 1
 template <int P> hipError_t launch_hop(const HopCfg& c, const HopJob<P>* djobs, int njob, int nblocks, hipStream_t s);
 
 // gauge and clover
-hipError_t launch_pack_links(const double2* Ucan, double2* U64, const Geo& g, hipStream_t s);
-hipError_t launch_unitarity(const double2* Ucan, long nlink, double* blockmax, int nblk, hipStream_t s);
-hipError_t launch_clover_build(const double2* Ucan, const Geo& g, double m0, double csw, double2* C0, double2* C1, hipStream_t s);
+// packed links, and *worst (0 on entry) = the bits of max |U U^dag - 1| over the links
+hipError_t launch_ingest(const double2* Ucan, double2* U64, const Geo& g, unsigned long long* worst, hipStream_t s);
+hipError_t launch_clover_build(const double2* U64, const Geo& g, double m0, double csw, double2* C0, double2* C1, hipStream_t s);
 hipError_t launch_clover_invert(const double2* C, double2* Ci, int Vh, int* err, hipStream_t s);
 hipError_t launch_add_diag(double2* C, int Vh, double delta, hipStream_t s);
 template <int P> hipError_t launch_convert_pairs(const double2* src, void* dst, long n, hipStream_t s);
