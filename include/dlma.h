@@ -250,9 +250,9 @@ int dlma_project(dlma_gauge_t g, int t, int nev, const void* V_t, const void* in
  * Allocation-free dlma_project, for callers that cannot allocate device memory
  * (code under stream capture, tight serving loops, harnesses that forbid it).
  * Same arguments, same kernels and bit-identical results as dlma_project, but:
- *   - the projection coefficients live in one fixed 1 MiB device array per GPU
- *     (65536 complex doubles), held from the first call on that GPU until the
- *     process ends; right-hand sides are processed in chunks of 16384 / nev;
+ *   - the projection coefficients and their partial sums live in one fixed 12 MiB
+ *     device array per GPU, held from the first call on that GPU until the
+ *     process ends; right-hand sides are processed in chunks that fit it;
  *   - no device memory is allocated or freed, and no library routine that
  *     allocates is called;
  *   - the call only enqueues work on `stream` and does not synchronise it.

@@ -838,9 +838,14 @@ extern "C" int dlma_project(dlma_gauge_t h, int t, int nev, const void* V_t, con
     if (nrhs == 0) return DLMA_OK;
     if (!in || !out || (nev > 0 && !V_t)) return fail(DLMA_EINVAL, "NULL pointer");
     hipStream_t s = S(stream);
-    Buf coef;
-    DLMA_TRY(coef.allocate(sizeof(double2) * std::max(1, nev) * 4 * (size_t)std::min(nrhs, 65535)));
-    DLMA_HIP(launch_project((const double2*)V_t, (const double2*)in, (double2*)out, g->geo, t, nev, nrhs, mode, coef.as<double2>(), s));
+    Buf coef, part;
+    const long per = 16L * std::max(1, nev), sets = std::min<long>((nrhs + 3) / 4, std::max(2L, (1L << 22) / per));
+    const long nc = per * sets, np = per * sets * project_ks(g->geo, nev);
+    const long cap = std::max(std::min(np, 4 * PROJ_PART_CAP), per * project_ks(g->geo, nev));
+    DLMA_TRY(coef.allocate(sizeof(double2) * nc));
+    DLMA_TRY(part.allocate(sizeof(double2) * cap));
+    DLMA_HIP(launch_project((const double2*)V_t, (const double2*)in, (double2*)out, g->geo, t, nev, nrhs, mode, coef.as<double2>(), nc,
+                            part.as<double2>(), cap, s));
     DLMA_HIP(hipStreamSynchronize(s));
     return DLMA_OK;
 }
@@ -939,13 +944,13 @@ extern "C" int dlma_correlators(dlma_gauge_t h, int t_src, int nev, const void* 
     ca.Vall = (const double2*)V_all;
     ca.L3 = L3; ca.fs = fs; ca.nt = T; ca.nev = nev;
     if (ndist > 0) {
-        ca.f0 = (const double2*)phi_dist; ca.ng = ndist; ca.ks = ksd;
+        ca.f0 = (const double2*)phi_dist; ca.ng = ndist; ca.nf = 4 * ndist; ca.ks = ksd;
         ca.taup = w + o_tdp; ca.gramp = w + o_gd;
         DLMA_HIP(launch_contract(ca, false, true, w + o_td, s));
         DLMA_HIP(launch_proj_gram(w + o_td, T, nev, ndist, 0, 0, 1, w + o_pd, s));
     }
     if (nnoise > 0) {
-        ca.f0 = (const double2*)phi; ca.f1 = (const double2*)phibar; ca.ng = nnoise; ca.ks = ksn;
+        ca.f0 = (const double2*)phi; ca.f1 = (const double2*)phibar; ca.ng = nnoise; ca.nf = 4 * nnoise; ca.ks = ksn;
         ca.taup = w + o_tnp; ca.gramp = w + o_gn;
         DLMA_HIP(launch_contract(ca, true, true, w + o_tn, s));
         DLMA_HIP(launch_proj_gram(w + o_tn, T, nev, nnoise, 0, 0, 2, w + o_pn, s));
@@ -1079,14 +1084,14 @@ extern "C" int dlma_correlators_grad(dlma_gauge_t h, int t_src, int nev, const v
         if (ndist > 0) {
             DLMA_TRY(dWPd.allocate(sizeof(double2) * WPd.size()));
             DLMA_HIP(hipMemcpyAsync(dWPd.p, WPd.data(), sizeof(double2) * WPd.size(), hipMemcpyHostToDevice, s));
-            ca.f0 = (const double2*)phi_dist; ca.ng = ndist; ca.ks = ksd;
+            ca.f0 = (const double2*)phi_dist; ca.ng = ndist; ca.nf = 4 * ndist; ca.ks = ksd;
             DLMA_HIP(launch_contract(ca, false, false, dtau.as<double2>(), s));
             DLMA_HIP(launch_tau_weights(dtau.as<double2>(), dWPd.as<double2>(), dtl, nact, nev, ndist, false, dTd.as<double2>(), s));
         }
         if (nnoise > 0) {
             DLMA_TRY(dWPn.allocate(sizeof(double2) * WPn.size()));
             DLMA_HIP(hipMemcpyAsync(dWPn.p, WPn.data(), sizeof(double2) * WPn.size(), hipMemcpyHostToDevice, s));
-            ca.f0 = (const double2*)phi; ca.f1 = (const double2*)phibar; ca.ng = nnoise; ca.ks = ksn;
+            ca.f0 = (const double2*)phi; ca.f1 = (const double2*)phibar; ca.ng = nnoise; ca.nf = 4 * nnoise; ca.ks = ksn;
             DLMA_HIP(launch_contract(ca, true, false, dtau.as<double2>(), s));
             DLMA_HIP(launch_tau_weights(dtau.as<double2>(), dWPn.as<double2>(), dtl, nact, nev, nnoise, true, dTn.as<double2>(), s));
         }

@@ -3,9 +3,9 @@
 // dlma_project takes its coefficient buffer c[r][k][s] = <v_k(t) x e_s, in_r>_t from
 // the library's device pool.  Callers that may not allocate device memory (code
 // under stream capture, serving loops) use this entry point instead: its
-// coefficients live in one fixed device array per GPU, declared below, and the
-// right-hand sides are processed in chunks that fit it.  The kernels are the same
-// as dlma_project's, so the two give bit-identical results.
+// coefficients and their partial sums live in one fixed device array per GPU, declared
+// below, and the right-hand sides are processed in chunks that fit it.  The kernels and
+// their split of the sums are dlma_project's, so the two give bit-identical results.
 #include <mutex>
 
 #include "laplace.h"
@@ -13,10 +13,13 @@
 
 namespace dlma {
 
-// Coefficient scratch: 65536 complex doubles (1 MiB) per GPU, held until the
-// process ends.  Host code never uses this name as an address: it is a host-side
-// stand-in.  The device address comes from hipGetSymbolAddress, once per device.
-constexpr long kProjScratchPairs = 65536;
+// Scratch per GPU, held until the process ends: the coefficients of at least four
+// right-hand sides at the largest nev (4 MiB) and the partial sums they are added from
+// (8 MiB).  Host code never uses this name as an address: it is a host-side stand-in.
+// The device address comes from hipGetSymbolAddress, once per device.
+constexpr int kProjMaxModes = 16384;
+constexpr long kProjCoefPairs = 16L * kProjMaxModes;
+constexpr long kProjScratchPairs = kProjCoefPairs + PROJ_PART_CAP;
 static __device__ __align__(256) double2 scratch[kProjScratchPairs];
 
 namespace {
@@ -55,21 +58,15 @@ extern "C" int dlma_project_noalloc(dlma_gauge_t h, int t, int nev, const void* 
     if (t < 0 || t >= g->dims[0]) return fail(DLMA_EINVAL, "timeslice out of range");
     if (mode != 0 && mode != 1) return fail(DLMA_EINVAL, "mode must be 0 or 1");
     if (nrhs < 0 || nev < 0) return fail(DLMA_EINVAL, "negative count");
-    const long per_rhs = 4L * std::max(1, nev);  // coefficients of one right-hand side
-    if (per_rhs > kProjScratchPairs)
+    if (nev > kProjMaxModes)
         return fail(DLMA_EINVAL, "nev = " + std::to_string(nev) + " exceeds the allocation-free projector's limit of " +
-                                     std::to_string(kProjScratchPairs / 4) + " modes");
+                                     std::to_string(kProjMaxModes) + " modes");
     if (nrhs == 0) return DLMA_OK;
     if (!in || !out || (nev > 0 && !V_t)) return fail(DLMA_EINVAL, "NULL pointer");
     double2* coef = nullptr;
     DLMA_TRY(scratch_on_current_device(&coef));
     hipStream_t s = (hipStream_t)stream;
-    const long fs = 12L * g->V;                         // complex numbers per spinor field
-    const int chunk = (int)(kProjScratchPairs / per_rhs);  // right-hand sides per pass through the scratch
-    for (int r0 = 0; r0 < nrhs; r0 += chunk) {
-        const int nr = std::min(chunk, nrhs - r0);
-        DLMA_HIP(launch_project((const double2*)V_t, (const double2*)in + (size_t)r0 * fs, (double2*)out + (size_t)r0 * fs,
-                                g->geo, t, nev, nr, mode, coef, s));
-    }
+    DLMA_HIP(launch_project((const double2*)V_t, (const double2*)in, (double2*)out, g->geo, t, nev, nrhs, mode, coef, kProjCoefPairs,
+                            coef + kProjCoefPairs, PROJ_PART_CAP, s));
     return DLMA_OK;
 }

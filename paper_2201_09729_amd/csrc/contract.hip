@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
     const int kc = r % a.ks, ti = r / a.ks;
     const int unit = ub * 4 + (int)(threadIdx.x >> 6);
     if (ti >= a.nt || unit >= a.nunit) return;  // whole waves
-    const int t = a.tlist ? a.tlist[ti] : ti;
+    const int t = a.tlist ? a.tlist[ti] : a.t0 + ti;
     const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
     const long L3 = a.L3;
     const long x0 = kc * a.chunk, x1 = x0 + a.chunk < L3 ? x0 + a.chunk : L3;
@@ -60,14 +60,14 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
     const int g0 = NOISE ? unit : 2 * unit;
     const bool two = NOISE || g0 + 1 < a.ng;
     const long col = ((long)t * L3 + x0 + q) * 12 + (m & 3) * 3;
-    const double2* p0 = a.f0 + ((long)g0 * 4 + (m >> 2)) * a.fs + col;
-    const double2* p1 = NOISE ? a.f1 + ((long)g0 * 4 + (m >> 2)) * a.fs + col
-                              : a.f0 + ((long)(two ? g0 + 1 : g0) * 4 + (m >> 2)) * a.fs + col;
+    auto field = [&](int g) { return (long)min(g * 4 + (m >> 2), a.nf - 1) * a.fs + col; };
+    const double2* p0 = a.f0 + field(g0);
+    const double2* p1 = NOISE ? a.f1 + field(g0) : a.f0 + field(two ? g0 + 1 : g0);
     const double2* pv[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
         const int k = a.k0 + 16 * b + m;  // modes past the last repeat it; their rows are not stored
-        pv[b] = a.Vall + (((long)t * a.nev + (k < a.nev ? k : a.nev - 1)) * L3 + x0 + q) * 3;
+        pv[b] = a.Vall + (((long)(t - a.tv0) * a.nev + (k < a.nev ? k : a.nev - 1)) * L3 + x0 + q) * 3;
     }
     const d4 z = {0.0, 0.0, 0.0, 0.0};
     d4 tr[2][MT], tm[2][MT], g00r = z, g00x = z, g10r = z, g10i = z;
@@ -286,6 +286,129 @@ hipError_t launch_proj_gram(const double2* tau, int nt, int nev, int ng, int oa,
 
 hipError_t launch_corr_pieces(const CorrPiecesArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_corr_pieces, dim3(a.T), dim3(1024), 0, s, a);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- projector
+//
+// box(t) in = sum_k v_k c_k with c = V^dag in on the contraction kernel (a right-hand side
+// is a field, four of them a column set), then out = c V or in - c V on timeslice t as a
+// matrix product (32 rows (site, colour) and eight right-hand sides per wave) in one
+// launch with the zero fill of the other timeslices.  Bound: the fill, a stream of
+// stores.  With a thread per (site, spin) storing 48 bytes apart and a block per (mode,
+// right-hand side) for c, 32 modes and right-hand sides at 24^3 x 48 took 1.32 ms;
+// 0.815 ms so (5.9 TB/s of stores).
+constexpr int FILL_PER_BLOCK = 1024;
+
+__global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long fs,
+                                                    int t, int nev, const double2* __restrict__ coef, int nrhs, int mode,
+                                                    unsigned nab, unsigned nrb) {
+    const long tofs = (long)t * L3 * 12;
+    if (blockIdx.x >= nab) {  // zeros off the timeslice
+        const unsigned fb = blockIdx.x - nab, nfb = (gridDim.x - nab) / (unsigned)nrhs;
+        const unsigned r = fb / nfb;
+        const long e0 = (long)(fb - r * nfb) * FILL_PER_BLOCK + threadIdx.x;
+        double2* o = out + (long)r * fs;
+#pragma unroll
+        for (int k = 0; k < FILL_PER_BLOCK / 256; ++k) {
+            const long e = e0 + k * 256;
+            if (e < fs && (e < tofs || e >= tofs + L3 * 12)) o[e] = make_double2(0.0, 0.0);
+        }
+        return;
+    }
+    const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
+    const long nrow = L3 * 3;
+    const unsigned ub = blockIdx.x / nrb;  // right-hand sides 8 ub .. 8 ub + 7
+    const long r0 = ((long)(blockIdx.x - ub * nrb) * 4 + (threadIdx.x >> 6)) * 32;
+    if (r0 >= nrow) return;  // whole waves
+    long row[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const long r = r0 + 16 * b + m;
+        row[b] = r < nrow ? r : nrow - 1;
+    }
+    const bool two = 8 * (int)ub + 4 < nrhs;
+    const d4 z = {0.0, 0.0, 0.0, 0.0};
+    d4 re[2][2] = {{z, z}, {z, z}}, im[2][2] = {{z, z}, {z, z}};
+    const double2* v = Vt + (long)q * nrow;
+    const double2* c = coef + ((long)ub * 2 * nev + q) * 16 + m;
+    const double2 zz = make_double2(0.0, 0.0);
+    for (int k = 0; k < nev; k += 4) {
+        const bool ok = k + q < nev;
+        double2 x[2], w[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) x[b] = ok ? v[(long)k * nrow + row[b]] : zz;
+        w[0] = ok ? c[(long)k * 16] : zz;
+        w[1] = ok && two ? c[((long)nev + k) * 16] : zz;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                re[h][b] = mma64(x[b].x, w[h].x, re[h][b]);
+                im[h][b] = mma64(x[b].x, w[h].y, im[h][b]);
+                re[h][b] = mma64(-x[b].y, w[h].y, re[h][b]);
+                im[h][b] = mma64(x[b].y, w[h].x, im[h][b]);
+            }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = 8 * (int)ub + 4 * h + (m >> 2);
+        if (r >= nrhs) continue;
+        const long base = (long)r * fs + tofs + (m & 3) * 3;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const long rw = r0 + 16 * b + 4 * i + q;
+                if (rw >= nrow) continue;
+                const long e = base + rw / 3 * 12 + rw % 3;
+                double2 o = make_double2(re[h][b][i], im[h][b][i]);
+                if (mode == 1) {
+                    const double2 x = in[e];
+                    o = make_double2(x.x - o.x, x.y - o.y);
+                }
+                out[e] = o;
+            }
+    }
+}
+
+// site chunks of c: about 96 sites each (24 steps of the contraction kernel), at most 128,
+// and few enough that four right-hand sides' partials fit PROJ_PART_CAP
+int project_ks(const Geo& g, int nev) {
+    const long L3 = (long)g.Z * g.Y * g.X;
+    const long k = std::min(std::min(L3 / 96, 128L), PROJ_PART_CAP / (16L * std::max(1, nev)));
+    return (int)std::max(1L, k);
+}
+
+hipError_t launch_project(const double2* Vt, const double2* in, double2* out, const Geo& g, int t, int nev, int nrhs, int mode,
+                          double2* coef, long coef_cap, double2* part, long part_cap, hipStream_t s) {
+    const long L3 = (long)g.Z * g.Y * g.X, fs = 24L * g.Vh;
+    const int ks = project_ks(g, nev);
+    // column sets (of four right-hand sides) per pass
+    const long per = 16L * std::max(1, nev);
+    long sets = std::min(coef_cap / per, ks > 1 ? part_cap / (per * ks) : coef_cap / per);
+    const unsigned nrb = (unsigned)((L3 * 3 + 127) / 128);
+    const unsigned nfb = (unsigned)((fs + FILL_PER_BLOCK - 1) / FILL_PER_BLOCK);
+    // pairs of sets share a wave, and the grid stays below 2^31 blocks
+    sets = std::min(sets, std::max(2L, (1L << 30) / (4L * nfb)));
+    if (sets > 2) sets -= sets & 1;
+    if (sets < 1) return hipErrorInvalidValue;
+    for (long r0 = 0; r0 < nrhs; r0 += 4 * sets) {
+        const int nr = (int)std::min<long>(4 * sets, nrhs - r0);
+        const double2* inr = in + r0 * fs;
+        if (nev > 0) {  // no modes: box(t) = 0 and the apply kernel reads no coefficient
+            ContractArgs a = {};
+            a.Vall = Vt; a.f0 = inr; a.L3 = L3; a.fs = fs;
+            a.t0 = a.tv0 = t;
+            a.nt = 1; a.nev = nev; a.ng = (nr + 3) / 4; a.nf = nr; a.ks = ks;
+            a.taup = part;
+            const hipError_t e = launch_contract(a, false, false, coef, s);
+            if (e != hipSuccess) return e;
+        }
+        const unsigned nab = nrb * (unsigned)((nr + 7) / 8);
+        hipLaunchKernelGGL(k_proj_apply, dim3(nab + nfb * (unsigned)nr), dim3(256), 0, s, Vt, inr, out + r0 * fs, L3, fs, t, nev,
+                           coef, nr, mode, nab, nrb);
+    }
     return hipGetLastError();
 }
 

@@ -48,17 +48,16 @@ hipError_t launch_block_update(const double2* X, const double2* Z, long n, int k
                                hipStream_t s);
 hipError_t launch_block_random(double2* V, long count, unsigned seed, hipStream_t s);
 hipError_t launch_phase_fix(double2* y, long n, int nvec, hipStream_t s);
-hipError_t launch_project(const double2* Vt, const double2* in, double2* out, const Geo& g, int t, int nev, int nrhs, int mode,
-                          double2* coef, hipStream_t s);
-
 // contractions
 // Column sets of 16 (label, spin) columns per source group: the groups of f0, or with
 // noise the phi (f0) and phibar (f1) of each group in turn (sets 2 g, 2 g + 1).
 struct ContractArgs {
     const double2 *Vall, *f0, *f1;
     long L3, fs;       // sites of a timeslice, complex numbers of a field
-    const int* tlist;  // the nt timeslices, nullptr = 0 .. nt - 1
+    const int* tlist;  // the nt timeslices, nullptr = t0 .. t0 + nt - 1
+    int t0, tv0;       // tv0: timeslice of Vall's first entry
     int nt, nev, ng, ks;
+    int nf;            // fields of f0 (4 ng, or fewer in the last group: its further columns repeat the last field)
     double2* taup;     // partials [ks][set][nt][nev][16] (unused with ks = 1)
     double2* gramp;    // [nt][ks][unit][noise ? 2 : 1][16][16]: (re, X) of (f0, f0), then (f1, f0)
     int nunit, k0;     // set by the launcher
@@ -70,6 +69,13 @@ hipError_t launch_contract(const ContractArgs& a, bool noise, bool gram, double2
 // part[nt][proj_gram_parts()][16][16] of sum_g sum_k conj(tau[oa + st g]) tau[ob + st g]
 int proj_gram_parts();
 hipError_t launch_proj_gram(const double2* tau, int nt, int nev, int ng, int oa, int ob, int st, double2* part, hipStream_t s);
+// box(t) of launch_project: coef and part hold coef_cap and part_cap complex numbers;
+// right-hand sides go through them in chunks.  The site chunks depend on the lattice and
+// nev alone, so the result does not depend on the capacities.
+constexpr long PROJ_PART_CAP = 524288;
+int project_ks(const Geo& g, int nev);
+hipError_t launch_project(const double2* Vt, const double2* in, double2* out, const Geo& g, int t, int nev, int nrhs, int mode,
+                          double2* coef, long coef_cap, double2* part, long part_cap, hipStream_t s);
 struct CorrPiecesArgs {
     const double2 *gd, *pd;         // dist: Gram partials [T][nud], projected partials
     const double2 *gn, *pn, *pq;    // noise: Gram partials [T][nun][2], projected (phi, phi) and (phibar, phi)

@@ -638,81 +638,4 @@ hipError_t launch_block_random(double2* V, long count, unsigned seed, hipStream_
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- projector
-
-// c[r][k][s] = sum_{m,col} conj(V[k][m][col]) in_r(t, m, s, col); one block per (k, r)
-__global__ void __launch_bounds__(256) k_proj_coef(const double2* __restrict__ Vt, const double2* __restrict__ in, long L3,
-                                                   long tofs, long fstride, int nev, double2* __restrict__ c) {
-    __shared__ double lds[4];
-    int k = blockIdx.x, r = blockIdx.y;
-    const double2* v = Vt + (long)k * L3 * 3;
-    const double2* f = in + (long)r * fstride + tofs;
-    double2 acc[4] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
-    for (long m = threadIdx.x; m < L3; m += 256) {
-        for (int col = 0; col < 3; ++col) {
-            double2 a = v[m * 3 + col];
-            for (int sp = 0; sp < 4; ++sp) {
-                double2 p = cconjmul(a, f[(m * 4 + sp) * 3 + col]);
-                acc[sp].x += p.x;
-                acc[sp].y += p.y;
-            }
-        }
-    }
-    for (int sp = 0; sp < 4; ++sp) {
-        double2 s = block_sum2<256>(acc[sp], lds);
-        if (threadIdx.x == 0) c[((long)r * nev + k) * 4 + sp] = s;
-    }
-}
-
-// out_r = box(t) in_r (mode 0) or (1 - box(t)) in_r (mode 1) on timeslice t, 0 elsewhere
-__global__ void k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long V, int t, int nev,
-                             const double2* __restrict__ c, int mode) {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;  // over V sites x 4 spins
-    int r = blockIdx.y;
-    if (i >= V * 4) return;
-    long site = i >> 2;
-    int sp = (int)(i & 3);
-    long base = ((long)r * V * 4 + i) * 3;
-    long tt = site / L3;
-    if (tt != t) {
-        for (int col = 0; col < 3; ++col) out[base + col] = make_double2(0, 0);
-        return;
-    }
-    long m = site - (long)t * L3;
-    double2 acc[3] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
-    const double2* cr = c + (long)r * nev * 4;
-    for (int k = 0; k < nev; ++k) {
-        double2 ck = cr[k * 4 + sp];
-        for (int col = 0; col < 3; ++col) {
-            double2 p = cmul2(Vt[((long)k * L3 + m) * 3 + col], ck);
-            acc[col].x += p.x;
-            acc[col].y += p.y;
-        }
-    }
-    for (int col = 0; col < 3; ++col) {
-        double2 o = acc[col];
-        if (mode == 1) {
-            double2 x = in[base + col];
-            o = make_double2(x.x - o.x, x.y - o.y);
-        }
-        out[base + col] = o;
-    }
-}
-
-hipError_t launch_project(const double2* Vt, const double2* in, double2* out, const Geo& g, int t, int nev, int nrhs, int mode,
-                          double2* coef, hipStream_t s) {
-    long L3 = (long)g.Z * g.Y * g.X;
-    long V = 2L * g.Vh;
-    for (int r0 = 0; r0 < nrhs; r0 += 65535) {
-        int nr = nrhs - r0 < 65535 ? nrhs - r0 : 65535;
-        const double2* inr = in + (long)r0 * V * 12;
-        double2* outr = out + (long)r0 * V * 12;
-        if (nev > 0)  // no modes: box(t) = 0 and the apply kernel reads no coefficient
-            hipLaunchKernelGGL(k_proj_coef, dim3(nev, nr), dim3(256), 0, s, Vt, inr, L3, (long)t * L3 * 12, V * 12, nev, coef);
-        hipLaunchKernelGGL(k_proj_apply, dim3((unsigned)((V * 4 + 255) / 256), nr), dim3(256), 0, s, Vt, inr, outr, L3, V, t, nev,
-                           coef, mode);
-    }
-    return hipGetLastError();
-}
-
 }  // namespace dlma

@@ -51,3 +51,26 @@ def test_contractions_at_tile_edges(orc, dims, nev, ndist, nnoise, ndil):
     for a, w in zip(grads, want):
         if a is not None:
             assert np.abs(a.cpu().numpy() - w).max() <= 1e-12 * gs
+
+
+@pytest.mark.parametrize("dims,nev,nrhs", [((2, 2, 2, 2), 1, 1), ((4, 4, 2, 6), 17, 5), ((2, 6, 10, 8), 33, 9), ((2, 4, 4, 4), 0, 3),
+                                           ((2, 6, 8, 8), 48, 16)])
+def test_projector_at_tile_edges(orc, dims, nev, nrhs):
+    """Modes in blocks of 16 and 32, right-hand sides in fours and eights with remainders, several site chunks."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2201_09729_amd import dlma as D
+    print("project", dims, nev, nrhs, flush=True)
+    n = 3 * int(np.prod(dims[1:]))
+    rng = np.random.default_rng(nev + nrhs)
+    V = np.linalg.qr(rng.standard_normal((n, max(nev, 1))) + 1j * rng.standard_normal((n, max(nev, 1))))[0][:, :nev]
+    V = np.ascontiguousarray(V.T).reshape((nev,) + dims[1:] + (3,))
+    x = synth.random_spinor(dims, nrhs, 8)
+    g = D.dlma_load_gauge(torch.from_numpy(synth.gauge_field(dims, 0.3, 1)).cuda(), 0.120, 1.0)
+    for t, mode in ((dims[0] - 1, 0), (0, 1)):
+        got = D.dlma_project(g, t, torch.from_numpy(V).cuda(), torch.from_numpy(x).cuda(), mode)
+        same = torch.full_like(got, float("nan"))
+        D.dlma_project_noalloc(g, t, torch.from_numpy(V).cuda(), torch.from_numpy(x).cuda(), mode, same)
+        assert torch.equal(got, same)
+        # orthonormal modes: FP64 sums of n products of O(1) entries
+        assert np.abs(got.cpu().numpy() - orc.project(V, x, t, mode)).max() < 1e-13 * np.abs(x).max()
