@@ -29,8 +29,7 @@ struct LapMode {
 // Grid: (site blocks of one timeslice, ceil(nv / VPT), nt).  Each thread takes VPT
 // vectors at one site: the six links of the site are loaded once and applied to all
 // of them, which halves the load instructions per vector at VPT = 4 (the kernel is
-// bound by the texture address path, like the stencils).  The partials of qd are
-// for nv = 1 (one vector per timeslice).
+// bound by the texture address path, like the stencils).
 template <int VPT>
 __global__ void __launch_bounds__(256) k_neg_lap(const double2* __restrict__ U64, Geo g, int t0, const double2* __restrict__ in,
                                                  double2* __restrict__ out, long tstride_in, long tstride_out, long vstride_in,
@@ -39,7 +38,6 @@ __global__ void __launch_bounds__(256) k_neg_lap(const double2* __restrict__ U64
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     const int kv0 = blockIdx.y * VPT, tl = blockIdx.z;
     const int nk = min(VPT, nv - kv0);  // uniform over the block
-    double dq = 0.0;
     if (m < L3) {
         const int t = t0 + tl;
         int x = m % g.X, y = (m / g.X) % g.Y, z = m / (g.X * g.Y);
@@ -99,15 +97,92 @@ __global__ void __launch_bounds__(256) k_neg_lap(const double2* __restrict__ U64
                 }
                 for (int a = 0; a < 3; ++a) o[(long)m * 3 + a] = acc[i][a];
             }
+    }
+}
+
+// One vector per timeslice: a block takes 64 sites, wave w the hop in direction 1 + w / 2
+// (forward for even w, backward for odd), so a thread has nine link loads and three of the
+// vector in flight and one timeslice fills six times the waves; the six terms meet in LDS
+// and the recurrence is applied on consecutive numbers.  Bound: the links through the
+// fabric (432 of 576 bytes per site), at one timeslice the latency of the chain of
+// launches.  With one thread per site doing all six hops an application on 32 timeslices
+// of 16^3 took 19.4 us, 15.1 us so (5.0 TB/s; 18.0 us without the range per XCD, which
+// keeps a link and its backward reader on one L2).
+constexpr int LAP_SITES = 64;
+
+__global__ void __launch_bounds__(6 * LAP_SITES) k_neg_lap1(const double2* __restrict__ U64, Geo g, int t0, const double2* __restrict__ in,
+                                                            double2* __restrict__ out, long tstride_in, long tstride_out, LapMode md,
+                                                            int nsb, int nt) {
+    __shared__ double2 hop[6][LAP_SITES * 3];
+    const int L3 = g.Z * g.Y * g.X;
+    // each XCD takes a contiguous range of (timeslice, site block)
+    const int lb = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int tl = lb / nsb, sb = lb - tl * nsb, t = t0 + tl;
+    if (tl >= nt) return;
+    const int lane = (int)threadIdx.x & 63, w = wave_uniform((int)threadIdx.x >> 6);
+    const int m0 = sb * LAP_SITES, m = m0 + lane;
+    const double2* v = in + tl * tstride_in;
+    if (m < L3) {
+        const int r1 = (int)mdiv(m >> 1, g.mXh), z = (int)mdiv(r1, g.mY);
+        const int x = m - r1 * g.X, y = r1 - z * g.Y;
+        const int j = 1 + (w >> 1), d = (w & 1) ? -1 : 1;
+        int xn = x, yn = y, zn = z;
+        if (j == 1) xn = x + d == g.X ? 0 : (x + d < 0 ? g.X - 1 : x + d);
+        if (j == 2) yn = y + d == g.Y ? 0 : (y + d < 0 ? g.Y - 1 : y + d);
+        if (j == 3) zn = z + d == g.Z ? 0 : (z + d < 0 ? g.Z - 1 : z + d);
+        const int mn = (zn * g.Y + yn) * g.X + xn;
+        // the link of this site (forward) or of the neighbour (backward)
+        const int ml = d > 0 ? m : mn, par = (d > 0 ? t + z + y + x : t + zn + yn + xn) & 1;
+        const double2* u = U64 + ((size_t)(par * 4 + j) * 9) * g.Vh + (((long)t * L3 + ml) >> 1);
+        double2 l[9], f[3], o[3];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) l[e] = u[(size_t)e * g.Vh];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) f[b] = v[(long)mn * 3 + b];
+        if (d > 0) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double2 p = cmul2(l[a * 3], f[0]), q = cmul2(l[a * 3 + 1], f[1]), r = cmul2(l[a * 3 + 2], f[2]);
+                o[a] = make_double2(p.x + q.x + r.x, p.y + q.y + r.y);
+            }
+        } else {  // (U^dag)_{ab} = conj(U_{ba})
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double2 p = cconjmul(l[a], f[0]), q = cconjmul(l[3 + a], f[1]), r = cconjmul(l[6 + a], f[2]);
+                o[a] = make_double2(p.x + q.x + r.x, p.y + q.y + r.y);
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) hop[w][lane * 3 + a] = o[a];
+    }
+    __syncthreads();
+    // number e of the block's 3 * LAP_SITES: waves 0 .. 2
+    double dq = 0.0;
+    const int e = (int)threadIdx.x;
+    if (e < 3 * LAP_SITES && m0 * 3 + e < L3 * 3) {
+        const long i = (long)m0 * 3 + e;
+        const double2 q = v[i];
+        double2 s = hop[0][e];
+#pragma unroll
+        for (int k = 1; k < 6; ++k) {
+            s.x += hop[k][e].x;
+            s.y += hop[k][e].y;
+        }
+        double2 o = make_double2(6.0 * q.x - s.x, 6.0 * q.y - s.y);
+        if (md.cheb) {
+            const double2 pr = md.prev ? md.prev[tl * md.tsp + i] : make_double2(0.0, 0.0);
+            o = make_double2(md.c2 * (md.c1 * q.x - o.x) - pr.x, md.c2 * (md.c1 * q.y - o.y) - pr.y);
+        }
+        out[tl * tstride_out + i] = o;
         if (md.qd) {
-            const double2* pq = md.qd + tl * md.tsqd + (long)m * 3;
-            for (int a = 0; a < 3; ++a) dq += pq[a].x * acc[0][a].x + pq[a].y * acc[0][a].y;
+            const double2 p = md.qd[tl * md.tsqd + i];
+            dq = p.x * o.x + p.y * o.y;
         }
     }
     if (md.qd) {  // uniform over the grid
-        __shared__ double lds[4];
-        dq = block_sum<256>(dq, lds);
-        if (threadIdx.x == 0) md.part[(long)tl * gridDim.x + blockIdx.x] = dq;
+        __shared__ double lds[6];
+        dq = block_sum<6 * LAP_SITES>(dq, lds);
+        if (threadIdx.x == 0) md.part[(long)tl * nsb + sb] = dq;
     }
 }
 
@@ -116,7 +191,8 @@ constexpr int LAP_VPT = 4;
 static hipError_t launch_lap(const double2* U64, const Geo& g, int t0, const double2* in, double2* out, long tsi, long tso,
                              int nt, int nv, long vsi, long vso, const LapMode& md, hipStream_t s);
 
-int lap_site_blocks(const Geo& g) { return (g.Z * g.Y * g.X + 255) / 256; }
+// blocks of 64 sites of a one-vector launch (the partials of qd per timeslice)
+int lap_site_blocks(const Geo& g) { return (g.Z * g.Y * g.X + LAP_SITES - 1) / LAP_SITES; }
 
 hipError_t launch_neg_lap(const double2* U64, const Geo& g, int t0, const double2* in, double2* out, long tsi, long tso,
                           int nt, hipStream_t s, int nv, long vsi, long vso, const double2* qd, double* part) {
@@ -127,12 +203,14 @@ hipError_t launch_neg_lap(const double2* U64, const Geo& g, int t0, const double
 
 static hipError_t launch_lap(const double2* U64, const Geo& g, int t0, const double2* in, double2* out, long tsi, long tso,
                              int nt, int nv, long vsi, long vso, const LapMode& md, hipStream_t s) {
-    if (nv == 1 || md.qd) {  // partials of qd: one vector per thread
-        hipLaunchKernelGGL(k_neg_lap<1>, dim3((unsigned)lap_site_blocks(g), nv, nt), dim3(256), 0, s, U64, g, t0, in, out, tsi,
-                           tso, vsi, vso, nv, md);
+    if (nv == 1) {
+        const int nsb = lap_site_blocks(g);
+        hipLaunchKernelGGL(k_neg_lap1, dim3((unsigned)((nsb * nt + 7) / 8 * 8)), dim3(6 * LAP_SITES), 0, s, U64, g, t0, in, out, tsi,
+                           tso, md, nsb, nt);
     } else {
-        hipLaunchKernelGGL(k_neg_lap<LAP_VPT>, dim3((unsigned)lap_site_blocks(g), (nv + LAP_VPT - 1) / LAP_VPT, nt), dim3(256),
-                           0, s, U64, g, t0, in, out, tsi, tso, vsi, vso, nv, md);
+        if (md.qd) return hipErrorInvalidValue;  // the partials are for one vector per timeslice
+        hipLaunchKernelGGL(k_neg_lap<LAP_VPT>, dim3((unsigned)((g.Z * g.Y * g.X + 255) / 256), (nv + LAP_VPT - 1) / LAP_VPT, nt),
+                           dim3(256), 0, s, U64, g, t0, in, out, tsi, tso, vsi, vso, nv, md);
     }
     return hipGetLastError();
 }
@@ -271,14 +349,21 @@ hipError_t launch_normalize_into(const double2* w, long tsw, double2* q, long ts
 
 // alpha_t = sum of the block partials of Re <q_j, w> written by the stencil that
 // produced w; w -= alpha_t q_j + beta_{j-1} q_{j-1}
-__global__ void k_lanczos_three_p(const double2* __restrict__ qj, const double2* __restrict__ qjm, long tsq,
+__global__ void __launch_bounds__(256) k_lanczos_three_p(const double2* __restrict__ qj, const double2* __restrict__ qjm, long tsq,
                                   double2* __restrict__ w, long tsw, long n, const double* __restrict__ apart, int nap,
                                   double* __restrict__ alpha, const double* __restrict__ beta, int astride, int j, int prev) {
+    __shared__ double lds[4], asum;
     long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
     int t = blockIdx.y;
     double a = 0.0;
-    for (int b = 0; b < nap; ++b) a += apart[(long)t * nap + b];
-    if (blockIdx.x == 0 && threadIdx.x == 0) alpha[(long)t * astride + j] = a;
+    for (int b = threadIdx.x; b < nap; b += 256) a += apart[(long)t * nap + b];
+    a = block_sum<256>(a, lds);
+    if (threadIdx.x == 0) {
+        asum = a;
+        if (blockIdx.x == 0) alpha[(long)t * astride + j] = a;
+    }
+    __syncthreads();
+    a = asum;
     if (e >= n) return;
     double2 v = w[t * tsw + e];
     double2 c = qj[t * tsq + e];

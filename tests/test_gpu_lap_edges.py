@@ -1,0 +1,29 @@
+"""Laplacian eigensolver on timeslices that are not multiples of its 64-site blocks."""
+import numpy as np
+import pytest
+
+from paper_2201_09729_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("dims,t0,nt", [((4, 2, 2, 2), 1, 3), ((2, 2, 6, 10), 0, 2), ((6, 4, 2, 14), 2, 3), ((2, 12, 14, 10), 0, 1)])
+def test_lap_eigs_ragged_timeslices(orc, dims, t0, nt):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2201_09729_amd import dlma as D
+    print("lap", dims, nt, flush=True)
+    U = synth.gauge_field(dims, 0.3, 4)
+    g = D.dlma_load_gauge(torch.from_numpy(U).cuda(), 0.120, 1.0)
+    nev = 3
+    v0 = torch.from_numpy(synth.gaussian_start(dims, nt, 11)).cuda()
+    V, ev = D.dlma_lap_eigs(g, nev, t0, nt, v0, tol=1e-11)
+    V = V.cpu().numpy()
+    for i in range(nt):
+        lv = np.stack([orc.laplacian(U, t0 + i, v) for v in V[i]])
+        # the stopping test is |lap v - lambda v| <= 12 tol
+        assert np.linalg.norm((lv - ev[i][:, None, None, None, None] * V[i]).reshape(nev, -1), axis=1).max() <= 1.3e-10
+        f = V[i].reshape(nev, -1)
+        assert np.abs(f.conj() @ f.T - np.eye(nev)).max() < 1e-12
