@@ -48,6 +48,7 @@ static int invert_clover(Gauge* g, hipStream_t s, const void* worst = nullptr, u
     }
     if (h) return fail(DLMA_EINVAL, "clover block not positive definite (kappa/csw out of range for this field)");
     for (int p = 1; p < 4; ++p) g->lo_ready[p] = false;
+    g->tclover_ready = false;
     return DLMA_OK;
 }
 

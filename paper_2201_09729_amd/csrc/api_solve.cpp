@@ -60,6 +60,7 @@ struct Cfg {
     double2 *brho = nullptr, *balpha = nullptr, *bomega = nullptr, *bbeta = nullptr;
     Buf dstate;                      // rr rr0 alpha beta tol2 abs2 nrm enrm (double) | active iters oact (int)
     int hnsb, vnsb;                  // site blocks of stencil and vector kernels
+    int thnsb = 0, tvnsb = 0, tcnsb = 0;  // site blocks of the tile stencils, vector kernels and conversions
     double *rr, *rr0, *alpha, *beta, *tol2, *abs2, *nrm, *enrm;
     int *active, *iters;
     int* oact;  // right-hand sides iterated in the last pass: the FP64 outer stencils skip the others
@@ -91,7 +92,44 @@ template <int P> struct Tables {
     Buf dbk1p, dbk2v, dbk1s, dbk2t, dbv, dbf;
     int nbv = 0, bbv = 0, bbf = 0;
     std::vector<BiFinJob> hbf;           // kept for per-pass updates (maxit)
+    // the same on right-hand-side tiles (tile.h), with the conversions in and out
+    bool tiled = false;
+    Buf dtk1p, dtk2v, dtk1s, dtk2t, dtv, dtc, dtc0, dtb;
+    TileHopJob th0;                      // the first configuration's job (windowed launches)
+    int bth = 0, btv = 0, btc = 0;
 };
+
+// BF16 BiCGStab solves take right-hand-side tiles when the tiles are filled well enough:
+// a tile's stencil costs the same for 9 right-hand sides as for 16.  Both stencils of
+// Dhat on 24x12^3, tiles against one thread per site: 16 of 16 51 against 59 us, 32 of 32
+// 77 against 99, 72 of 80 150 against 185, 12 of 16 51 against 45; 32x16^3, 24 of 32 192
+// against 198; 48x24^3, 96 of 96 2.73 against 4.0 ms.  So up to a quarter more columns than
+// right-hand sides, where they are at worst equal.  A tile's fields must fit a buffer
+// resource (768 bytes per site, 32-bit offsets).  A caller's own rhs_block asks for the
+// per-thread stencils.
+bool tile_fill(const std::vector<std::pair<int, int>>& vh_nrhs) {
+    double have = 0, need = 0;
+    for (auto& c : vh_nrhs) {
+        if ((size_t)c.first * 768 >= ((size_t)1 << 32)) return false;
+        have += (double)c.first * c.second;
+        need += (double)c.first * tile_count(c.second) * TILE;
+    }
+    return need <= 1.25 * have;
+}
+
+TileHopJob tile_hop_job(const Gauge* g, int par, int nrhs) {
+    TileHopJob j = {};
+    j.g = g->geo;
+    j.par = par;
+    j.nrhs = nrhs;
+    j.ntile = tile_count(nrhs);
+    j.R = tile_hop_rows(g->geo);
+    j.nstrip = ceil_div(g->geo.Y, j.R);
+    j.nbt = tile_hop_nbt(g->geo);
+    j.pstride = g->geo.T * j.nbt;
+    j.L = g->tL[par].as<uint32_t>();
+    return j;
+}
 
 template <class T> int upload(Buf& b, const std::vector<T>& v, hipStream_t s) {
     DLMA_TRY(b.allocate(sizeof(T) * std::max<size_t>(1, v.size())));
@@ -99,11 +137,12 @@ template <class T> int upload(Buf& b, const std::vector<T>& v, hipStream_t s) {
     return DLMA_OK;
 }
 
-template <int P> int alloc_cfg(Cfg& c, bool bicg, hipStream_t s) {
+template <int P> int alloc_cfg(Cfg& c, bool bicg, bool tiled, hipStream_t s) {
     Gauge* g = c.g;
-    size_t n = c.nrhs;
+    const size_t nreal = c.nrhs;
+    size_t n = tiled ? (size_t)tile_count(c.nrhs) * TILE : nreal;  // right-hand sides held by the inner fields
     int Vh = g->Vh;
-    size_t full64 = sizeof(double2) * n * 24 * Vh, half64 = sizeof(double2) * n * 12 * Vh;
+    size_t full64 = sizeof(double2) * nreal * 24 * Vh, half64 = sizeof(double2) * nreal * 12 * Vh;
     DLMA_TRY(c.B.allocate(full64));
     DLMA_TRY(c.X.allocate(full64));
     DLMA_TRY(c.tsup.allocate(sizeof(int) * (size_t)c.nrhs * g->geo.T));
@@ -135,6 +174,7 @@ template <int P> int alloc_cfg(Cfg& c, bool bicg, hipStream_t s) {
             DLMA_TRY(c.nbt.allocate(nb));
             DLMA_TRY(c.nbrh.allocate(sizeof(float) * Vh));
         }
+        n = nreal;
         DLMA_TRY(c.bstate.allocate(sizeof(double2) * 4 * n));
         c.brho = c.bstate.as<double2>();
         c.balpha = c.brho + n;
@@ -142,11 +182,18 @@ template <int P> int alloc_cfg(Cfg& c, bool bicg, hipStream_t s) {
         c.bbeta = c.brho + 3 * n;
         DLMA_HIP(hipMemsetAsync(c.bstate.p, 0, sizeof(double2) * 4 * n, s));
     }
+    n = nreal;
     c.hnsb = hop_nsb(g->geo);
     c.vnsb = ceil_div(Vh, VEC_BS);
     int pmax = std::max(std::max(2 * c.hnsb, 3 * c.vnsb), hop_nq(F_DOTX | F_DOTXH) * c.hnsb);
+    if (tiled) {
+        c.thnsb = g->geo.T * tile_hop_nbt(g->geo);
+        c.tvnsb = ceil_div(Vh, TVEC_SITES);
+        c.tcnsb = ceil_div(Vh, TCONV_SITES);
+        pmax = std::max(pmax, std::max(std::max(hop_nq(F_DOTX | F_DOTXH) * c.thnsb, 2 * c.tvnsb), c.tcnsb));
+    }
     DLMA_TRY(c.part.allocate(sizeof(double) * n * pmax));
-    if (bicg) DLMA_TRY(c.parts.allocate(sizeof(double) * n * 2 * c.vnsb));
+    if (bicg) DLMA_TRY(c.parts.allocate(sizeof(double) * n * 2 * (tiled ? c.tvnsb : c.vnsb)));
     DLMA_TRY(c.dstate.allocate(sizeof(double) * 8 * n + sizeof(int) * 3 * n + 256));
     double* d = c.dstate.as<double>();
     c.rr = d; c.rr0 = d + n; c.alpha = d + 2 * n; c.beta = d + 3 * n; c.tol2 = d + 4 * n; c.abs2 = d + 5 * n;
@@ -172,12 +219,18 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
     std::vector<FinJob> finB, finR, finI, finAB, finE;
     std::vector<BiVecJob<P>> bvv;
     std::vector<BiFinJob> bfv;
+    std::vector<TileHopJob> tk1p, tk2v, tk1s, tk2t;
+    std::vector<TileVecJob> tvv;
+    std::vector<TileConvJob> tcv, tcv0;
+    std::vector<TileBackJob> tbv;
     int rhs0B = 0, rhs0R = 0, rhs0I = 0, rhs0AB = 0, rhs0E = 0, rhs0BF = 0;
     for (auto& c : cs) {
         Gauge* g = c.g;
         int Vh = g->Vh, n = c.nrhs;
         const double2* U64 = g->U64.as<double2>();
         int* tsup = c.tsup.as<int>();
+        // the inner solution as the FP64 kernels read it (tiles: copied back into y's storage)
+        const Buf& xv = t.tiled ? c.y : c.xs;
         const int vt = g->geo.Z * g->geo.Y * g->geo.Xh, T = g->geo.T;
         // the support flags of B on a vector job; dil: the job's input vanishes where
         // t - dil .. t + dil are unflagged
@@ -264,7 +317,7 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
             vnE.push_back(e64);
             vnE0.push_back(with_support(e64, 1));
             VecJob<P> a = v;
-            a.a = half_view<P>(c.xs.p, nrm_of<P>(c.nxs), Vh);
+            a.a = half_view<P>(xv.p, nrm_of<P>(c.nxs), Vh);
             acc.push_back(a);
             VecJob<P64> a64 = v64;
             a64.b = full_view(c.X.p, Vh, 0);
@@ -297,7 +350,7 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
             recon0.push_back(j);
         }
         {   // inner CG stencils
-            const typename PT<P>::S* U = (const typename PT<P>::S*)gauge_links(g, P);
+            const typename PT<P>::S* U = (const typename PT<P>::S*)gauge_links(g, P);  // (unused with tiles)
             const typename PT<P>::S* Cee = (const typename PT<P>::S*)gauge_clover_ee(g, P);
             const typename PT<P>::S* Cio = (const typename PT<P>::S*)gauge_clover_oo_inv(g, P);
             SF<P> vp = half_view<P>(c.p.p, nrm_of<P>(c.np), Vh), vy = half_view<P>(c.y.p, nrm_of<P>(c.ny), Vh);
@@ -343,8 +396,43 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
                 bf.part_s = c.parts.as<double>();
                 bf.rho = c.brho; bf.alpha = c.balpha; bf.omega = c.bomega; bf.beta = c.bbeta;
                 bf.rr = c.rr; bf.tol2 = c.tol2; bf.active = c.active; bf.iters = c.iters; bf.maxit = 1 << 30;
+                if (t.tiled) {
+                    bf.npart = c.tvnsb;
+                    bf.nparth = c.thnsb;
+                }
                 bfv.push_back(bf);
             }
+        }
+        if (t.tiled) {
+            auto w = [](const Buf& b) { return b.as<uint32_t>(); };
+            uint32_t *p = w(c.p), *y = w(c.y), *v = w(c.w), *r = w(c.r), *x = w(c.xs), *sf = w(c.bs), *tf = w(c.bt), *rh = w(c.brh);
+            TileHopJob j1 = tile_hop_job(g, 1, n), j2 = tile_hop_job(g, 0, n);
+            j1.active = j2.active = c.active;
+            j2.part = c.part.as<double>();
+            j2.rh = rh;
+            TileHopJob a = j1; a.in = p; a.out = y; tk1p.push_back(a);
+            TileHopJob b = j2; b.x = p; b.in = y; b.out = v; tk2v.push_back(b);
+            TileHopJob d = j1; d.in = sf; d.out = y; tk1s.push_back(d);
+            TileHopJob e = j2; e.x = sf; e.in = y; e.out = tf; tk2t.push_back(e);
+            TileVecJob tv = {};
+            tv.Vh = Vh; tv.nrhs = n; tv.ntile = tile_count(n); tv.nsb = c.tvnsb;
+            tv.r = r; tv.rh = rh; tv.p = p; tv.v = v; tv.s = sf; tv.t = tf; tv.x = x;
+            tv.alpha = c.balpha; tv.omega = c.bomega; tv.beta = c.bbeta;
+            tv.active = c.active; tv.part = c.part.as<double>(); tv.part_s = c.parts.as<double>(); tv.pstride = c.tvnsb;
+            tv.tdist = c.tdist.as<int>(); tv.titer = c.iters; tv.vt = vt; tv.T = T;
+            tvv.push_back(tv);
+            TileConvJob tc = {};
+            tc.Vh = Vh; tc.nrhs = n; tc.ntile = tv.ntile; tc.nsb = c.tcnsb;
+            tc.src = half_view<P64>(c.E.p, nullptr, Vh);
+            tc.s = c.enrm; tc.active = c.oact; tc.a = r; tc.b = p; tc.c = x;
+            tc.part = c.part.as<double>(); tc.pstride = c.tcnsb;
+            tcv.push_back(tc);
+            tc.tsup = tsup; tc.tdil = 1; tc.vt = vt; tc.T = T;
+            tcv0.push_back(tc);
+            TileBackJob tb = {};
+            tb.Vh = Vh; tb.nrhs = n; tb.ntile = tv.ntile; tb.nsb = c.tcnsb;
+            tb.a = x; tb.v = y;
+            tbv.push_back(tb);
         }
         FinJob f = {};
         f.nrhs = n; f.part = c.part.as<double>();
@@ -352,7 +440,7 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
         f.active = c.active; f.iters = c.iters; f.out = c.nrm; f.maxit = 1 << 30;
         FinJob fb = f; fb.npart = 2 * c.vnsb; fb.rhs0 = rhs0B; rhs0B += n; finB.push_back(fb);
         FinJob fr = f; fr.npart = 2 * c.hnsb; fr.rhs0 = rhs0R; rhs0R += n; finR.push_back(fr);
-        FinJob fi = f; fi.npart = c.vnsb; fi.rhs0 = rhs0I; rhs0I += n; fi.out = c.enrm; finI.push_back(fi);
+        FinJob fi = f; fi.npart = t.tiled ? c.tcnsb : c.vnsb; fi.rhs0 = rhs0I; rhs0I += n; fi.out = c.enrm; finI.push_back(fi);
         FinJob fe = f; fe.npart = c.vnsb; fe.rhs0 = rhs0E; rhs0E += n; fe.out = c.enrm; finE.push_back(fe);
         FinJob fa = f; fa.npart = c.hnsb; fa.rhs0 = rhs0AB; rhs0AB += n; finAB.push_back(fa);
     }
@@ -385,6 +473,23 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
         DLMA_TRY(upload(t.dbk1p, bk1p, s)); DLMA_TRY(upload(t.dbk2v, bk2v, s));
         DLMA_TRY(upload(t.dbk1s, bk1s, s)); DLMA_TRY(upload(t.dbk2t, bk2t, s));
         DLMA_TRY(upload(t.dbv, bvv, s)); DLMA_TRY(upload(t.dbf, bfv, s));
+    }
+    if (t.tiled) {
+        auto hops = [](std::vector<TileHopJob>& v) {
+            int b = 0;
+            for (auto& j : v) { j.blk0 = b; b += tile_hop_blocks(j, j.g.T); }
+            return b;
+        };
+        t.bth = hops(tk1p); hops(tk2v); hops(tk1s); hops(tk2t);
+        t.th0 = tk1p[0];
+        t.btv = t.btc = 0;
+        for (size_t i = 0; i < tvv.size(); ++i) {
+            tvv[i].blk0 = t.btv; t.btv += tvv[i].nsb * tvv[i].ntile;
+            tcv[i].blk0 = tcv0[i].blk0 = tbv[i].blk0 = t.btc; t.btc += tcv[i].nsb * tcv[i].ntile;
+        }
+        DLMA_TRY(upload(t.dtk1p, tk1p, s)); DLMA_TRY(upload(t.dtk2v, tk2v, s)); DLMA_TRY(upload(t.dtk1s, tk1s, s));
+        DLMA_TRY(upload(t.dtk2t, tk2t, s)); DLMA_TRY(upload(t.dtv, tvv, s)); DLMA_TRY(upload(t.dtc, tcv, s));
+        DLMA_TRY(upload(t.dtc0, tcv0, s)); DLMA_TRY(upload(t.dtb, tbv, s));
     }
     t.nb64 = nb64;
     t.nresid = (int)resid.size(); t.nprep = (int)prep.size(); t.nrecon = (int)recon.size();
@@ -520,7 +625,48 @@ int bicg_iteration(std::vector<Cfg>& cs, Tables<P>& t, int nb, const std::vector
     return DLMA_OK;
 }
 
+// The merged iteration on right-hand-side tiles.
+int tile_iteration(std::vector<Cfg>& cs, Tables<PB16>& t, const std::vector<int>& nact, hipStream_t s, const IterWin* w = nullptr) {
+    Profiler& pr = Profiler::get();
+    constexpr int FX = F_DOTX | F_DOTXH;
+    auto launch = [&](int i, int kind, int flags, const Buf& jobs, int kc) -> int {
+        int nblk = t.bth, tw0 = 0, twn = 0;
+        double bytes = 0, frac = 1;
+        if (w && w->twn[i] > 0) {
+            Cfg& c = cs[0];
+            tw0 = w->tw0[i];
+            twn = w->twn[i];
+            nblk = tile_hop_blocks(t.th0, twn);
+            frac = (double)twn / c.g->geo.T;
+            if (hop_nq(flags) > 0)
+                DLMA_HIP(hipMemsetAsync(c.part.p, 0, sizeof(double) * (size_t)c.nrhs * hop_nq(flags) * c.thnsb, s));
+        }
+        hipEvent_t a = nullptr;
+        if (pr.on) {
+            for (size_t k = 0; k < cs.size(); ++k) bytes += frac * hop_bytes(PB16, kind, flags, cs[k].g->Vh, nact[k]);
+            pr.begin(kc, bytes, s, a);
+        }
+        DLMA_HIP(launch_tile_hop(kind, flags, jobs.as<TileHopJob>(), t.nk, nblk, tw0, twn, s));
+        if (pr.on) pr.end(a, kc, bytes, s);
+        return DLMA_OK;
+    };
+    const TileVecJob* tv = t.dtv.as<TileVecJob>();
+    const BiFinJob* bf = t.dbf.as<BiFinJob>();
+    DLMA_TRY(launch(0, K1, 0, t.dtk1p, KC_K1));
+    DLMA_TRY(launch(1, K2, F_DOTR, t.dtk2v, KC_K2V));
+    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_ALPHA, s));
+    DLMA_HIP(launch_tile_vec(tv, t.nbv, t.btv, BV_SH, s));
+    DLMA_TRY(launch(2, K1, 0, t.dtk1s, KC_K1));
+    DLMA_TRY(launch(3, K2, FX, t.dtk2t, KC_K2T));
+    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_OMBETA, s));
+    DLMA_HIP(launch_tile_vec(tv, t.nbv, t.btv, BV_XRP, s));
+    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_CONV, s));
+    return DLMA_OK;
+}
+
 template <int P> int inner_iteration(std::vector<Cfg>& cs, Tables<P>& t, int nb, const std::vector<int>& nact, hipStream_t s) {
+    if constexpr (P == PB16)
+        if (t.tiled) return tile_iteration(cs, t, nact, s);
     return t.bicg ? bicg_iteration<P>(cs, t, nb, nact, s) : cg_iteration<P>(cs, t, nb, nact, s);
 }
 
@@ -561,9 +707,16 @@ template <int P> int tune_hop(Gauge* g, int nrhs, int fixed_nb, SF<P> vp, SF<P> 
 
 template <int P>
 int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
+    bool tiled = false;
+    if (P == PB16) {
+        std::vector<std::pair<int, int>> sizes;
+        for (auto& c : cs) sizes.emplace_back(c.g->Vh, c.nrhs);
+        tiled = o.inner_solver == 1 && o.rhs_block == 0 && tile_fill(sizes);
+    }
     for (auto& c : cs) {
-        DLMA_TRY(gauge_prepare(c.g, P, s));
-        DLMA_TRY(alloc_cfg<P>(c, o.inner_solver == 1, s));
+        if (tiled) DLMA_TRY(gauge_prepare_tiles(c.g, s));
+        else DLMA_TRY(gauge_prepare(c.g, P, s));
+        DLMA_TRY(alloc_cfg<P>(c, o.inner_solver == 1, tiled, s));
     }
     if (o.rhs_block < 0 || o.rhs_block > 4)
         return fail(DLMA_EINVAL, "rhs_block must be 0 .. 4");
@@ -576,7 +729,7 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
     {
         Cfg& c = cs[big];
         int Vh = c.g->Vh;
-        DLMA_TRY(tune_hop<P>(c.g, c.nrhs, o.rhs_block, half_view<P>(c.p.p, nrm_of<P>(c.np), Vh),
+        if (!tiled) DLMA_TRY(tune_hop<P>(c.g, c.nrhs, o.rhs_block, half_view<P>(c.p.p, nrm_of<P>(c.np), Vh),
                              half_view<P>(c.y.p, nrm_of<P>(c.ny), Vh), half_view<P>(c.w.p, nrm_of<P>(c.nw), Vh), tin, s));
         DLMA_TRY(tune_hop<P64>(c.g, c.nrhs, 0, half_view<P64>(c.E.p, nullptr, Vh), half_view<P64>(c.T.p, nullptr, Vh),
                                full_view(c.R.p, Vh, 0), t64, s));
@@ -585,7 +738,10 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
     const int nb = tin.nb;
     Tables<P> t;
     t.bicg = o.inner_solver == 1;
-    if (t.bicg)  // BiCGStab's shadow residual: one fixed seeded random field per configuration
+    t.tiled = tiled;
+    if (tiled)
+        for (auto& c : cs) DLMA_HIP(launch_tile_random(c.brh.as<uint32_t>(), c.g->Vh, 0x5eedu + (unsigned)c.gidx, s));
+    else if (t.bicg)  // BiCGStab's shadow residual: one fixed seeded random field per configuration
         for (auto& c : cs)
             DLMA_HIP(launch_fill_random<P>(half_view<P>(c.brh.p, nrm_of<P>(c.nbrh), c.g->Vh), c.g->Vh, 1,
                                            0x5eedu + (unsigned)c.gidx, s));
@@ -602,7 +758,7 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
     DLMA_HIP(launch_norm<P64>(t.dvnB.template as<VecJob<P64>>(), t.nvnB, t.bvnB, s));
     // first pass from x = 0 (FP16 BiCGStab): distances to each source's support, for the
     // reach of the Krylov vectors; otherwise 0 (everything within reach)
-    const bool reach_skip = P == P16 && t.bicg && !o.use_x0;
+    const bool reach_skip = (P == P16 || t.tiled) && t.bicg && !o.use_x0;
     for (auto& c : cs) {
         if (reach_skip) DLMA_HIP(launch_tdist(c.tsup.as<int>(), c.tdist.as<int>(), c.nrhs, c.g->geo.T, s));
         else DLMA_HIP(hipMemsetAsync(c.tdist.p, 0, c.tdist.n, s));
@@ -815,8 +971,12 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
             DLMA_HIP(launch_norm<P64>((from_b ? t.dvnE0 : t.dvnE).template as<VecJob<P64>>(), t.nconv, t.bvnE, s));
             DLMA_HIP(launch_finish(t.dfinE.template as<FinJob>(), t.nfin, t.bfin, FIN_NORM, s));
         }
-        DLMA_HIP(launch_conv_from64<P>(t.dconv.template as<VecJob<P>>(), t.nconv, t.bconv,
-                                       (from_b ? t.dconv640 : t.dconv64).template as<VecJob<P64>>(), s));
+        if (t.tiled) {
+            DLMA_HIP(launch_tile_conv((from_b ? t.dtc0 : t.dtc).template as<TileConvJob>(), t.nbv, t.btc, s));
+        } else {
+            DLMA_HIP(launch_conv_from64<P>(t.dconv.template as<VecJob<P>>(), t.nconv, t.bconv,
+                                           (from_b ? t.dconv640 : t.dconv64).template as<VecJob<P64>>(), s));
+        }
         for (auto& f : t.hfinI) { f.rel2 = rel * rel; f.maxit = std::max(1, o.maxiter - maxused); }
         for (auto& f : t.hfinAB) f.maxit = std::max(1, o.maxiter - maxused);
         DLMA_HIP(hipMemcpyAsync(t.dfinI.p, t.hfinI.data(), sizeof(FinJob) * t.hfinI.size(), hipMemcpyHostToDevice, s));
@@ -825,7 +985,11 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
         if (t.bicg) {  // rho = (rh, r) (p = r already), per-pass iteration caps
             for (auto& f : t.hbf) f.maxit = std::max(1, o.maxiter - maxused);
             DLMA_HIP(hipMemcpyAsync(t.dbf.p, t.hbf.data(), sizeof(BiFinJob) * t.hbf.size(), hipMemcpyHostToDevice, s));
-            DLMA_HIP(launch_bivec<P>(t.dbv.template as<BiVecJob<P>>(), t.nbv, t.bbv, BV_RR, s));
+            if (t.tiled) {
+                DLMA_HIP(launch_tile_vec(t.dtv.template as<TileVecJob>(), t.nbv, t.btv, BV_RR, s));
+            } else {
+                DLMA_HIP(launch_bivec<P>(t.dbv.template as<BiVecJob<P>>(), t.nbv, t.bbv, BV_RR, s));
+            }
             DLMA_HIP(launch_bifinish(t.dbf.template as<BiFinJob>(), t.nbv, t.bbf, BF_INIT, s));
         }
         const bool windowed = from_b && arcn > 0;
@@ -833,9 +997,11 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
             for (auto& c : cs) {
                 if (from_b) {  // what the skipped sites and blocks leave untouched starts at zero:
                     // s (the s step), and with windowed stencils also y, v and t
-                    for (Buf* f : {&c.bs, &c.nbs}) DLMA_HIP(hipMemsetAsync(f->p, 0, f->n, s));
+                    for (Buf* f : {&c.bs, &c.nbs})
+                        if (f->p) DLMA_HIP(hipMemsetAsync(f->p, 0, f->n, s));
                     if (windowed)
-                        for (Buf* f : {&c.y, &c.ny, &c.w, &c.nw, &c.bt, &c.nbt}) DLMA_HIP(hipMemsetAsync(f->p, 0, f->n, s));
+                        for (Buf* f : {&c.y, &c.ny, &c.w, &c.nw, &c.bt, &c.nbt})
+                            if (f->p) DLMA_HIP(hipMemsetAsync(f->p, 0, f->n, s));
                 } else if (pass == 1) {  // dense from here on: everything within reach
                     DLMA_HIP(hipMemsetAsync(c.tdist.p, 0, c.tdist.n, s));
                 }
@@ -858,7 +1024,8 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
                     w.twn[i] = W < T ? W : 0;
                 }
                 if (w.twn[0] == 0) break;
-                DLMA_TRY(bicg_iteration<P>(cs, t, nb, nact, s, &w));
+                if constexpr (P == PB16) DLMA_TRY(tile_iteration(cs, t, nact, s, &w));
+                else DLMA_TRY(bicg_iteration<P>(cs, t, nb, nact, s, &w));
             }
         }
         // inner CG
@@ -888,6 +1055,8 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
             }
             if (tot == 0) break;
         }
+        if (t.tiled)  // the solution in the layout of the FP64 kernels, into y's storage
+            DLMA_HIP(launch_tile_back(t.dtb.template as<TileBackJob>(), t.nbv, t.btc, s));
         // reconstruction (FP16: the even sites' accumulation is fused into the next residual)
         if (P == P16) acc_pending = true;
         else DLMA_HIP(launch_accum_to64<P>(t.dacc.template as<VecJob<P>>(), t.dacc64.template as<VecJob<P64>>(), t.nconv, t.bconv, s));
@@ -1152,11 +1321,61 @@ int bench_impl(Gauge* g, int nrhs, int nb, int napply, double* ms_out, double* b
 // ---------------------------------------------------------------- Schur operator
 
 namespace {
+// the same on right-hand-side tiles
+int schur_tiles(Gauge* g, const void* in, void* out, int nrhs, hipStream_t s) {
+    DLMA_TRY(gauge_prepare_tiles(g, s));
+    const int Vh = g->Vh, nt = tile_count(nrhs), vnsb = ceil_div(Vh, VEC_BS), tcnsb = ceil_div(Vh, TCONV_SITES);
+    const size_t full64 = sizeof(double2) * (size_t)nrhs * 24 * Vh, wb = sizeof(uint32_t) * (size_t)nt * Vh * 192;
+    Buf a64, b64, f[4], ones, act, part, dc, d1, d2, db, dac, dac64;
+    DLMA_TRY(a64.allocate(full64));
+    DLMA_TRY(b64.allocate(full64));
+    for (int i = 0; i < 4; ++i) DLMA_TRY(f[i].allocate(wb));
+    DLMA_TRY(part.allocate(sizeof(double) * (size_t)nrhs * tcnsb));
+    DLMA_TRY(upload(ones, std::vector<double>((size_t)nrhs, 1.0), s));
+    DLMA_TRY(upload(act, std::vector<int>((size_t)nrhs, 1), s));
+    DLMA_HIP(launch_canon_to_eo((const double2*)in, a64.as<double2>(), g->geo, nrhs, s));
+    TileConvJob tc = {};
+    tc.Vh = Vh; tc.nrhs = nrhs; tc.ntile = nt; tc.nsb = tcnsb;
+    tc.src = full_view(a64.p, Vh, 0);
+    tc.s = ones.as<double>(); tc.active = act.as<int>();
+    tc.a = f[0].as<uint32_t>(); tc.b = f[1].as<uint32_t>(); tc.c = f[2].as<uint32_t>();  // b and c are scratch
+    tc.part = part.as<double>(); tc.pstride = tcnsb;
+    TileHopJob j1 = tile_hop_job(g, 1, nrhs), j2 = tile_hop_job(g, 0, nrhs);
+    j1.in = tc.a; j1.out = tc.b;
+    j2.x = tc.a; j2.in = tc.b; j2.out = tc.c;
+    TileBackJob tb = {};
+    tb.Vh = Vh; tb.nrhs = nrhs; tb.ntile = nt; tb.nsb = tcnsb;
+    tb.a = tc.c; tb.v = f[3].as<uint32_t>();
+    VecJob<PB16> ac = {};
+    ac.Vh = Vh; ac.nrhs = nrhs; ac.nsb = vnsb;
+    ac.a = half_view<PB16>(f[3].p, nullptr, Vh);
+    ac.s = ones.as<double>();
+    VecJob<P64> ac64 = {};
+    ac64.Vh = Vh; ac64.nrhs = nrhs; ac64.nsb = vnsb;
+    ac64.a = full_view(b64.p, Vh, 0);
+    ac64.b = full_view(a64.p, Vh, 0);  // accumulator of the kernel, scratch here
+    DLMA_TRY(upload(dc, std::vector<TileConvJob>{tc}, s)); DLMA_TRY(upload(d1, std::vector<TileHopJob>{j1}, s));
+    DLMA_TRY(upload(d2, std::vector<TileHopJob>{j2}, s)); DLMA_TRY(upload(db, std::vector<TileBackJob>{tb}, s));
+    DLMA_TRY(upload(dac, std::vector<VecJob<PB16>>{ac}, s)); DLMA_TRY(upload(dac64, std::vector<VecJob<P64>>{ac64}, s));
+    const int nblk = tile_hop_blocks(j1, g->geo.T);
+    DLMA_HIP(launch_tile_conv(dc.as<TileConvJob>(), 1, tcnsb * nt, s));
+    DLMA_HIP(launch_tile_hop(K1, 0, d1.as<TileHopJob>(), 1, nblk, 0, 0, s));
+    DLMA_HIP(launch_tile_hop(K2, 0, d2.as<TileHopJob>(), 1, nblk, 0, 0, s));
+    DLMA_HIP(launch_tile_back(db.as<TileBackJob>(), 1, tcnsb * nt, s));
+    DLMA_HIP(hipMemsetAsync(b64.p, 0, full64, s));
+    DLMA_HIP(launch_accum_to64<PB16>(dac.as<VecJob<PB16>>(), dac64.as<VecJob<P64>>(), 1, vnsb * nrhs, s));
+    DLMA_HIP(launch_eo_to_canon(b64.as<double2>(), (double2*)out, g->geo, nrhs, s));
+    DLMA_HIP(hipStreamSynchronize(s));
+    return DLMA_OK;
+}
+
 // out_e = Dhat in_e (or Dhat^dag in_e) with the inner stencils of precision P: the
 // even sites of `in` rounded to P at scale 1 by the solver's conversion kernel, the
 // solver's K1 and K2 launches, the result widened to FP64; odd sites of out are 0.
 template <int P>
 int schur_impl(Gauge* g, const void* in, void* out, int nrhs, int dagger, int nb, int sg, int win, hipStream_t s) {
+    if constexpr (P == PB16)  // the solver's stencils for this many right-hand sides
+        if (nb == 0 && !dagger && tile_fill({{g->Vh, nrhs}})) return schur_tiles(g, in, out, nrhs, s);
     DLMA_TRY(gauge_prepare(g, P, s));
     const int Vh = g->Vh;
     const size_t full64 = sizeof(double2) * (size_t)nrhs * 24 * Vh;

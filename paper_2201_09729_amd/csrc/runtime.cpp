@@ -105,6 +105,23 @@ int gauge_prepare(Gauge* g, int prec, hipStream_t s) {
     return DLMA_OK;
 }
 
+int gauge_prepare_tiles(Gauge* g, hipStream_t s) {
+    const size_t b = sizeof(uint32_t) * 144 * (size_t)g->Vh;
+    if (!g->tlinks_ready) {
+        for (int par = 0; par < 2; ++par) {
+            DLMA_TRY(g->tL[par].allocate(b));
+            DLMA_HIP(launch_tile_links(g->U64.as<double2>(), g->geo, par, g->tL[par].as<uint32_t>(), s));
+        }
+        g->tlinks_ready = true;
+    }
+    if (!g->tclover_ready) {
+        for (int par = 0; par < 2; ++par)
+            DLMA_HIP(launch_tile_clover((par ? g->Ci64 : g->Cl64[0]).as<double2>(), g->Vh, g->tL[par].as<uint32_t>(), s));
+        g->tclover_ready = true;
+    }
+    return DLMA_OK;
+}
+
 const void* gauge_links(const Gauge* g, int prec) { return prec == P64 ? g->U64.p : g->Ulo[prec].p; }
 const void* gauge_clover_ee(const Gauge* g, int prec) { return prec == P64 ? g->Cl64[0].p : g->Cee[prec].p; }
 const void* gauge_clover_oo_inv(const Gauge* g, int prec) { return prec == P64 ? g->Ci64.p : g->Cio[prec].p; }

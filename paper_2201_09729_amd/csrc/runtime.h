@@ -8,6 +8,7 @@
 
 #include "../../include/dlma.h"
 #include "kernels.h"
+#include "tile.h"
 
 namespace dlma {
 
@@ -85,6 +86,9 @@ struct Gauge {
     Buf Cee[4];     // A_ee in that precision
     Buf Cio[4];     // A_oo^-1 in that precision
     bool lo_ready[4] = {false, false, false, false};
+    // links and clover (A_ee, A_oo^-1) of the right-hand-side tiles (tile.h) per output parity
+    Buf tL[2];
+    bool tlinks_ready = false, tclover_ready = false;
 };
 
 // Autotuner results, shared by all handles: (T, Z, Y, X, precision, nrhs) -> right-hand sides per thread
@@ -92,6 +96,7 @@ int tuned_lookup(const int dims[4], int prec, int nrhs);
 void tuned_store(const int dims[4], int prec, int nrhs, int nb);
 
 int gauge_prepare(Gauge* g, int prec, hipStream_t s);  // low-precision copies on demand
+int gauge_prepare_tiles(Gauge* g, hipStream_t s);
 const void* gauge_links(const Gauge* g, int prec);
 const void* gauge_clover_ee(const Gauge* g, int prec);
 const void* gauge_clover_oo_inv(const Gauge* g, int prec);
