@@ -28,10 +28,11 @@ namespace dlma {
 // 16^3 x 32 with 32 modes, 128 distillation and 32 noise solutions the projections and
 // Grams took 23.8 ms as one block per field and four modes, every field read nev / 4
 // times for tau and 8 times for the Grams, and the sums over groups and spins 43 ms on
-// the host (67.2 ms per call); now 1.89 ms per call, 41 TFLOP/s of a 64 TFLOP/s FP64
+// the host (67.2 ms per call); now 1.75 ms per call, 41 TFLOP/s of a 64 TFLOP/s FP64
 // matrix product.
 typedef double d4 __attribute__((ext_vector_type(4)));
 
+__device__ __forceinline__ double2 cconjmul(double2 a, double2 b) { return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x); }
 __device__ __forceinline__ d4 mma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 // Result tile (re, im) of one wave into [16][16] complex numbers, rows limited to nrow
@@ -49,7 +50,8 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
     const int lb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     const int nub = (a.nunit + 3) / 4;
     const int ub = lb % nub, r = lb / nub;
-    const int kc = r % a.ks, ti = r / a.ks;
+    const int rk = r / a.nkb, kc = rk % a.ks, ti = rk / a.ks;
+    const int k0 = a.k0 + (r - rk * a.nkb) * 16 * MT;  // first of this wave's modes
     const int unit = ub * 4 + (int)(threadIdx.x >> 6);
     if (ti >= a.nt || unit >= a.nunit) return;  // whole waves
     const int t = a.tlist ? a.tlist[ti] : a.t0 + ti;
@@ -66,7 +68,7 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
     const double2* pv[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
-        const int k = a.k0 + 16 * b + m;  // modes past the last repeat it; their rows are not stored
+        const int k = k0 + 16 * b + m;  // modes past the last repeat it; their rows are not stored
         pv[b] = a.Vall + (((long)(t - a.tv0) * a.nev + (k < a.nev ? k : a.nev - 1)) * L3 + x0 + q) * 3;
     }
     const d4 z = {0.0, 0.0, 0.0, 0.0};
@@ -123,7 +125,7 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
         if (s == 0 || two)
 #pragma unroll
             for (int b = 0; b < MT; ++b) {
-                const int k = a.k0 + 16 * b;
+                const int k = k0 + 16 * b;
                 const int set = NOISE ? 2 * g0 + s : g0 + s;
                 if (k < a.nev)
                     store_tile(a.taup + ((((long)kc * nset + set) * a.nt + ti) * a.nev + k) * 16, lane, a.nev - k, tr[s][b], tm[s][b]);
@@ -137,9 +139,9 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
 }
 
 // Site chunks per (unit, timeslice): about 4096 waves in all (eight per SIMD slot pair),
-// at least 16 steps of four sites each
+// at least 16 steps of four sites each, or 4 while there are fewer than 64 chunks
 static int contract_chunks(long L3, long waves) {
-    const long want = (4096 + waves - 1) / waves, most = L3 / 64 > 1 ? L3 / 64 : 1;
+    const long want = (4096 + waves - 1) / waves, most = std::max(1L, std::max(L3 / 64, std::min(L3 / 16, 64L)));
     return (int)(want < 1 ? 1 : (want > most ? most : want));
 }
 
@@ -148,27 +150,44 @@ int contract_ks(const Geo& g, int nt, int units) {
 }
 
 template <bool NOISE> static hipError_t launch_contract_t(ContractArgs a, bool gram, hipStream_t s) {
-    const long nb = (long)a.nt * a.ks * ((a.nunit + 3) / 4);
-    const dim3 grid((unsigned)((nb + 7) / 8 * 8)), block(256);
-    for (a.k0 = 0; a.k0 < a.nev; a.k0 += 32) {
-        const bool one = a.nev - a.k0 <= 16, gr = gram && a.k0 == 0;
-        if (gr && one) hipLaunchKernelGGL((k_contract<NOISE, true, 1>), grid, block, 0, s, a);
-        else if (gr) hipLaunchKernelGGL((k_contract<NOISE, true, 2>), grid, block, 0, s, a);
-        else if (one) hipLaunchKernelGGL((k_contract<NOISE, false, 1>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_contract<NOISE, false, 2>), grid, block, 0, s, a);
+    if (a.nev <= 0) return hipSuccess;
+    const dim3 block(256);
+    auto grid = [&] { return dim3((unsigned)(((long)a.nt * a.ks * ((a.nunit + 3) / 4) * a.nkb + 7) / 8 * 8)); };
+    a.k0 = 0;
+    a.nkb = 1;
+    if (gram) {  // with the first modes
+        if (a.nev <= 16) hipLaunchKernelGGL((k_contract<NOISE, true, 1>), grid(), block, 0, s, a);
+        else hipLaunchKernelGGL((k_contract<NOISE, true, 2>), grid(), block, 0, s, a);
+        a.k0 = 32;
     }
+    const int left = a.nev - a.k0;
+    if (left <= 0) return hipGetLastError();
+    // 32 modes per wave halve the reads of the fields; 16 while there are too few waves
+    const bool one = left <= 16 || (long)a.nt * a.ks * a.nunit * ((left + 31) / 32) < 1024;
+    a.nkb = one ? (left + 15) / 16 : (left + 31) / 32;
+    if (one) hipLaunchKernelGGL((k_contract<NOISE, false, 1>), grid(), block, 0, s, a);
+    else hipLaunchKernelGGL((k_contract<NOISE, false, 2>), grid(), block, 0, s, a);
     return hipGetLastError();
 }
 
-// tau[i] = sum of its ks partials, in order
-__global__ void k_sum_parts(const double2* __restrict__ p, long n, int ks, double2* __restrict__ o) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    double2 v = p[i];
-    for (int k = 1; k < ks; ++k) {
+// tau[i] = sum of its ks partials: 16 values per block, sixteen slices of the partials each
+__global__ void __launch_bounds__(256) k_sum_parts(const double2* __restrict__ p, long n, int ks, double2* __restrict__ o) {
+    __shared__ double2 sm[16][16];
+    const int e = (int)threadIdx.x & 15, sl = (int)threadIdx.x >> 4;
+    const long i = (long)blockIdx.x * 16 + e;  // n is a multiple of 16
+    double2 v = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int k = sl; k < ks; k += 16) {
         const double2 w = p[i + k * n];
         v.x += w.x;
         v.y += w.y;
+    }
+    sm[sl][e] = v;
+    __syncthreads();
+    if (sl > 0) return;
+    for (int k = 1; k < 16; ++k) {
+        v.x += sm[k][e].x;
+        v.y += sm[k][e].y;
     }
     o[i] = v;
 }
@@ -182,7 +201,7 @@ hipError_t launch_contract(const ContractArgs& a0, bool noise, bool gram, double
     const hipError_t e = noise ? launch_contract_t<true>(a, gram, s) : launch_contract_t<false>(a, gram, s);
     if (e != hipSuccess || a.ks == 1) return e;
     const long n = (long)(noise ? 2 : 1) * a.ng * a.nt * a.nev * 16;
-    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.taup, n, a.ks, tau);
+    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)(n / 16)), dim3(256), 0, s, a.taup, n, a.ks, tau);
     return hipGetLastError();
 }
 
@@ -214,10 +233,12 @@ constexpr int PROJ_BLOCKS = 4;  // k_proj_gram blocks per timeslice (16 partials
 
 // C[gamma][part][delta] from the partial sums of the three Grams and their projected
 // forms, block delta: thread e = (i, j) of four slices adds its entry over the partials,
-// W[gamma][e] holds the piece's spin weights sum_Gamma N[s][s'] M[a][b] / (Gammas).
+// W[gamma][e] holds the piece's spin weights sum_Gamma N[s][s'] M[a][b] / (Gammas).  A chain
+// of sums: a wave per (gamma, part) with shuffles, 20 us; the whole block on each in turn, two
+// barriers apiece, took 80 us.
 __global__ void __launch_bounds__(1024) k_corr_pieces(CorrPiecesArgs a) {
     __shared__ double2 sm[4][256];
-    __shared__ double lds[16];
+    __shared__ double2 pc[DLMA_NPARTS][256];
     const int d = blockIdx.x, T = a.T, t = (a.t_src + d) % T;
     const int e = (int)threadIdx.x & 255, sl = (int)threadIdx.x >> 8;
     const int eT = (e & 15) * 16 + (e >> 4);
@@ -262,17 +283,30 @@ __global__ void __launch_bounds__(1024) k_corr_pieces(CorrPiecesArgs a) {
     auto sub = [](double2 x, double2 y) { return make_double2(x.x - y.x, x.y - y.y); };
     const double2 piece[DLMA_NPARTS] = {sub(F[2][0], F[2][1]), F[2][1], sub(sub(F[1][0], F[2][0]), sub(F[1][1], F[2][1])),
                                         sub(F[1][1], F[2][1]), F[1][0], F[0][1], sub(F[0][0], F[0][1])};
-    for (int gi = 0; gi < DLMA_NGAMMA; ++gi) {
-        const double2 w = a.W[gi * 256 + e];
-        const bool on = sl == 0 && (w.x != 0.0 || w.y != 0.0);
-        for (int p = 0; p < DLMA_NPARTS; ++p) {
-            const double2 c = piece[p];
-            const double re = block_sum<1024>(on ? w.x * c.x - w.y * c.y : 0.0, lds);
-            const double im = block_sum<1024>(on ? w.x * c.y + w.y * c.x : 0.0, lds);
-            if (threadIdx.x == 0) {
-                const double s = p < 5 ? a.inv_nvec : 1.0;
-                a.C[((long)gi * DLMA_NPARTS + p) * T + d] = make_double2(re * s, im * s);
+    if (sl == 0)
+        for (int p = 0; p < DLMA_NPARTS; ++p) pc[p][e] = piece[p];
+    __syncthreads();
+    // one wave per (gamma, part)
+    const int lane = (int)threadIdx.x & 63;
+    for (int o = (int)threadIdx.x >> 6; o < DLMA_NGAMMA * DLMA_NPARTS; o += 16) {
+        const int gi = o / DLMA_NPARTS, p = o - gi * DLMA_NPARTS;
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double2 w = a.W[gi * 256 + 64 * k + lane], c = pc[p][64 * k + lane];
+            if (w.x != 0.0 || w.y != 0.0) {  // absent entries enter nothing, not even a NaN
+                re += w.x * c.x - w.y * c.y;
+                im += w.x * c.y + w.y * c.x;
             }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            re += __shfl_xor(re, off, 64);
+            im += __shfl_xor(im, off, 64);
+        }
+        if (lane == 0) {
+            const double s = p < 5 ? a.inv_nvec : 1.0;
+            a.C[((long)gi * DLMA_NPARTS + p) * T + d] = make_double2(re * s, im * s);
         }
     }
 }
@@ -293,13 +327,14 @@ hipError_t launch_corr_pieces(const CorrPiecesArgs& a, hipStream_t s) {
 //
 // box(t) in = sum_k v_k c_k with c = V^dag in on the contraction kernel (a right-hand side
 // is a field, four of them a column set), then out = c V or in - c V on timeslice t as a
-// matrix product (32 rows (site, colour) and eight right-hand sides per wave) in one
+// matrix product (32 rows (site, colour) and four or eight right-hand sides per wave) in one
 // launch with the zero fill of the other timeslices.  Bound: the fill, a stream of
 // stores.  With a thread per (site, spin) storing 48 bytes apart and a block per (mode,
 // right-hand side) for c, 32 modes and right-hand sides at 24^3 x 48 took 1.32 ms;
-// 0.815 ms so (5.9 TB/s of stores).
+// 0.77 ms so (6.3 TB/s of stores).
 constexpr int FILL_PER_BLOCK = 1024;
 
+template <int H>  // column sets per wave
 __global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long fs,
                                                     int t, int nev, const double2* __restrict__ coef, int nrhs, int mode,
                                                     unsigned nab, unsigned nrb) {
@@ -318,7 +353,7 @@ __global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ 
     }
     const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
     const long nrow = L3 * 3;
-    const unsigned ub = blockIdx.x / nrb;  // right-hand sides 8 ub .. 8 ub + 7
+    const unsigned ub = blockIdx.x / nrb;  // right-hand sides 4 H ub ..
     const long r0 = ((long)(blockIdx.x - ub * nrb) * 4 + (threadIdx.x >> 6)) * 32;
     if (r0 >= nrow) return;  // whole waves
     long row[2];
@@ -327,21 +362,25 @@ __global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ 
         const long r = r0 + 16 * b + m;
         row[b] = r < nrow ? r : nrow - 1;
     }
-    const bool two = 8 * (int)ub + 4 < nrhs;
+    const bool two = H == 2 && 8 * (int)ub + 4 < nrhs;
     const d4 z = {0.0, 0.0, 0.0, 0.0};
-    d4 re[2][2] = {{z, z}, {z, z}}, im[2][2] = {{z, z}, {z, z}};
+    d4 re[H][2], im[H][2];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) re[h][b] = im[h][b] = z;
     const double2* v = Vt + (long)q * nrow;
-    const double2* c = coef + ((long)ub * 2 * nev + q) * 16 + m;
+    const double2* c = coef + ((long)ub * H * nev + q) * 16 + m;
     const double2 zz = make_double2(0.0, 0.0);
     for (int k = 0; k < nev; k += 4) {
         const bool ok = k + q < nev;
-        double2 x[2], w[2];
+        double2 x[2], w[H];
 #pragma unroll
         for (int b = 0; b < 2; ++b) x[b] = ok ? v[(long)k * nrow + row[b]] : zz;
         w[0] = ok ? c[(long)k * 16] : zz;
-        w[1] = ok && two ? c[((long)nev + k) * 16] : zz;
+        if (H == 2) w[H - 1] = ok && two ? c[((long)nev + k) * 16] : zz;
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < H; ++h)
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 re[h][b] = mma64(x[b].x, w[h].x, re[h][b]);
@@ -351,8 +390,8 @@ __global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ 
             }
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int r = 8 * (int)ub + 4 * h + (m >> 2);
+    for (int h = 0; h < H; ++h) {
+        const int r = 4 * (H * (int)ub + h) + (m >> 2);
         if (r >= nrhs) continue;
         const long base = (long)r * fs + tofs + (m & 3) * 3;
 #pragma unroll
@@ -372,11 +411,48 @@ __global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ 
     }
 }
 
-// site chunks of c: about 96 sites each (24 steps of the contraction kernel), at most 128,
-// and few enough that four right-hand sides' partials fit PROJ_PART_CAP
+// c of one mode and one right-hand side per block, for few of them
+__global__ void __launch_bounds__(256) k_proj_coef(const double2* __restrict__ Vt, const double2* __restrict__ in, long L3, long tofs,
+                                                   long fs, int nev, double2* __restrict__ coef) {
+    const int k = blockIdx.x, r = blockIdx.y;
+    const double2* v = Vt + (long)k * L3 * 3;
+    const double2* f = in + (long)r * fs + tofs;
+    // thread (site, spin): 48 contiguous bytes, four sites' spins contiguous
+    const int sp = (int)threadIdx.x & 3;
+    double2 a = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (long x = threadIdx.x >> 2; x < L3; x += 64)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double2 p = cconjmul(v[x * 3 + c], f[(x * 4 + sp) * 3 + c]);
+            a.x += p.x;
+            a.y += p.y;
+        }
+    // over the sixteen sites of a wave, then the waves
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) {
+        a.x += __shfl_xor(a.x, off, 64);
+        a.y += __shfl_xor(a.y, off, 64);
+    }
+    __shared__ double2 sm[4][4];
+    const int lane = (int)threadIdx.x & 63;
+    if (lane < 4) sm[threadIdx.x >> 6][lane] = a;
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double2 t = sm[0][threadIdx.x];
+        for (int w = 1; w < 4; ++w) {
+            t.x += sm[w][threadIdx.x].x;
+            t.y += sm[w][threadIdx.x].y;
+        }
+        coef[((long)(r >> 2) * nev + k) * 16 + (r & 3) * 4 + threadIdx.x] = t;
+    }
+}
+
+// site chunks of c: 16 sites each (four steps of the contraction kernel, 1.5 us apiece), at
+// most 256, and few enough that four right-hand sides' partials fit PROJ_PART_CAP
 int project_ks(const Geo& g, int nev) {
     const long L3 = (long)g.Z * g.Y * g.X;
-    const long k = std::min(std::min(L3 / 96, 128L), PROJ_PART_CAP / (16L * std::max(1, nev)));
+    const long k = std::min(std::min(L3 / 16, 256L), PROJ_PART_CAP / (16L * std::max(1, nev)));
     return (int)std::max(1L, k);
 }
 
@@ -391,12 +467,22 @@ hipError_t launch_project(const double2* Vt, const double2* in, double2* out, co
     const unsigned nfb = (unsigned)((fs + FILL_PER_BLOCK - 1) / FILL_PER_BLOCK);
     // pairs of sets share a wave, and the grid stays below 2^31 blocks
     sets = std::min(sets, std::max(2L, (1L << 30) / (4L * nfb)));
-    if (sets > 2) sets -= sets & 1;
+    if (sets > 2 && 4 * sets < nrhs) sets -= sets & 1;
     if (sets < 1) return hipErrorInvalidValue;
+    // Few modes and right-hand sides on a small timeslice: one launch for c instead of the
+    // contraction's two, while a block's passes over its L3 sites stay short.  8 modes, one
+    // right-hand side (us per call): 4^3 27 against 32, 600 sites 28 against 33, 12^3 31
+    // against 33, 16^3 38 against 34; 64 modes, 64 right-hand sides: 4^3 46 against 49, 600
+    // sites 80 against 67.
+    const bool direct = L3 <= 2048 && (double)nev * nrhs * L3 * L3 <= (double)(1L << 28);
+    // one column set per wave until the waves of 32 rows fill the chip
+    const int H = nrhs > 4 && (L3 * 3 + 31) / 32 * ((nrhs + 7) / 8) >= 1024 ? 2 : 1;
     for (long r0 = 0; r0 < nrhs; r0 += 4 * sets) {
         const int nr = (int)std::min<long>(4 * sets, nrhs - r0);
         const double2* inr = in + r0 * fs;
-        if (nev > 0) {  // no modes: box(t) = 0 and the apply kernel reads no coefficient
+        if (nev > 0 && direct) {
+            hipLaunchKernelGGL(k_proj_coef, dim3(nev, nr), dim3(256), 0, s, Vt, inr, L3, (long)t * L3 * 12, fs, nev, coef);
+        } else if (nev > 0) {  // no modes: box(t) = 0 and the apply kernel reads no coefficient
             ContractArgs a = {};
             a.Vall = Vt; a.f0 = inr; a.L3 = L3; a.fs = fs;
             a.t0 = a.tv0 = t;
@@ -405,8 +491,8 @@ hipError_t launch_project(const double2* Vt, const double2* in, double2* out, co
             const hipError_t e = launch_contract(a, false, false, coef, s);
             if (e != hipSuccess) return e;
         }
-        const unsigned nab = nrb * (unsigned)((nr + 7) / 8);
-        hipLaunchKernelGGL(k_proj_apply, dim3(nab + nfb * (unsigned)nr), dim3(256), 0, s, Vt, inr, out + r0 * fs, L3, fs, t, nev,
+        const unsigned nab = nrb * (unsigned)((nr + 4 * H - 1) / (4 * H));
+        hipLaunchKernelGGL(H == 2 ? k_proj_apply<2> : k_proj_apply<1>, dim3(nab + nfb * (unsigned)nr), dim3(256), 0, s, Vt, inr, out + r0 * fs, L3, fs, t, nev,
                            coef, nr, mode, nab, nrb);
     }
     return hipGetLastError();

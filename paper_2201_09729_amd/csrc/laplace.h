@@ -60,7 +60,7 @@ struct ContractArgs {
     int nf;            // fields of f0 (4 ng, or fewer in the last group: its further columns repeat the last field)
     double2* taup;     // partials [ks][set][nt][nev][16] (unused with ks = 1)
     double2* gramp;    // [nt][ks][unit][noise ? 2 : 1][16][16]: (re, X) of (f0, f0), then (f1, f0)
-    int nunit, k0;     // set by the launcher
+    int nunit, k0, nkb;  // set by the launcher
     long chunk;
 };
 int contract_ks(const Geo& g, int nt, int units);
