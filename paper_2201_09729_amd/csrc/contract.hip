@@ -549,7 +549,7 @@ hipError_t launch_tau_weights(const double2* tau, const double2* WP, const int* 
 // of each of the unit's two halves the columns, so V is read once for both halves.
 // Bound: the matrix cores and the field streams alike.  At 12^3 x 24 with 21 modes,
 // 13 distillation and 6 noise groups forward and backward together took 20.9 ms (tau and
-// tau' on the host, a VALU kernel here), 2.50 ms with the projections above, 1.89 ms so.
+// tau' on the host, a VALU kernel here), 2.50 ms with the projections above, 1.85 ms so.
 template <bool NOISE>
 __global__ void __launch_bounds__(256) k_corr_grad(CorrGradArgs a) {
     constexpr int NIN = NOISE ? 32 : 16;
