@@ -117,30 +117,6 @@ extern "C" int dlma_gauge_info(dlma_gauge_t h, int dims_out[4], double* kappa_ou
     return DLMA_OK;
 }
 
-// y = D x (or g5 D g5 x) on full FP64 even-odd fields, both parities in one launch
-int apply_full64(Gauge* g, void* in_eo, void* out_eo, int nrhs, int dagger, hipStream_t s) {
-    std::vector<HopJob<P64>> jobs;
-    for (int par = 0; par < 2; ++par) {
-        HopJob<P64> j = hop_job<P64>(g, par, nrhs, 1);
-        j.U = g->U64.as<double2>();
-        j.C = g->Cl64[par].as<double2>();
-        j.x = full_view(in_eo, g->Vh, par);
-        j.in = full_view(in_eo, g->Vh, 1 - par);
-        j.out = full_view(out_eo, g->Vh, par);
-        j.ca = 1.0;
-        j.ch = -0.5;
-        jobs.push_back(j);
-    }
-    int nblk = assign_blocks(jobs);
-    Buf dj;
-    DLMA_TRY(dj.allocate(sizeof(HopJob<P64>) * jobs.size()));
-    DLMA_HIP(hipMemcpyAsync(dj.p, jobs.data(), sizeof(HopJob<P64>) * jobs.size(), hipMemcpyHostToDevice, s));
-    HopCfg c{K2, dagger ? (F_G5IN | F_G5OUT) : 0, 1};
-    DLMA_HIP(launch_hop<P64>(c, dj.as<HopJob<P64>>(), (int)jobs.size(), nblk, s));
-    DLMA_HIP(hipStreamSynchronize(s));
-    return DLMA_OK;
-}
-
 extern "C" int dlma_apply_dw(dlma_gauge_t h, const void* in, void* out, int nrhs, int dagger, void* stream) {
     Gauge* g = (Gauge*)h;
     if (!g) return fail(DLMA_EINVAL, "NULL handle");
@@ -149,13 +125,16 @@ extern "C" int dlma_apply_dw(dlma_gauge_t h, const void* in, void* out, int nrhs
     if (!in || !out) return fail(DLMA_EINVAL, "NULL field pointer");
     if (in == out) return fail(DLMA_EINVAL, "in and out must not overlap");
     hipStream_t s = S(stream);
-    size_t bytes = sizeof(double2) * (size_t)nrhs * 24 * g->Vh;
-    Buf a, b;
-    DLMA_TRY(a.allocate(bytes));
-    DLMA_TRY(b.allocate(bytes));
-    DLMA_HIP(launch_canon_to_eo((const double2*)in, a.as<double2>(), g->geo, nrhs, s));
-    DLMA_TRY(apply_full64(g, a.p, b.p, nrhs, dagger, s));
-    DLMA_HIP(launch_eo_to_canon(b.as<double2>(), (double2*)out, g->geo, nrhs, s));
+    DiracArgs a = {};
+    a.U = g->U64.as<double2>();
+    a.C0 = g->Cl64[0].as<double2>();
+    a.C1 = g->Cl64[1].as<double2>();
+    a.in = (const double2*)in;
+    a.out = (double2*)out;
+    a.g = g->geo;
+    a.nrhs = nrhs;
+    a.sg = dagger ? -1.0 : 1.0;
+    DLMA_HIP(launch_dirac(a, s));
     DLMA_HIP(hipStreamSynchronize(s));
     return DLMA_OK;
 }

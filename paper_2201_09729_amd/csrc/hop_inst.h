@@ -39,7 +39,6 @@ hipError_t launch_hop<DLMA_PREC>(const HopCfg& c, const HopJob<DLMA_PREC>* djobs
 #endif
 #if DLMA_PREC == 0
     // FP64 only: full operator, defect-correction residual, Schur source, reconstruction
-    DLMA_HOP_ALLNB(K2, F_G5IN | F_G5OUT)
     DLMA_HOP_ALLNB(K2, F_HASB | F_NORM)
     DLMA_HOP_ALLNB(K2, F_HASB | F_NORM | F_ACCX)  // even-site residual with the accumulation fused
     DLMA_HOP_ALLNB(K2, F_NOA)

@@ -122,6 +122,16 @@ template <int P> hipError_t launch_convert_pairs(const double2* src, void* dst, 
 hipError_t launch_regroup16(const double2* src, void* dst, int M, int K, int G, int Vh, hipStream_t s);
 
 // full FP64 fields <-> canonical
+struct DiracArgs {
+    const double2 *U, *C0, *C1;  // links and clover planes per parity (P64)
+    const double2* in;
+    double2* out;
+    Geo g;
+    int nrhs;
+    double sg;                   // 1: D, -1: D^dag
+    int ng, nT, R, nstrip, nch;  // set by the launcher
+};
+hipError_t launch_dirac(DiracArgs a, hipStream_t s);  // dirac.hip
 hipError_t launch_canon_to_eo(const double2* can, double2* eo, const Geo& g, int nrhs, hipStream_t s, int g5 = 0);
 hipError_t launch_eo_to_canon(const double2* eo, double2* can, const Geo& g, int nrhs, hipStream_t s, int g5 = 0);
 
