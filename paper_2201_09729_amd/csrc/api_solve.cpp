@@ -123,9 +123,9 @@ TileHopJob tile_hop_job(const Gauge* g, int par, int nrhs) {
     j.par = par;
     j.nrhs = nrhs;
     j.ntile = tile_count(nrhs);
-    j.R = tile_hop_rows(g->geo);
+    j.R = tile_hop_rows(g->geo, nrhs);
     j.nstrip = ceil_div(g->geo.Y, j.R);
-    j.nbt = tile_hop_nbt(g->geo);
+    j.nbt = tile_hop_nbt(g->geo, nrhs);
     j.pstride = g->geo.T * j.nbt;
     j.L = g->tL[par].as<uint32_t>();
     return j;
@@ -187,8 +187,8 @@ template <int P> int alloc_cfg(Cfg& c, bool bicg, bool tiled, hipStream_t s) {
     c.vnsb = ceil_div(Vh, VEC_BS);
     int pmax = std::max(std::max(2 * c.hnsb, 3 * c.vnsb), hop_nq(F_DOTX | F_DOTXH) * c.hnsb);
     if (tiled) {
-        c.thnsb = g->geo.T * tile_hop_nbt(g->geo);
-        c.tvnsb = ceil_div(Vh, TVEC_SITES);
+        c.thnsb = g->geo.T * tile_hop_nbt(g->geo, c.nrhs);
+        c.tvnsb = ceil_div(Vh, tile_vec_sites(Vh, c.nrhs));
         c.tcnsb = ceil_div(Vh, TCONV_SITES);
         pmax = std::max(pmax, std::max(std::max(hop_nq(F_DOTX | F_DOTXH) * c.thnsb, 2 * c.tvnsb), c.tcnsb));
     }
@@ -415,7 +415,7 @@ template <int P> int build_tables(std::vector<Cfg>& cs, Tables<P>& t, int nb, in
             TileHopJob d = j1; d.in = sf; d.out = y; tk1s.push_back(d);
             TileHopJob e = j2; e.x = sf; e.in = y; e.out = tf; tk2t.push_back(e);
             TileVecJob tv = {};
-            tv.Vh = Vh; tv.nrhs = n; tv.ntile = tile_count(n); tv.nsb = c.tvnsb;
+            tv.Vh = Vh; tv.nrhs = n; tv.ntile = tile_count(n); tv.nsb = c.tvnsb; tv.sites = tile_vec_sites(Vh, n);
             tv.r = r; tv.rh = rh; tv.p = p; tv.v = v; tv.s = sf; tv.t = tf; tv.x = x;
             tv.alpha = c.balpha; tv.omega = c.bomega; tv.beta = c.bbeta;
             tv.active = c.active; tv.part = c.part.as<double>(); tv.part_s = c.parts.as<double>(); tv.pstride = c.tvnsb;

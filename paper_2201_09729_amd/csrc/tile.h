@@ -20,11 +20,16 @@
 namespace dlma {
 
 constexpr int TILE = 16;         // right-hand sides per tile
-constexpr int TILE_SITES = 48;   // sites per stencil block, about
-constexpr int TVEC_SITES = 64;   // sites per block of the vector kernels
 constexpr int TCONV_SITES = 32;  // sites per block of the layout conversions
 
 inline int tile_count(int nrhs) { return (nrhs + TILE - 1) / TILE; }
+// Sites per block of the stencil (about) and vector kernels, whose four waves take them in
+// turn: enough to spread a block's start, few while the blocks do not fill the chip.  8x12x10x12 with
+// 16 right-hand sides: the x, r, p update 24 us with 64 sites per block.  48x24^3 with 96: 24 to
+// 100 sites of a stencil block are alike, 256 are 10% slower.
+inline bool tile_short(int Vh, int nrhs) { return (long)Vh * tile_count(nrhs) < 65536; }
+inline int tile_hop_sites(int Vh, int nrhs) { return tile_short(Vh, nrhs) ? 8 : 48; }
+inline int tile_vec_sites(int Vh, int nrhs) { return tile_short(Vh, nrhs) ? 8 : 64; }
 
 // One Schur stencil of one configuration.  A block covers R y rows (the last strip fewer) of
 // one z plane of one timeslice, for one tile.
@@ -40,13 +45,23 @@ struct TileHopJob {
     double* part;          // part[(r * NQ + q) * pstride + site block]
     int pstride;           // T * nbt
 };
-inline int tile_hop_rows(const Geo& g) {
-    const int r = TILE_SITES / g.Xh;
+inline int tile_hop_rows(const Geo& g, int nrhs) {
+    const int r = tile_hop_sites(g.Vh, nrhs) / g.Xh;
     return r < 1 ? 1 : (r > g.Y ? g.Y : r);
 }
-inline int tile_hop_nbt(const Geo& g) { const int r = tile_hop_rows(g); return g.Z * ((g.Y + r - 1) / r); }
+inline int tile_hop_nbt(const Geo& g, int nrhs) { const int r = tile_hop_rows(g, nrhs); return g.Z * ((g.Y + r - 1) / r); }
+// XCDs along the timeslices of a launch (the rest along z): all eight where they divide the
+// timeslices or leave few idle, else the largest power of two that does
+HD int tile_xcd_t(int Tw) {
+    int n = 8;
+    while (n > 1 && Tw % n != 0 && Tw < 4 * n) n >>= 1;
+    return n;
+}
 // blocks of a launch of one job over twn timeslices (twn = T: all of them)
-inline int tile_hop_blocks(const TileHopJob& j, int twn) { return 8 * ((twn + 7) / 8) * j.nbt * j.ntile; }
+inline int tile_hop_blocks(const TileHopJob& j, int twn) {
+    const int nT = tile_xcd_t(twn), nZ = 8 / nT;
+    return 8 * ((twn + nT - 1) / nT) * ((j.g.Z + nZ - 1) / nZ) * j.nstrip * j.ntile;
+}
 
 // kind, flags as hop.h (K1 0; K2 0, F_DOTR, F_DOTX | F_DOTXH); tw0, twn as HopCfg
 hipError_t launch_tile_hop(int kind, int flags, const TileHopJob* d, int njob, int nblocks, int tw0, int twn,
@@ -54,7 +69,8 @@ hipError_t launch_tile_hop(int kind, int flags, const TileHopJob* d, int njob, i
 
 // Steps of one iteration (BiVecMode BV_RR, BV_SH, BV_XRP) on tile fields
 struct TileVecJob {
-    int Vh, nrhs, ntile, nsb, blk0;  // nsb = ceil(Vh / TVEC_SITES); blocks = nsb * ntile
+    int Vh, nrhs, ntile, nsb, blk0;  // nsb = ceil(Vh / sites); blocks = nsb * ntile
+    int sites;                       // per block
     uint32_t *r, *rh, *p, *v, *s, *t, *x;
     const double2 *alpha, *omega, *beta;
     const int* active;

@@ -28,9 +28,9 @@ __device__ __forceinline__ double sum_over_q(double v) {
     return v + __shfl_xor(v, 32, 64);
 }
 
-HD void wst3(const WSrc& s, uint32_t v, uint32_t u, u32x3 w) {
+template <int CP> HD void wst3(const WSrc& s, uint32_t v, uint32_t u, u32x3 w) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_raw_buffer_store_b96(w, s.r, (int)v, (int)u, CP_NT);
+    __builtin_amdgcn_raw_buffer_store_b96(w, s.r, (int)v, (int)u, CP);
 #else
     (void)s; (void)v; (void)u; (void)w;
 #endif

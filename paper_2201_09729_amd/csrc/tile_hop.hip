@@ -14,9 +14,9 @@
 // 2^-24).
 //   K1 (odd):  out = C (ch H in), ch = -1/2;  K2 (even): out = C x + 1/2 H in,
 // K2's own-site term being a ninth direction of the same product.
-// Block order: an XCD owns a contiguous range of timeslices and walks strips of y rows
-// outermost, then z, then its timeslices, so the +-t and +-z neighbours of a strip stay in
-// its L2.
+// Block order: an XCD owns a contiguous range of timeslices (and of z, with few timeslices)
+// and walks strips of y rows outermost, then z, then its timeslices, so the +-t and +-z
+// neighbours of a strip stay in its L2.
 // Bound: latency and the misses of L2 (a site's 6 KB of neighbours come 1.6 to 2 times
 // over from the memory side); 75 to 85 registers keep six waves per SIMD.  48x24^3 with 96
 // right-hand sides: K1 1.29, K2 1.44 ms (1.9 and 2.1 ms with one thread per site and one to
@@ -73,13 +73,15 @@ k_tile_hop(const TileHopJob* __restrict__ jobs, int njob, int tw0, int twn) {
     // block -> (tile, strip, z, timeslice)
     const int lb = bid - J.blk0, xcd = lb & 7, k0 = lb >> 3;
     const int T = J.g.T, Tw = twn > 0 ? twn : T;
-    const int tl = xcd * Tw / 8, nt = (xcd + 1) * Tw / 8 - tl;
-    if (nt == 0) return;
-    const int per = J.nbt * nt;
+    const int nT = tile_xcd_t(Tw), nZ = 8 / nT, xt = xcd % nT, xz = xcd / nT;
+    const int tl = xt * Tw / nT, nt = (xt + 1) * Tw / nT - tl;
+    const int zl = xz * J.g.Z / nZ, nz = (xz + 1) * J.g.Z / nZ - zl;
+    const int per = J.nstrip * nz * nt;
+    if (per == 0) return;
     const int tile = k0 / per;
     if (tile >= J.ntile) return;
     const int kk = k0 - tile * per, sz = kk / nt;
-    const int strip = sz / J.g.Z, z = sz - strip * J.g.Z;
+    const int strip = sz / nz, z = zl + sz - strip * nz;
     const int tw = tl + (kk - sz * nt);
     const int t = twn > 0 ? (tw0 + tw < T ? tw0 + tw : tw0 + tw - T) : tw;
     const int Y = J.g.Y, Xh = J.g.Xh, Vh = J.g.Vh;
@@ -226,7 +228,7 @@ k_tile_hop(const TileHopJob* __restrict__ jobs, int njob, int tw0, int twn) {
         for (int e = 0; e < 3; ++e) ow[e] = pack16(v[2 * e], v[2 * e + 1]);
         if (use) {
             wide_store_begin();
-            wst3(out, lane12, 768u * (uint32_t)cb, (u32x3){ow[0], ow[1], ow[2]});
+            wst3<CP_NT>(out, lane12, 768u * (uint32_t)cb, (u32x3){ow[0], ow[1], ow[2]});
             wide_store_end();
         }
         if (DOTS) {
