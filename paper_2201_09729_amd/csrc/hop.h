@@ -156,7 +156,8 @@ HD void hop_site(const HopJob<P>& J, int cb, int g0, double (&qs)[NB][HOP_NQ_MAX
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         int r = g0 + j;
-        use[j] = rhs_active(J, r);
+        // (a lone right-hand side is active, or the kernel has left: no branches between the loads)
+        use[j] = NB == 1 || rhs_active(J, r);
         for (int q = 0; q < HOP_NQ_MAX; ++q) qs[j][q] = 0.0;
     }
     R acc[NB][24];
