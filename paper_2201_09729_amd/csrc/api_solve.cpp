@@ -565,13 +565,9 @@ template <int P> int cg_iteration(std::vector<Cfg>& cs, Tables<P>& t, int nb, co
 
 // One BiCGStab iteration on Dhat for every configuration (the steps of bicg.hip with
 // the solver's stencil kernels for the two operator applications).
-// FP16 fields take the merged iteration: K2 for t also forms (rh, t) of the stored t
-// and the s step (rh, s) of the stored s, so rho' = (rh, s) - omega (rh, t) and beta
-// are known before the updates, and x, r and p are updated in one pass (9 launches,
-// 11 field passes of the vector steps instead of 13).  The other precisions run the
-// three separate updates.
-constexpr int bicg_dotx_flags(int P) { return P == P16 ? (F_DOTX | F_DOTXH) : F_DOTX; }
-
+// K2 for t also forms (rh, t) of the stored t and the s step (rh, s) of the stored s, so
+// rho' = (rh, s) - omega (rh, t) and beta are known before the updates, and x, r and p
+// are updated in one pass (9 launches, 11 field passes of the vector steps instead of 13).
 // Timeslice windows of the four stencil launches of one iteration (K1 of p, K2 for v,
 // K1 of s, K2 for t; twn = 0: every timeslice).  Used by the first pass of a single
 // configuration while its Krylov vectors have not reached every timeslice.
@@ -580,7 +576,7 @@ struct IterWin { int tw0[4], twn[4]; };
 template <int P>
 int bicg_iteration(std::vector<Cfg>& cs, Tables<P>& t, int nb, const std::vector<int>& nact, hipStream_t s,
                    const IterWin* w = nullptr) {
-    constexpr int FX = bicg_dotx_flags(P);
+    constexpr int FX = F_DOTX | F_DOTXH;
     double b1 = 0, b2v = 0, b2t = 0;
     if (Profiler::get().on)
         for (size_t i = 0; i < cs.size(); ++i) {
@@ -609,19 +605,12 @@ int bicg_iteration(std::vector<Cfg>& cs, Tables<P>& t, int nb, const std::vector
     DLMA_TRY(launch(0, K1, 0, t.dbk1p, t.bk1, KC_K1, b1));
     DLMA_TRY(launch(1, K2, F_DOTR, t.dbk2v, t.bk2, KC_K2V, b2v));
     DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_ALPHA, s));
-    DLMA_HIP(launch_bivec<P>(bv, t.nbv, t.bbv, P == P16 ? BV_SH : BV_S, s));
+    DLMA_HIP(launch_bivec<P>(bv, t.nbv, t.bbv, BV_SH, s));
     DLMA_TRY(launch(2, K1, 0, t.dbk1s, t.bk1, KC_K1, b1));
     DLMA_TRY(launch(3, K2, FX, t.dbk2t, t.bk2, KC_K2T, b2t));
-    if (P == P16) {
-        DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_OMBETA, s));
-        DLMA_HIP(launch_bivec<P>(bv, t.nbv, t.bbv, BV_XRP, s));
-        DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_CONV, s));
-        return DLMA_OK;
-    }
-    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_OMEGA, s));
-    DLMA_HIP(launch_bivec<P>(bv, t.nbv, t.bbv, BV_XR, s));
-    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_BETA, s));
-    DLMA_HIP(launch_bivec<P>(bv, t.nbv, t.bbv, BV_P, s));
+    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_OMBETA, s));
+    DLMA_HIP(launch_bivec<P>(bv, t.nbv, t.bbv, BV_XRP, s));
+    DLMA_HIP(launch_bifinish(bf, t.nbv, t.bbf, BF_CONV, s));
     return DLMA_OK;
 }
 

@@ -2,8 +2,8 @@
 // Dhat (the alternative inner solver of dlma_solve).  One iteration is
 //   v = Dhat p;            alpha = rho / (rh, v)
 //   s = r - alpha v;       t = Dhat s;       omega = (t, s) / (t, t)
-//   x += alpha p + omega s;  r = s - omega t;  rho' = (rh, r);  beta = (rho'/rho)(alpha/omega)
-//   p = r + beta (p - omega v)
+//   rho' = (rh, s) - omega (rh, t);          beta = (rho'/rho)(alpha/omega)
+//   x += alpha p + omega s;  r = s - omega t;  p = r + beta (p - omega v)
 // with (a, b) = sum conj(a_i) b_i over the even sites.  The operator applications
 // are the solver's stencil kernels; everything here is a streaming pass over fields
 // of the storage precision, in FP64 arithmetic, with deterministic two-stage sums.
@@ -12,7 +12,7 @@
 // rh = r_0 the scalar (rh, r) loses almost all of the spreading residual, which
 // leaves the FP16 recursion to drift from the true residual.  Every right-hand
 // side of a configuration reads the same field (its views have RHS stride 0), so
-// the x/r update and K2 with (rh, v) read it once per site rather than per RHS.
+// the s step and K2 read it once per site rather than per RHS.
 #include "kernels.h"
 
 namespace dlma {
@@ -49,69 +49,11 @@ HD void bv16_cplx(const uint32_t w[12], float n, float v[24]) {
     }
 }
 
-template <int MODE> HD void bivec16(const BiVecJob<P16>& J, int r, uint32_t site, double& q0, double& q1, double& q2) {
+template <int MODE> HD void bivec16(const BiVecJob<P16>& J, int r, uint32_t site, double& q0, double& q1) {
     const uint32_t Vh = (uint32_t)J.Vh, G16 = 16u * Vh, s16 = 16u * site, lo = 4u * site;
     uint32_t wa[12], wb[12], wc[12];
     float a[24], b[24], c[24];
-    if (MODE == BV_S) {  // s = r - alpha v
-        const F16Field R = f16_field(J.r, J.Vh, r), V = f16_field(J.v, J.Vh, r), S = f16_field(J.s, J.Vh, r);
-        const float ar = (float)J.alpha[r].x, ai = (float)J.alpha[r].y;
-        load_words<CP_NT>(R, s16, G16, wa);
-        load_words<CP_NT>(V, s16, G16, wb);
-        const float nr = wldf<CP_NT>(R.n, lo, 0), nv = wldf<CP_NT>(V.n, lo, 0);
-        bv16_cplx(wa, nr, a);
-        bv16_cplx(wb, nv, b);
-#pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            c[2 * i] = a[2 * i] - (ar * b[2 * i] - ai * b[2 * i + 1]);
-            c[2 * i + 1] = a[2 * i + 1] - (ar * b[2 * i + 1] + ai * b[2 * i]);
-        }
-        (void)store16(S, G16, site, c);
-    } else if (MODE == BV_XR) {  // x += alpha p + omega s; r = s - omega t; |r|^2, (rh, r)
-        const F16Field X = f16_field(J.x, J.Vh, r), Pp = f16_field(J.p, J.Vh, r), S = f16_field(J.s, J.Vh, r);
-        const F16Field T = f16_field(J.t, J.Vh, r), R = f16_field(J.r, J.Vh, r), RH = f16_field(J.rh, J.Vh, r);
-        const float alr = (float)J.alpha[r].x, ali = (float)J.alpha[r].y;
-        const float omr = (float)J.omega[r].x, omi = (float)J.omega[r].y;
-        // every load first (the stores to x and r could alias them as far as the
-        // compiler can tell, which would otherwise hold the later loads behind them)
-        uint32_t wt[12], wh[12];
-        load_words<CP_NT>(X, s16, G16, wa);
-        load_words<CP_NT>(Pp, s16, G16, wb);
-        load_words<CP_NT>(S, s16, G16, wc);
-        load_words<CP_NT>(T, s16, G16, wt);
-        load_words(RH, s16, G16, wh);  // cached: every RHS reads this one field
-        const float nx = wldf<CP_NT>(X.n, lo, 0), np = wldf<CP_NT>(Pp.n, lo, 0), ns = wldf<CP_NT>(S.n, lo, 0);
-        const float nt = wldf<CP_NT>(T.n, lo, 0), nh = wldf(RH.n, lo, 0);
-        bv16_cplx(wa, nx, a);
-        bv16_cplx(wb, np, b);
-        bv16_cplx(wc, ns, c);
-#pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            const float pr = b[2 * i], pi = b[2 * i + 1], sr = c[2 * i], si = c[2 * i + 1];
-            a[2 * i] += alr * pr - ali * pi + omr * sr - omi * si;
-            a[2 * i + 1] += alr * pi + ali * pr + omr * si + omi * sr;
-        }
-        bv16_cplx(wt, nt, b);
-#pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            const float tr = b[2 * i], ti = b[2 * i + 1];
-            c[2 * i] -= omr * tr - omi * ti;
-            c[2 * i + 1] -= omr * ti + omi * tr;
-        }
-        (void)store16(X, G16, site, a);
-        // |r|^2 and (rh, r) of the new residual before its storage rounding
-        q0 = (double)store16(R, G16, site, c);
-        for (int i = 0; i < 12; ++i) wa[i] = wh[i];
-        float re = 0.f, im = 0.f;
-#pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            const float hr = lo16(wa[i]), hi = hi16(wa[i]), rr = c[2 * i], ri = c[2 * i + 1];
-            re = __builtin_fmaf(hr, rr, __builtin_fmaf(hi, ri, re));
-            im = __builtin_fmaf(hr, ri, __builtin_fmaf(-hi, rr, im));
-        }
-        q1 = (double)re * nh;
-        q2 = (double)im * nh;
-    } else if (MODE == BV_SH) {  // s = r - alpha v, and (rh, s) of the stored s
+    if (MODE == BV_SH) {  // s = r - alpha v, and (rh, s) of the stored s
         const F16Field R = f16_field(J.r, J.Vh, r), V = f16_field(J.v, J.Vh, r), S = f16_field(J.s, J.Vh, r);
         const F16Field RH = f16_field(J.rh, J.Vh, r);
         const float ar = (float)J.alpha[r].x, ai = (float)J.alpha[r].y;
@@ -133,7 +75,7 @@ template <int MODE> HD void bivec16(const BiVecJob<P16>& J, int r, uint32_t site
         dot16(wh, wc, re, im);
         q0 = (double)re * ((double)nh * ms);
         q1 = (double)im * ((double)nh * ms);
-    } else if (MODE == BV_XRP) {  // x += alpha p + omega s; r = s - omega t; p = r + beta (p - omega v); |r|^2
+    } else {  // BV_XRP: x += alpha p + omega s; r = s - omega t; p = r + beta (p - omega v); |r|^2
         const F16Field X = f16_field(J.x, J.Vh, r), Pp = f16_field(J.p, J.Vh, r), S = f16_field(J.s, J.Vh, r);
         const F16Field T = f16_field(J.t, J.Vh, r), R = f16_field(J.r, J.Vh, r), V = f16_field(J.v, J.Vh, r);
         const float alr = (float)J.alpha[r].x, ali = (float)J.alpha[r].y;
@@ -175,30 +117,67 @@ template <int MODE> HD void bivec16(const BiVecJob<P16>& J, int r, uint32_t site
             b[2 * i + 1] = c[2 * i + 1] + ber * di + bei * dr;
         }
         (void)store16(Pp, G16, site, b);
-    } else {  // BV_P: p = r + beta (p - omega v)
-        const F16Field R = f16_field(J.r, J.Vh, r), Pp = f16_field(J.p, J.Vh, r), V = f16_field(J.v, J.Vh, r);
-        const float ber = (float)J.beta[r].x, bei = (float)J.beta[r].y;
-        const float omr = (float)J.omega[r].x, omi = (float)J.omega[r].y;
-        load_words<CP_NT>(R, s16, G16, wa);
-        load_words<CP_NT>(Pp, s16, G16, wb);
-        load_words<CP_NT>(V, s16, G16, wc);
-        const float nr = wldf<CP_NT>(R.n, lo, 0), np = wldf<CP_NT>(Pp.n, lo, 0), nv = wldf<CP_NT>(V.n, lo, 0);
-        bv16_cplx(wa, nr, a);
-        bv16_cplx(wb, np, b);
-        bv16_cplx(wc, nv, c);
+    }
+}
+
+// The FP64, FP32 and BF16 fields: half a spinor at a time, every load of it before its
+// stores (which could alias them as far as the compiler can tell), FP64 arithmetic.
+template <int P, int MODE> HD void bivec_planes(const BiVecJob<P>& J, int r, int cb, double& q0, double& q1) {
+    using R = typename PT<P>::R;
+    const int Vh = J.Vh;
 #pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            const float dr = b[2 * i] - (omr * c[2 * i] - omi * c[2 * i + 1]);
-            const float di = b[2 * i + 1] - (omr * c[2 * i + 1] + omi * c[2 * i]);
-            b[2 * i] = a[2 * i] + ber * dr - bei * di;
-            b[2 * i + 1] = a[2 * i + 1] + ber * di + bei * dr;
+    for (int h = 0; h < 2; ++h) {
+        R a[12], b[12], c[12], d[12], f[12];
+        if (MODE == BV_RR) {
+            load_half_spinor<P, R>(J.rh, Vh, r, cb, h, a);
+            load_half_spinor<P, R>(J.r, Vh, r, cb, h, c);
+        } else if (MODE == BV_SH) {  // s = r - alpha v, and (rh, s) of the stored s
+            const Cd al = ld2(J.alpha, r);
+            load_half_spinor<P, R>(J.rh, Vh, r, cb, h, a);
+            load_half_spinor<P, R>(J.r, Vh, r, cb, h, c);
+            load_half_spinor<P, R>(J.v, Vh, r, cb, h, b);
+#pragma unroll
+            for (int i = 0; i < 12; i += 2) {
+                const double br = b[i], bi = b[i + 1];
+                c[i] = stored<P, R>((R)((double)c[i] - (al.r * br - al.i * bi)));
+                c[i + 1] = stored<P, R>((R)((double)c[i + 1] - (al.r * bi + al.i * br)));
+            }
+            store_half_spinor<P, R>(J.s, Vh, r, cb, h, c);
         }
-        (void)store16(Pp, G16, site, b);
+        if (MODE == BV_RR || MODE == BV_SH)
+#pragma unroll
+            for (int i = 0; i < 12; i += 2) {
+                const double ar = a[i], ai = a[i + 1], br = c[i], bi = c[i + 1];
+                q0 += ar * br + ai * bi;
+                q1 += ar * bi - ai * br;
+            }
+        if (MODE == BV_XRP) {  // x += alpha p + omega s; r = s - omega t; p = r + beta (p - omega v); |r|^2
+            const Cd al = ld2(J.alpha, r), om = ld2(J.omega, r), be = ld2(J.beta, r);
+            load_half_spinor<P, R>(J.x, Vh, r, cb, h, a);
+            load_half_spinor<P, R>(J.p, Vh, r, cb, h, b);
+            load_half_spinor<P, R>(J.s, Vh, r, cb, h, c);
+            load_half_spinor<P, R>(J.t, Vh, r, cb, h, d);
+            load_half_spinor<P, R>(J.v, Vh, r, cb, h, f);
+#pragma unroll
+            for (int i = 0; i < 12; i += 2) {
+                const double pr = b[i], pi = b[i + 1], sr = c[i], si = c[i + 1], tr = d[i], ti = d[i + 1], vr = f[i], vi = f[i + 1];
+                a[i] = (R)((double)a[i] + al.r * pr - al.i * pi + om.r * sr - om.i * si);
+                a[i + 1] = (R)((double)a[i + 1] + al.r * pi + al.i * pr + om.r * si + om.i * sr);
+                c[i] = (R)(sr - (om.r * tr - om.i * ti));
+                c[i + 1] = (R)(si - (om.r * ti + om.i * tr));
+                const double rr = c[i], ri = c[i + 1], gr = pr - (om.r * vr - om.i * vi), gi = pi - (om.r * vi + om.i * vr);
+                b[i] = (R)(rr + be.r * gr - be.i * gi);
+                b[i + 1] = (R)(ri + be.r * gi + be.i * gr);
+                q0 += rr * rr + ri * ri;
+            }
+            store_half_spinor<P, R>(J.x, Vh, r, cb, h, a);
+            store_half_spinor<P, R>(J.r, Vh, r, cb, h, c);
+            store_half_spinor<P, R>(J.p, Vh, r, cb, h, b);
+        }
     }
 }
 
 template <int P, int MODE> __global__ void __launch_bounds__(VEC_BS) k_bivec(const BiVecJob<P>* jobs, int njob) {
-    using R = typename PT<P>::R;
     const int bid = blockIdx.x;
     int jb = 0;
     while (jb + 1 < njob && bid >= jobs[jb + 1].blk0) ++jb;
@@ -208,113 +187,42 @@ template <int P, int MODE> __global__ void __launch_bounds__(VEC_BS) k_bivec(con
     const int sb = lb - r * J.nsb;
     const int cb = sb * VEC_BS + (int)threadIdx.x;
     const bool act = rhs_active(J, r);  // uniform over the block
-    constexpr int NQ = (MODE == BV_RR || MODE == BV_RV || MODE == BV_SH) ? 2
-                       : ((MODE == BV_TS || MODE == BV_XR) ? 3 : (MODE == BV_XRP ? 1 : 0));
+    constexpr int NQ = MODE == BV_XRP ? 1 : 2;
     double* part = MODE == BV_SH ? J.part_s : J.part;
     if (!act) {  // the whole block: zero partials, no block sums
         if ((int)threadIdx.x < NQ) part[((long)r * NQ + (int)threadIdx.x) * J.pstride + sb] = 0.0;
         return;
     }
-    double q0 = 0, q1 = 0, q2 = 0;
-    if constexpr (P == P16 && (MODE == BV_S || MODE == BV_XR || MODE == BV_P || MODE == BV_SH || MODE == BV_XRP)) {
+    double q0 = 0, q1 = 0;
+    if constexpr (P == P16 && MODE != BV_RR) {
         // first pass: beyond the reach of the outputs everything is zero and stays so
         constexpr int reach = MODE == BV_SH ? 3 : 5;
-        const bool near = (MODE != BV_SH && MODE != BV_XRP) || cb >= J.Vh ||
-                          in_reach(J.tdist, J.titer, J.T, r, J.tdist ? cb / J.vt : 0, reach);
-        if (act && near && cb < J.Vh) bivec16<MODE>(J, r, (uint32_t)cb, q0, q1, q2);
-    } else if constexpr (MODE == BV_SH || MODE == BV_XRP) {
-        // the merged iteration exists for FP16 fields only (launch_bivec refuses the others)
-    } else if (act && cb < J.Vh) {
-        R a[24], b[24], c[24];
-        if (MODE == BV_RR || MODE == BV_RV) {
-            load_spinor<P, R>(J.rh, J.Vh, r, cb, a);
-            load_spinor<P, R>(MODE == BV_RR ? J.r : J.v, J.Vh, r, cb, b);
+        const bool near = cb < J.Vh && in_reach(J.tdist, J.titer, J.T, r, J.tdist ? cb / J.vt : 0, reach);
+        if (near) bivec16<MODE>(J, r, (uint32_t)cb, q0, q1);
+    } else if constexpr (P == P16) {
+        if (cb < J.Vh) {
+            float a[24], b[24];
+            load_spinor<P, float>(J.rh, J.Vh, r, cb, a);
+            load_spinor<P, float>(J.r, J.Vh, r, cb, b);
             for (int i = 0; i < 12; ++i) {
                 const double ar = a[2 * i], ai = a[2 * i + 1], br = b[2 * i], bi = b[2 * i + 1];
                 q0 += ar * br + ai * bi;
                 q1 += ar * bi - ai * br;
             }
-        } else if (MODE == BV_S) {
-            const Cd al = ld2(J.alpha, r);
-            load_spinor<P, R>(J.r, J.Vh, r, cb, a);
-            load_spinor<P, R>(J.v, J.Vh, r, cb, b);
-            for (int i = 0; i < 12; ++i) {
-                const double br = b[2 * i], bi = b[2 * i + 1];
-                c[2 * i] = (R)((double)a[2 * i] - (al.r * br - al.i * bi));
-                c[2 * i + 1] = (R)((double)a[2 * i + 1] - (al.r * bi + al.i * br));
-            }
-            store_spinor<P, R>(J.s, J.Vh, r, cb, c);
-        } else if (MODE == BV_TS) {
-            load_spinor<P, R>(J.t, J.Vh, r, cb, a);
-            load_spinor<P, R>(J.s, J.Vh, r, cb, b);
-            for (int i = 0; i < 12; ++i) {
-                const double ar = a[2 * i], ai = a[2 * i + 1], br = b[2 * i], bi = b[2 * i + 1];
-                q0 += ar * br + ai * bi;
-                q1 += ar * bi - ai * br;
-                q2 += ar * ar + ai * ai;
-            }
-        } else if (MODE == BV_XR) {
-            const Cd al = ld2(J.alpha, r), om = ld2(J.omega, r);
-            load_spinor<P, R>(J.x, J.Vh, r, cb, a);
-            load_spinor<P, R>(J.p, J.Vh, r, cb, b);
-            load_spinor<P, R>(J.s, J.Vh, r, cb, c);
-            for (int i = 0; i < 12; ++i) {
-                const double pr = b[2 * i], pi = b[2 * i + 1], sr = c[2 * i], si = c[2 * i + 1];
-                a[2 * i] = (R)((double)a[2 * i] + al.r * pr - al.i * pi + om.r * sr - om.i * si);
-                a[2 * i + 1] = (R)((double)a[2 * i + 1] + al.r * pi + al.i * pr + om.r * si + om.i * sr);
-            }
-            store_spinor<P, R>(J.x, J.Vh, r, cb, a);
-            load_spinor<P, R>(J.t, J.Vh, r, cb, b);
-            for (int i = 0; i < 12; ++i) {
-                const double tr = b[2 * i], ti = b[2 * i + 1];
-                c[2 * i] = (R)((double)c[2 * i] - (om.r * tr - om.i * ti));
-                c[2 * i + 1] = (R)((double)c[2 * i + 1] - (om.r * ti + om.i * tr));
-            }
-            store_spinor<P, R>(J.r, J.Vh, r, cb, c);
-            // |r|^2 and (rh, r) of the new residual before its storage rounding
-            load_spinor<P, R>(J.rh, J.Vh, r, cb, a);
-            for (int i = 0; i < 12; ++i) {
-                const double hr = a[2 * i], hi = a[2 * i + 1], rr = c[2 * i], ri = c[2 * i + 1];
-                q0 += rr * rr + ri * ri;
-                q1 += hr * rr + hi * ri;
-                q2 += hr * ri - hi * rr;
-            }
-        } else {  // BV_P
-            const Cd be = ld2(J.beta, r), om = ld2(J.omega, r);
-            load_spinor<P, R>(J.r, J.Vh, r, cb, a);
-            load_spinor<P, R>(J.p, J.Vh, r, cb, b);
-            load_spinor<P, R>(J.v, J.Vh, r, cb, c);
-            for (int i = 0; i < 12; ++i) {
-                const double dr = (double)b[2 * i] - (om.r * c[2 * i] - om.i * c[2 * i + 1]);
-                const double di = (double)b[2 * i + 1] - (om.r * c[2 * i + 1] + om.i * c[2 * i]);
-                b[2 * i] = (R)((double)a[2 * i] + be.r * dr - be.i * di);
-                b[2 * i + 1] = (R)((double)a[2 * i + 1] + be.r * di + be.i * dr);
-            }
-            store_spinor<P, R>(J.p, J.Vh, r, cb, b);
         }
+    } else {
+        if (cb < J.Vh) bivec_planes<P, MODE>(J, r, cb, q0, q1);
     }
-    if (NQ > 0) bi_partial(q0, part, ((long)r * NQ + 0) * J.pstride + sb);
+    bi_partial(q0, part, ((long)r * NQ + 0) * J.pstride + sb);
     if (NQ > 1) bi_partial(q1, part, ((long)r * NQ + 1) * J.pstride + sb);
-    if (NQ > 2) bi_partial(q2, part, ((long)r * NQ + 2) * J.pstride + sb);
 }
 
 template <int P> hipError_t launch_bivec(const BiVecJob<P>* j, int njob, int nblocks, int mode, hipStream_t s) {
     if (nblocks <= 0) return hipSuccess;
     switch (mode) {
     case BV_RR: hipLaunchKernelGGL((k_bivec<P, BV_RR>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
-    case BV_RV: hipLaunchKernelGGL((k_bivec<P, BV_RV>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
-    case BV_S: hipLaunchKernelGGL((k_bivec<P, BV_S>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
-    case BV_TS: hipLaunchKernelGGL((k_bivec<P, BV_TS>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
-    case BV_XR: hipLaunchKernelGGL((k_bivec<P, BV_XR>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
-    case BV_P: hipLaunchKernelGGL((k_bivec<P, BV_P>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
-    case BV_SH:
-        if (P != P16) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_bivec<P, BV_SH>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob);
-        break;
-    case BV_XRP:
-        if (P != P16) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_bivec<P, BV_XRP>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob);
-        break;
+    case BV_SH: hipLaunchKernelGGL((k_bivec<P, BV_SH>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
+    case BV_XRP: hipLaunchKernelGGL((k_bivec<P, BV_XRP>), dim3(nblocks), dim3(VEC_BS), 0, s, j, njob); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -340,9 +248,9 @@ template <int mode> __global__ void __launch_bounds__(256) k_bifinish(const BiFi
     const BiFinJob& J = jobs[jb];
     const int r = bid - J.rhs0;
     if (r >= J.nrhs) return;  // uniform over the block
-    constexpr int NQ = (mode == BF_ALPHA || mode == BF_INIT) ? 2 : (mode == BF_OMBETA ? 5 : (mode == BF_CONV ? 1 : 3));
+    constexpr int NQ = (mode == BF_ALPHA || mode == BF_INIT) ? 2 : (mode == BF_OMBETA ? 5 : 1);
     constexpr int NS = mode == BF_OMBETA ? 2 : 0;  // (rh, s) from the s step's own partials
-    const int np = (mode == BF_ALPHA || mode == BF_OMEGA || mode == BF_OMBETA) ? J.nparth : J.npart;
+    const int np = (mode == BF_ALPHA || mode == BF_OMBETA) ? J.nparth : J.npart;
     double q[7] = {0, 0, 0, 0, 0, 0, 0};
     const double* pp = J.part + (size_t)r * NQ * np;
 #pragma unroll 4
@@ -392,9 +300,6 @@ template <int mode> __global__ void __launch_bounds__(256) k_bifinish(const BiFi
         } else {
             st(J.alpha, r, cdivc(ld2(J.rho, r), d));
         }
-    } else if (mode == BF_OMEGA) {
-        const Cd ts = {q[0], q[1]};
-        st(J.omega, r, (finite2(ts) && q[2] > 0.0 && isfinite(q[2])) ? Cd{ts.r / q[2], ts.i / q[2]} : zero);
     } else if (mode == BF_OMBETA) {
         // omega = (t, s) / |t|^2; rho' = (rh, s) - omega (rh, t), both on the stored s and t, is
         // (rh, s - omega t) for the r = s - omega t that the merged update forms from them
@@ -409,27 +314,13 @@ template <int mode> __global__ void __launch_bounds__(256) k_bifinish(const BiFi
         // on a breakdown the update still runs (with beta = 0) and BF_CONV stops the right-hand side
         st(J.beta, r, brk ? zero : cmulc(cdivc(rho1, rho), cdivc(al, om)));
         st(J.rho, r, brk ? zero : rho1);
-    } else if (mode == BF_CONV) {
+    } else {  // BF_CONV
         const double rr = q[0];
         J.rr[r] = rr;
         const int it = J.iters[r] + 1;
         J.iters[r] = it;
         const Cd rho = ld2(J.rho, r);  // zero after a breakdown
         if (!isfinite(rr) || rr <= J.tol2[r] || it >= J.maxit || (rho.r == 0.0 && rho.i == 0.0)) J.active[r] = 0;
-    } else {  // BF_BETA
-        const double rr = q[0];
-        const Cd rho1 = {q[1], q[2]};
-        J.rr[r] = rr;
-        const int it = J.iters[r] + 1;
-        J.iters[r] = it;
-        const Cd rho = ld2(J.rho, r), om = ld2(J.omega, r), al = ld2(J.alpha, r);
-        const bool brk = (om.r == 0.0 && om.i == 0.0) || (rho.r == 0.0 && rho.i == 0.0) || !finite2(rho1);
-        if (!isfinite(rr) || rr <= J.tol2[r] || it >= J.maxit || brk) {
-            J.active[r] = 0;
-            return;
-        }
-        st(J.beta, r, cmulc(cdivc(rho1, rho), cdivc(al, om)));
-        st(J.rho, r, rho1);
     }
 }
 
@@ -439,8 +330,6 @@ hipError_t launch_bifinish(const BiFinJob* j, int njob, int nblocks, int mode, h
     switch (mode) {
     case BF_INIT: hipLaunchKernelGGL(k_bifinish<BF_INIT>, g, b, 0, s, j, njob); break;
     case BF_ALPHA: hipLaunchKernelGGL(k_bifinish<BF_ALPHA>, g, b, 0, s, j, njob); break;
-    case BF_OMEGA: hipLaunchKernelGGL(k_bifinish<BF_OMEGA>, g, b, 0, s, j, njob); break;
-    case BF_BETA: hipLaunchKernelGGL(k_bifinish<BF_BETA>, g, b, 0, s, j, njob); break;
     case BF_OMBETA: hipLaunchKernelGGL(k_bifinish<BF_OMBETA>, g, b, 0, s, j, njob); break;
     case BF_CONV: hipLaunchKernelGGL(k_bifinish<BF_CONV>, g, b, 0, s, j, njob); break;
     default: return hipErrorInvalidValue;

@@ -34,7 +34,7 @@ enum HopFlags {
     F_ACCUM = 128,  // K1: out += result
     F_DOTX = 256,   // K2: partials of sum conj(out) x (re, im) and |out|^2
     F_DOTR = 512,   // K2: partials of sum conj(r) out (re, im), r the job's r field
-    F_DOTXH = 1024, // K2, FP16, with F_DOTX: also sum conj(r) out of the stored (rounded) out (re, im)
+    F_DOTXH = 1024, // K2, with F_DOTX: also sum conj(r) out of the stored (rounded) out (re, im)
     F_IN16 = 2048,  // FP64 kernels: the hopping input is the FP16 field in16 times sqrt(in16s[r])
     F_ACCX = 4096,  // K2, FP64: first x += in16 * sqrt(in16s[r]) (stored), then the operator on it
 };
@@ -112,6 +112,12 @@ template <int P, class R> HD void store_half_spinor(const SF<P>& f, int Vh, int 
     typename PT<P>::S* b = f.v + (size_t)r * f.rs + (size_t)blk * 6 * Vh + cb;
 #pragma unroll
     for (int c = 0; c < 6; ++c) stp<P>(b, (size_t)c * Vh, (typename PT<P>::R)s[2 * c], (typename PT<P>::R)s[2 * c + 1]);
+}
+
+// a number as the storage precision holds it
+template <int P, class R> HD R stored(R v) {
+    if constexpr (P == PB16) return (R)bf16_to_f(f_to_bf16((float)v));
+    else return v;
 }
 
 // The hopping input of right-hand side r at site cb: the job's field, or with IN16
@@ -331,6 +337,19 @@ HD void hop_site(const HopJob<P>& J, int cb, int g0, double (&qs)[NB][HOP_NQ_MAX
                         }
                         qs[j][0] = re;
                         qs[j][1] = im;
+                        if (FL & F_DOTXH) {  // conj(r) out of the stored out
+                            load_spinor<P, R>(J.r, Vh, g0 + j, cb, v);
+                            re = im = 0;
+#pragma unroll
+                            for (int c = 0; c < 12; ++c) {
+                                const double ar = v[2 * c], ai = v[2 * c + 1];
+                                const double br = stored<P, R>(acc[j][2 * c]), bi = stored<P, R>(acc[j][2 * c + 1]);
+                                re += ar * br + ai * bi;
+                                im += ar * bi - ai * br;
+                            }
+                            qs[j][3] = re;
+                            qs[j][4] = im;
+                        }
                     }
                 }
             }
