@@ -49,24 +49,32 @@ class Pool {
 struct Buf {
     void* p = nullptr;
     size_t n = 0;
+    bool part = false;  // a range of another buffer, which outlives this one
     Buf() = default;
     Buf(const Buf&) = delete;
     Buf& operator=(const Buf&) = delete;
-    Buf(Buf&& o) noexcept : p(o.p), n(o.n) { o.p = nullptr; o.n = 0; }
+    Buf(Buf&& o) noexcept : p(o.p), n(o.n), part(o.part) { o.p = nullptr; o.n = 0; o.part = false; }
     Buf& operator=(Buf&& o) noexcept {
         if (this != &o) {
             reset();
-            p = o.p; n = o.n;
-            o.p = nullptr; o.n = 0;
+            p = o.p; n = o.n; part = o.part;
+            o.p = nullptr; o.n = 0; o.part = false;
         }
         return *this;
     }
     ~Buf() { reset(); }
     int allocate(size_t bytes);  // DLMA_OK or DLMA_ENOMEM
     void reset() {
-        if (p) Pool::get().release(p, n);
+        if (p && !part) Pool::get().release(p, n);
         p = nullptr;
         n = 0;
+        part = false;
+    }
+    void range(const Buf& whole, size_t offset, size_t bytes) {
+        reset();
+        p = (char*)whole.p + offset;
+        n = bytes;
+        part = true;
     }
     template <class T> T* as() const { return (T*)p; }
 };
