@@ -839,7 +839,7 @@ extern "C" int dlma_project(dlma_gauge_t h, int t, int nev, const void* V_t, con
     if (!in || !out || (nev > 0 && !V_t)) return fail(DLMA_EINVAL, "NULL pointer");
     hipStream_t s = S(stream);
     Buf coef, part;
-    const long per = 16L * std::max(1, nev), sets = std::min<long>((nrhs + 3) / 4, std::max(2L, (1L << 22) / per));
+    const long per = 16L * std::max(1, nev), sets = std::min<long>((nrhs + 3L) / 4, 16384);
     const long nc = per * sets, np = per * sets * project_ks(g->geo, nev);
     const long cap = std::max(std::min(np, 4 * PROJ_PART_CAP), per * project_ks(g->geo, nev));
     DLMA_TRY(coef.allocate(sizeof(double2) * nc));

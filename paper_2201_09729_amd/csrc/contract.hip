@@ -460,15 +460,14 @@ hipError_t launch_project(const double2* Vt, const double2* in, double2* out, co
                           double2* coef, long coef_cap, double2* part, long part_cap, hipStream_t s) {
     const long L3 = (long)g.Z * g.Y * g.X, fs = 24L * g.Vh;
     const int ks = project_ks(g, nev);
-    // column sets (of four right-hand sides) per pass
-    const long per = 16L * std::max(1, nev);
-    long sets = std::min(coef_cap / per, ks > 1 ? part_cap / (per * ks) : coef_cap / per);
+    // column sets (of four right-hand sides): those whose c fit coef, and of them those per
+    // contraction, whose partials fit part (pairs of sets share a wave)
+    const long per = 16L * std::max(1, nev), sets = coef_cap / per;
+    long psets = ks > 1 ? part_cap / (per * ks) : sets;
+    if (psets > 2) psets -= psets & 1;
+    if (sets < 1 || psets < 1) return hipErrorInvalidValue;
     const unsigned nrb = (unsigned)((L3 * 3 + 127) / 128);
     const unsigned nfb = (unsigned)((fs + FILL_PER_BLOCK - 1) / FILL_PER_BLOCK);
-    // pairs of sets share a wave, and the grid stays below 2^31 blocks
-    sets = std::min(sets, std::max(2L, (1L << 30) / (4L * nfb)));
-    if (sets > 2 && 4 * sets < nrhs) sets -= sets & 1;
-    if (sets < 1) return hipErrorInvalidValue;
     // Few modes and right-hand sides on a small timeslice: one launch for c instead of the
     // contraction's two, while a block's passes over its L3 sites stay short.  8 modes, one
     // right-hand side (us per call): 4^3 27 against 32, 600 sites 28 against 33, 12^3 31
@@ -477,23 +476,32 @@ hipError_t launch_project(const double2* Vt, const double2* in, double2* out, co
     const bool direct = L3 <= 2048 && (double)nev * nrhs * L3 * L3 <= (double)(1L << 28);
     // one column set per wave until the waves of 32 rows fill the chip
     const int H = nrhs > 4 && (L3 * 3 + 31) / 32 * ((nrhs + 7) / 8) >= 1024 ? 2 : 1;
+    // right-hand sides per apply: fewer than 2^32 threads, pairs of sets together
+    const long arhs = ((1L << 24) - 1 - nrb) / (nfb + (nrb + 3) / 4) / 8 * 8;
     for (long r0 = 0; r0 < nrhs; r0 += 4 * sets) {
-        const int nr = (int)std::min<long>(4 * sets, nrhs - r0);
+        const long nr = std::min<long>(4 * sets, nrhs - r0);
         const double2* inr = in + r0 * fs;
+        // every c before any output, which may overlap the inputs of other right-hand sides
         if (nev > 0 && direct) {
-            hipLaunchKernelGGL(k_proj_coef, dim3(nev, nr), dim3(256), 0, s, Vt, inr, L3, (long)t * L3 * 12, fs, nev, coef);
+            hipLaunchKernelGGL(k_proj_coef, dim3(nev, (unsigned)nr), dim3(256), 0, s, Vt, inr, L3, (long)t * L3 * 12, fs, nev, coef);
         } else if (nev > 0) {  // no modes: box(t) = 0 and the apply kernel reads no coefficient
-            ContractArgs a = {};
-            a.Vall = Vt; a.f0 = inr; a.L3 = L3; a.fs = fs;
-            a.t0 = a.tv0 = t;
-            a.nt = 1; a.nev = nev; a.ng = (nr + 3) / 4; a.nf = nr; a.ks = ks;
-            a.taup = part;
-            const hipError_t e = launch_contract(a, false, false, coef, s);
-            if (e != hipSuccess) return e;
+            for (long p0 = 0; p0 < nr; p0 += 4 * psets) {
+                ContractArgs a = {};
+                a.Vall = Vt; a.f0 = inr + p0 * fs; a.L3 = L3; a.fs = fs;
+                a.t0 = a.tv0 = t;
+                a.nf = (int)std::min(4 * psets, nr - p0);
+                a.nt = 1; a.nev = nev; a.ng = (a.nf + 3) / 4; a.ks = ks;
+                a.taup = part;
+                const hipError_t e = launch_contract(a, false, false, coef + p0 / 4 * per, s);
+                if (e != hipSuccess) return e;
+            }
         }
-        const unsigned nab = nrb * (unsigned)((nr + 4 * H - 1) / (4 * H));
-        hipLaunchKernelGGL(H == 2 ? k_proj_apply<2> : k_proj_apply<1>, dim3(nab + nfb * (unsigned)nr), dim3(256), 0, s, Vt, inr, out + r0 * fs, L3, fs, t, nev,
-                           coef, nr, mode, nab, nrb);
+        for (long a0 = 0; a0 < nr; a0 += arhs) {
+            const int na = (int)std::min(arhs, nr - a0);
+            const unsigned nab = nrb * (unsigned)((na + 4 * H - 1) / (4 * H));
+            hipLaunchKernelGGL(H == 2 ? k_proj_apply<2> : k_proj_apply<1>, dim3(nab + nfb * (unsigned)na), dim3(256), 0, s, Vt,
+                               inr + a0 * fs, out + (r0 + a0) * fs, L3, fs, t, nev, coef + a0 / 4 * per, na, mode, nab, nrb);
+        }
     }
     return hipGetLastError();
 }

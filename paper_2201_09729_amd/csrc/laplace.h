@@ -69,9 +69,10 @@ hipError_t launch_contract(const ContractArgs& a, bool noise, bool gram, double2
 // part[nt][proj_gram_parts()][16][16] of sum_g sum_k conj(tau[oa + st g]) tau[ob + st g]
 int proj_gram_parts();
 hipError_t launch_proj_gram(const double2* tau, int nt, int nev, int ng, int oa, int ob, int st, double2* part, hipStream_t s);
-// box(t) of launch_project: coef and part hold coef_cap and part_cap complex numbers;
-// right-hand sides go through them in chunks.  The site chunks depend on the lattice and
-// nev alone, so the result does not depend on the capacities.
+// box(t) of launch_project: coef and part hold coef_cap and part_cap complex numbers.  The
+// coefficients of as many right-hand sides as coef holds are formed before the first of
+// their outputs is written, in chunks that fit part.  The site chunks depend on the lattice
+// and nev alone, so the result does not depend on the capacities.
 constexpr long PROJ_PART_CAP = 524288;
 int project_ks(const Geo& g, int nev);
 hipError_t launch_project(const double2* Vt, const double2* in, double2* out, const Geo& g, int t, int nev, int nrhs, int mode,

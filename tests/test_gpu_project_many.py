@@ -1,0 +1,43 @@
+"""The projector's passes through its scratch: with more right-hand sides than one contraction
+takes, every coefficient is formed before the first output is written, so mode 0 (which reads
+its inputs for the coefficients alone) may write over the inputs of later right-hand sides."""
+import numpy as np
+import pytest
+
+from paper_2201_09729_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def D():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2201_09729_amd import dlma
+    return dlma
+
+
+# 32 modes on 16^3: 64 right-hand sides per contraction (allocation-free: 16); on 4^2 x 8 the
+# one-launch coefficients
+@pytest.mark.parametrize("dims,nev,n", [((2, 16, 16, 16), 32, 70), ((2, 4, 4, 8), 5, 21)])
+@pytest.mark.parametrize("alloc", [True, False])
+def test_outputs_over_later_inputs(D, dims, nev, n, alloc):
+    print("project over inputs", dims, nev, n, alloc, flush=True)
+    g = D.dlma_load_gauge(torch.from_numpy(synth.gauge_field(dims, 0.2, 3)).cuda(), 0.121, 1.0)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    V = torch.randn((nev,) + dims[1:] + (3,), dtype=torch.complex128, device="cuda", generator=gen)
+    x = torch.randn((n,) + dims + (4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    ref = D.dlma_project(g, 1, V, x, 0)  # separate fields: the same kernels, the same numbers
+    buf = torch.empty((n + 1,) + dims + (4, 3), dtype=torch.complex128, device="cuda")
+    buf[:n] = x
+    (D.dlma_project if alloc else D.dlma_project_noalloc)(g, 1, V, buf[:n], 0, buf[1:])  # one field further
+    torch.cuda.synchronize()
+    assert torch.equal(buf[1:], ref)
+    f, v = x[:, 1].reshape(n, -1, 4, 3).cpu().numpy(), V.reshape(nev, -1, 3).cpu().numpy()
+    f = f.transpose(0, 2, 1, 3).reshape(n * 4, -1)
+    v = v.reshape(nev, -1)
+    tol = (v.shape[1] + nev + 8) * 2.0**-52 * ((np.abs(f) @ np.abs(v).T) @ np.abs(v))
+    out = ref[:, 1].reshape(n, -1, 4, 3).cpu().numpy().transpose(0, 2, 1, 3).reshape(n * 4, -1)
+    assert np.all(np.abs(out - (f @ v.conj().T) @ v) <= tol)
