@@ -170,26 +170,29 @@ template <bool NOISE> static hipError_t launch_contract_t(ContractArgs a, bool g
     return hipGetLastError();
 }
 
-// tau[i] = sum of its ks partials: 16 values per block, sixteen slices of the partials each
+// tau[i] = sum of its ks partials: 16 values per block at a time, sixteen slices of the partials each
 __global__ void __launch_bounds__(256) k_sum_parts(const double2* __restrict__ p, long n, int ks, double2* __restrict__ o) {
     __shared__ double2 sm[16][16];
     const int e = (int)threadIdx.x & 15, sl = (int)threadIdx.x >> 4;
-    const long i = (long)blockIdx.x * 16 + e;  // n is a multiple of 16
-    double2 v = make_double2(0.0, 0.0);
+    for (long i = (long)blockIdx.x * 16 + e; i < n; i += (long)gridDim.x * 16) {  // n is a multiple of 16
+        double2 v = make_double2(0.0, 0.0);
 #pragma unroll 4
-    for (int k = sl; k < ks; k += 16) {
-        const double2 w = p[i + k * n];
-        v.x += w.x;
-        v.y += w.y;
+        for (int k = sl; k < ks; k += 16) {
+            const double2 w = p[i + k * n];
+            v.x += w.x;
+            v.y += w.y;
+        }
+        sm[sl][e] = v;
+        __syncthreads();
+        if (sl == 0) {
+            for (int k = 1; k < 16; ++k) {
+                v.x += sm[k][e].x;
+                v.y += sm[k][e].y;
+            }
+            o[i] = v;
+        }
+        __syncthreads();
     }
-    sm[sl][e] = v;
-    __syncthreads();
-    if (sl > 0) return;
-    for (int k = 1; k < 16; ++k) {
-        v.x += sm[k][e].x;
-        v.y += sm[k][e].y;
-    }
-    o[i] = v;
 }
 
 hipError_t launch_contract(const ContractArgs& a0, bool noise, bool gram, double2* tau, hipStream_t s) {
@@ -201,7 +204,8 @@ hipError_t launch_contract(const ContractArgs& a0, bool noise, bool gram, double
     const hipError_t e = noise ? launch_contract_t<true>(a, gram, s) : launch_contract_t<false>(a, gram, s);
     if (e != hipSuccess || a.ks == 1) return e;
     const long n = (long)(noise ? 2 : 1) * a.ng * a.nt * a.nev * 16;
-    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)(n / 16)), dim3(256), 0, s, a.taup, n, a.ks, tau);
+    // (a launch ends at 2^32 threads)
+    hipLaunchKernelGGL(k_sum_parts, dim3((unsigned)std::min(n / 16, 1L << 20)), dim3(256), 0, s, a.taup, n, a.ks, tau);
     return hipGetLastError();
 }
 

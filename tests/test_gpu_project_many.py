@@ -41,3 +41,21 @@ def test_outputs_over_later_inputs(D, dims, nev, n, alloc):
     tol = (v.shape[1] + nev + 8) * 2.0**-52 * ((np.abs(f) @ np.abs(v).T) @ np.abs(v))
     out = ref[:, 1].reshape(n, -1, 4, 3).cpu().numpy().transpose(0, 2, 1, 3).reshape(n * 4, -1)
     assert np.all(np.abs(out - (f @ v.conj().T) @ v) <= tol)
+
+
+def test_correlators_of_many_modes_and_sources(D):
+    """2065 modes and 254 source groups on 32 timeslices: 2^28 projections and more, in two site
+    chunks.  PP_exact of the pseudoscalar is the sum of |tau|^2, all terms positive: relative
+    tolerance 2^-52 times the 96 terms of a projection (twice) and the 16 nev ndist of the sum."""
+    dims, nev, nd = (32, 2, 4, 4), 2065, 254
+    print("many modes", dims, nev, nd, flush=True)
+    g = D.dlma_load_gauge(torch.from_numpy(synth.gauge_field(dims, 0.2, 3)).cuda(), 0.121, 1.0)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    V = torch.randn((32, nev, 2, 4, 4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    x = torch.randn((4 * nd,) + dims + (4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    got = D.dlma_correlators_array(g, 5, V, x)[0, 5]
+    for t in range(32):
+        f = x[:, t].reshape(4 * nd, 32, 4, 3).transpose(1, 2).reshape(16 * nd, 96)
+        ref = (f @ V[t].reshape(nev, 96).conj().T.contiguous()).abs().square().sum().item()
+        d = (t - 5) % 32
+        assert abs(got[d, 0] - ref) <= (192 + 16 * nev * nd) * 2.0**-52 * ref and abs(got[d, 1]) <= 1e-9 * ref, t
