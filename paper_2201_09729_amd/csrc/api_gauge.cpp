@@ -32,6 +32,9 @@ static int check_dims(const int* dims) {
 // A_oo^-1 from A_oo; *bits (host, may be NULL) also receives the 8 bytes at `worst` (device),
 // read with the inversion's error flag after one synchronisation
 static int invert_clover(Gauge* g, hipStream_t s, const void* worst = nullptr, unsigned long long* bits = nullptr) {
+    // the storage-precision copies are of the former A, whatever becomes of the inversion
+    for (int p = 1; p < 4; ++p) g->lo_ready[p] = false;
+    g->tclover_ready = false;
     Buf err;
     DLMA_TRY(err.allocate(sizeof(int)));
     DLMA_HIP(hipMemsetAsync(err.p, 0, sizeof(int), s));
@@ -47,8 +50,6 @@ static int invert_clover(Gauge* g, hipStream_t s, const void* worst = nullptr, u
             return fail(DLMA_EINVAL, "links are not unitary to 1e-10 (max |U U^dag - 1| = " + std::to_string(m) + ")");
     }
     if (h) return fail(DLMA_EINVAL, "clover block not positive definite (kappa/csw out of range for this field)");
-    for (int p = 1; p < 4; ++p) g->lo_ready[p] = false;
-    g->tclover_ready = false;
     return DLMA_OK;
 }
 
