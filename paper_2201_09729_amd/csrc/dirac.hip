@@ -416,7 +416,6 @@ hipError_t launch_dirac(DiracArgs a, hipStream_t s) {
     a.ng = per;
     a.nT = g.T % 8 == 0 ? 8 : (g.T % 4 == 0 ? 4 : 2);
     const int ntm = g.T / a.nT, nZ = 8 / a.nT, nzm = (g.Z + nZ - 1) / nZ;
-    const long nsg = (a.nrhs + per - 1) / per;
     // sites of a strip: an XCD's timeslices of three z planes for up to 12 right-hand sides in
     // 8 MB (of 2, 4, 8, 16 MB at 24^3 x 48 the best by 4%; 12 right-hand sides together 1.7 ms,
     // two 2.0, one 2.6: they share the links)
@@ -424,15 +423,23 @@ hipError_t launch_dirac(DiracArgs a, hipStream_t s) {
     if (sites) {
         a.nstrip = (int)((pw + std::max(1L, l2 / 64) - 1) / std::max(1L, l2 / 64));
         a.nch = (int)((pw + a.nstrip - 1) / a.nstrip);
-        const long waves = nsg * a.nstrip * nzm * ntm * a.nch * a.ng;
-        hipLaunchKernelGGL(k_dirac_sites, dim3((unsigned)((waves + 3) / 4 * 8)), dim3(256), 0, s, a);
     } else {
         const int step = 16 / std::gcd(g.X, 16);  // rows that fill whole waves
         a.R = (int)std::min<long>(std::max<long>(step, l2 / g.X / step * step), g.Y);
         a.nstrip = (g.Y + a.R - 1) / a.R;
         a.nch = (a.R * g.X + 15) / 16;
-        const long waves = nsg * a.nstrip * nzm * ntm * a.nch * a.ng;
-        hipLaunchKernelGGL(k_dirac, dim3((unsigned)((waves + 3) / 4 * 8)), dim3(256), 0, s, a);
+    }
+    // a launch's 32-bit grid ends at 2^32 threads, 512 per wave of an XCD
+    const long group = (long)a.nstrip * nzm * ntm * a.nch * a.ng, most = std::max(1L, (1L << 23) / group - 1) * per;
+    const int all = a.nrhs;
+    for (long r0 = 0; r0 < all; r0 += most) {
+        a.nrhs = (int)std::min(most, all - r0);
+        const long waves = (a.nrhs + per - 1) / per * group;
+        const dim3 grid((unsigned)((waves + 3) / 4 * 8));
+        if (sites) hipLaunchKernelGGL(k_dirac_sites, grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(k_dirac, grid, dim3(256), 0, s, a);
+        a.in += a.nrhs * 24L * g.Vh;
+        a.out += a.nrhs * 24L * g.Vh;
     }
     return hipGetLastError();
 }
