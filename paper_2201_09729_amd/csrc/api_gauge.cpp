@@ -126,6 +126,15 @@ extern "C" int dlma_apply_dw(dlma_gauge_t h, const void* in, void* out, int nrhs
     if (!in || !out) return fail(DLMA_EINVAL, "NULL field pointer");
     if (in == out) return fail(DLMA_EINVAL, "in and out must not overlap");
     hipStream_t s = S(stream);
+    // fields that overlap in part: D reads neighbours, so it works from a copy of its input
+    const size_t bytes = sizeof(double2) * (size_t)nrhs * 24 * g->Vh;
+    const char *pi = (const char*)in, *po = (const char*)out;
+    Buf copy;
+    if (pi < po + bytes && po < pi + bytes) {
+        DLMA_TRY(copy.allocate(bytes));
+        DLMA_HIP(hipMemcpyAsync(copy.p, in, bytes, hipMemcpyDeviceToDevice, s));
+        in = copy.p;
+    }
     DiracArgs a = {};
     a.U = g->U64.as<double2>();
     a.C0 = g->Cl64[0].as<double2>();
