@@ -24,12 +24,15 @@ constexpr int TCONV_SITES = 32;  // sites per block of the layout conversions
 
 inline int tile_count(int nrhs) { return (nrhs + TILE - 1) / TILE; }
 // Sites per block of the stencil (about) and vector kernels, whose four waves take them in
-// turn: enough to spread a block's start, few while the blocks do not fill the chip.  8x12x10x12 with
-// 16 right-hand sides: the x, r, p update 24 us with 64 sites per block.  48x24^3 with 96: 24 to
-// 100 sites of a stencil block are alike, 256 are 10% slower.
-inline bool tile_short(int Vh, int nrhs) { return (long)Vh * tile_count(nrhs) < 65536; }
-inline int tile_hop_sites(int Vh, int nrhs) { return tile_short(Vh, nrhs) ? 8 : 48; }
-inline int tile_vec_sites(int Vh, int nrhs) { return tile_short(Vh, nrhs) ? 8 : 64; }
+// turn: enough to spread a block's start, few while the blocks do not fill the chip.  Vector
+// kernels, 8x12x10x12 with 16 right-hand sides: the x, r, p update 24 us with 64 sites per block.
+// Stencils, whole BF16 solves (ms) with 8 and 48 sites per block: 24x8x12x16 with 16 right-hand
+// sides (18432 tile sites) 8.6, 9.0; 10x12x10x12 with 44 (21600) 9.5, 10.1; 12x8x16x10 with 48
+// (23040) 10.8, 10.2; 16x12^3 with 32 (27648) 11.4, 10.8; 24x12^3 with 48 (62208) 22.6, 20.5.
+// 48x24^3 with 96: 24 to 100 sites of a stencil block are alike, 256 are 10% slower.
+inline long tile_sites(int Vh, int nrhs) { return (long)Vh * tile_count(nrhs); }
+inline int tile_hop_sites(int Vh, int nrhs) { return tile_sites(Vh, nrhs) < 22000 ? 8 : 48; }
+inline int tile_vec_sites(int Vh, int nrhs) { return tile_sites(Vh, nrhs) < 65536 ? 8 : 64; }
 
 // One Schur stencil of one configuration.  A block covers R y rows (the last strip fewer) of
 // one z plane of one timeslice, for one tile.
@@ -45,9 +48,13 @@ struct TileHopJob {
     double* part;          // part[(r * NQ + q) * pstride + site block]
     int pstride;           // T * nbt
 };
+// equal strips: 20x12x10x12 with 32 right-hand sides 11.8 ms per solve with strips of 8 and 2
+// rows, 11.5 with 5 and 5
 inline int tile_hop_rows(const Geo& g, int nrhs) {
     const int r = tile_hop_sites(g.Vh, nrhs) / g.Xh;
-    return r < 1 ? 1 : (r > g.Y ? g.Y : r);
+    if (r < 1) return 1;
+    const int n = (g.Y + r - 1) / r;
+    return (g.Y + n - 1) / n;
 }
 inline int tile_hop_nbt(const Geo& g, int nrhs) { const int r = tile_hop_rows(g, nrhs); return g.Z * ((g.Y + r - 1) / r); }
 // XCDs along the timeslices of a launch (the rest along z): all eight where they divide the
