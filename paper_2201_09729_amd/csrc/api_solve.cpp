@@ -100,22 +100,32 @@ template <int P> struct Tables {
     int bth = 0, btv = 0, btc = 0;
 };
 
-// BF16 BiCGStab solves take right-hand-side tiles when the tiles are filled well enough:
-// a tile's stencil costs the same for 9 right-hand sides as for 16.  Both stencils of
-// Dhat on 24x12^3, tiles against one thread per site: 16 of 16 51 against 59 us, 32 of 32
-// 77 against 99, 72 of 80 150 against 185, 12 of 16 51 against 45; 32x16^3, 24 of 32 192
-// against 198; 48x24^3, 96 of 96 2.73 against 4.0 ms.  So up to a quarter more columns than
-// right-hand sides, where they are at worst equal.  A tile's fields must fit a buffer
-// resource (768 bytes per site, 32-bit offsets).  A caller's own rhs_block asks for the
-// per-thread stencils.
-bool tile_fill(const std::vector<std::pair<int, int>>& vh_nrhs) {
-    double have = 0, need = 0;
-    for (auto& c : vh_nrhs) {
-        if ((size_t)c.first * 768 >= ((size_t)1 << 32)) return false;
-        have += (double)c.first * c.second;
-        need += (double)c.first * tile_count(c.second) * TILE;
+// BF16 BiCGStab solves take right-hand-side tiles when the tiles are filled well enough: a
+// tile costs the same for 9 right-hand sides as for 16 and runs until its last has converged,
+// while the per-thread stencils skip each that has.  Whole solves (ms), per-thread and tiles:
+//   below 32768 tile sites the launches count, of which tiles have shorter ones, and a quarter
+//   more columns than right-hand sides still pays: 8x4^3 with 13 4.2, 3.1; 16x8^3 with 29 5.6,
+//   5.2; 16x12^3 with 24 (a third more, not taken) 9.6, 10.2;
+//   above, up to 8% more columns: 16x12^3 with 48 of 48 15.0, 14.5; 32x16^3 with 64 of 64 82,
+//   76, 31 of 32 41.1, 40.2, 29 of 32 37.5, 39.5; 48x24^3 with 16 of 16 109, 101, 15 of 16 105,
+//   107, 13 of 16 88, 103;
+//   the per-thread blocks leave whole timeslices to an XCD, which wants for work when they do
+//   not divide by 8 (8 ceil(T / 8) / T); about its root is left of that in a solve: 10x18^3 with
+//   52 of 64 41.6, 35.3; 18x14^3 with 80 of 96 (and two small ones) 56.0, 49.3.
+// A tile's fields must fit a buffer resource (768 bytes per site, 32-bit offsets).  A caller's
+// own rhs_block asks for the per-thread stencils.
+bool tile_fill(const std::vector<std::pair<const Geo*, int>>& geo_nrhs) {
+    double have = 0, need = 0, slack = 0, sites = 0;
+    for (auto& c : geo_nrhs) {
+        const Geo& g = *c.first;
+        if ((size_t)g.Vh * 768 >= ((size_t)1 << 32)) return false;
+        const double work = (double)g.Vh * c.second;
+        have += work;
+        slack += work * std::sqrt(8.0 * ceil_div(g.T, 8) / g.T);
+        need += (double)tile_sites(g.Vh, c.second) * TILE;
+        sites += (double)tile_sites(g.Vh, c.second);
     }
-    return need <= 1.25 * have;
+    return need <= 1.25 * have && (sites < 32768 || need <= 1.08 * slack);
 }
 
 TileHopJob tile_hop_job(const Gauge* g, int par, int nrhs) {
@@ -721,8 +731,8 @@ template <int P>
 int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
     bool tiled = false;
     if (P == PB16) {
-        std::vector<std::pair<int, int>> sizes;
-        for (auto& c : cs) sizes.emplace_back(c.g->Vh, c.nrhs);
+        std::vector<std::pair<const Geo*, int>> sizes;
+        for (auto& c : cs) sizes.emplace_back(&c.g->geo, c.nrhs);
         tiled = o.inner_solver == 1 && o.rhs_block == 0 && tile_fill(sizes);
     }
     for (auto& c : cs) {
@@ -1387,7 +1397,7 @@ int schur_tiles(Gauge* g, const void* in, void* out, int nrhs, hipStream_t s) {
 template <int P>
 int schur_impl(Gauge* g, const void* in, void* out, int nrhs, int dagger, int nb, int sg, int win, hipStream_t s) {
     if constexpr (P == PB16)  // the solver's stencils for this many right-hand sides
-        if (nb == 0 && !dagger && tile_fill({{g->Vh, nrhs}})) return schur_tiles(g, in, out, nrhs, s);
+        if (nb == 0 && !dagger && tile_fill({{&g->geo, nrhs}})) return schur_tiles(g, in, out, nrhs, s);
     DLMA_TRY(gauge_prepare(g, P, s));
     const int Vh = g->Vh;
     const size_t full64 = sizeof(double2) * (size_t)nrhs * 24 * Vh;
