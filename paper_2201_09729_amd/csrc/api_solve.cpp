@@ -735,10 +735,24 @@ int solve_impl(std::vector<Cfg>& cs, const dlma_solve_opts& o, hipStream_t s) {
         for (auto& c : cs) sizes.emplace_back(&c.g->geo, c.nrhs);
         tiled = o.inner_solver == 1 && o.rhs_block == 0 && tile_fill(sizes);
     }
-    for (auto& c : cs) {
-        if (tiled) DLMA_TRY(gauge_prepare_tiles(c.g, s));
-        else DLMA_TRY(gauge_prepare(c.g, P, s));
-        DLMA_TRY(alloc_cfg<P>(c, o.inner_solver == 1, tiled, s));
+    if (tiled) {
+        int rc = DLMA_OK;
+        for (size_t i = 0; i < cs.size() && rc == DLMA_OK; ++i) rc = alloc_cfg<P>(cs[i], true, true, s);
+        std::vector<Gauge*> made;
+        for (size_t i = 0; i < cs.size() && rc == DLMA_OK; ++i) {
+            if (!cs[i].g->tlinks_ready) made.push_back(cs[i].g);
+            rc = gauge_prepare_tiles(cs[i].g, s);
+        }
+        if (rc == DLMA_ENOMEM) {  // the per-thread stencils need less: no padding, smaller links
+            for (Gauge* g : made) gauge_drop_tiles(g);
+            tiled = false;
+        } else {
+            DLMA_TRY(rc);
+        }
+    }
+    if (!tiled) {  // (fields first: each replaces the padded one of tiles that did not fit)
+        for (auto& c : cs) DLMA_TRY(alloc_cfg<P>(c, o.inner_solver == 1, false, s));
+        for (auto& c : cs) DLMA_TRY(gauge_prepare(c.g, P, s));
     }
     if (o.rhs_block < 0 || o.rhs_block > 4)
         return fail(DLMA_EINVAL, "rhs_block must be 0 .. 4");
@@ -1397,7 +1411,12 @@ int schur_tiles(Gauge* g, const void* in, void* out, int nrhs, hipStream_t s) {
 template <int P>
 int schur_impl(Gauge* g, const void* in, void* out, int nrhs, int dagger, int nb, int sg, int win, hipStream_t s) {
     if constexpr (P == PB16)  // the solver's stencils for this many right-hand sides
-        if (nb == 0 && !dagger && tile_fill({{&g->geo, nrhs}})) return schur_tiles(g, in, out, nrhs, s);
+        if (nb == 0 && !dagger && tile_fill({{&g->geo, nrhs}})) {
+            const bool had = g->tlinks_ready;
+            const int rc = schur_tiles(g, in, out, nrhs, s);
+            if (rc != DLMA_ENOMEM) return rc;
+            if (!had) gauge_drop_tiles(g);  // the per-thread stencils need less
+        }
     DLMA_TRY(gauge_prepare(g, P, s));
     const int Vh = g->Vh;
     const size_t full64 = sizeof(double2) * (size_t)nrhs * 24 * Vh;

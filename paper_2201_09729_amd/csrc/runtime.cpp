@@ -122,6 +122,11 @@ int gauge_prepare_tiles(Gauge* g, hipStream_t s) {
     return DLMA_OK;
 }
 
+void gauge_drop_tiles(Gauge* g) {
+    g->tlinks_ready = g->tclover_ready = false;
+    for (Buf& b : g->tL) b.reset();
+}
+
 const void* gauge_links(const Gauge* g, int prec) { return prec == P64 ? g->U64.p : g->Ulo[prec].p; }
 const void* gauge_clover_ee(const Gauge* g, int prec) { return prec == P64 ? g->Cl64[0].p : g->Cee[prec].p; }
 const void* gauge_clover_oo_inv(const Gauge* g, int prec) { return prec == P64 ? g->Ci64.p : g->Cio[prec].p; }

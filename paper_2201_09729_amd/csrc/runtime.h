@@ -105,6 +105,7 @@ void tuned_store(const int dims[4], int prec, int nrhs, int nb);
 
 int gauge_prepare(Gauge* g, int prec, hipStream_t s);  // low-precision copies on demand
 int gauge_prepare_tiles(Gauge* g, hipStream_t s);
+void gauge_drop_tiles(Gauge* g);
 const void* gauge_links(const Gauge* g, int prec);
 const void* gauge_clover_ee(const Gauge* g, int prec);
 const void* gauge_clover_oo_inv(const Gauge* g, int prec);
