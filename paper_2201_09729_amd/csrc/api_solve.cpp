@@ -1344,8 +1344,6 @@ int bench_impl(Gauge* g, int nrhs, int nb, int napply, double* ms_out, double* b
     DLMA_HIP(hipEventSynchronize(e1));
     float ms = 0;
     DLMA_HIP(hipEventElapsedTime(&ms, e0, e1));
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     DLMA_HIP(hipStreamSynchronize(s));
     if (Profiler::get().on) Profiler::get().collect();
     if (ms_out) *ms_out = ms / napply;
