@@ -354,7 +354,8 @@ int dlma_profile_read(int kclass, long long* launches, double* total_ms, double*
 /*
  * Apply the Schur operator Dhat (and Dhat^dag alternately) napply times to nrhs
  * internal random vectors in precision prec (DLMA_PREC_*: FP64, FP32, FP16, BF16
- * storage), rhs_block right-hand sides per thread (1 .. 4; 0 = autotuned).
+ * storage), rhs_block right-hand sides per thread (1 .. 4; 0 = the kernels and launch
+ * shape that dlma_solve takes; BF16 on right-hand-side tiles: Dhat alone).
  * Returns milliseconds per application in ms_out (host) and algorithmic bytes per
  * application in bytes_out (host).  For bandwidth measurements.
  */

@@ -647,9 +647,17 @@ int bicg_iteration(std::vector<Cfg>& cs, Tables<P>& t, int nb, const std::vector
     return DLMA_OK;
 }
 
+int tile_launch(int kind, int flags, const Buf& jobs, int njob, int nblk, int tw0, int twn, int kc, double bytes, hipStream_t s) {
+    Profiler& pr = Profiler::get();
+    hipEvent_t a = nullptr;
+    if (pr.on) pr.begin(kc, bytes, s, a);
+    DLMA_HIP(launch_tile_hop(kind, flags, jobs.as<TileHopJob>(), njob, nblk, tw0, twn, s));
+    if (pr.on) pr.end(a, kc, bytes, s);
+    return DLMA_OK;
+}
+
 // The merged iteration on right-hand-side tiles.
 int tile_iteration(std::vector<Cfg>& cs, Tables<PB16>& t, const std::vector<int>& nact, hipStream_t s, const IterWin* w = nullptr) {
-    Profiler& pr = Profiler::get();
     constexpr int FX = F_DOTX | F_DOTXH;
     auto launch = [&](int i, int kind, int flags, const Buf& jobs, int kc) -> int {
         int nblk = t.bth, tw0 = 0, twn = 0;
@@ -663,14 +671,9 @@ int tile_iteration(std::vector<Cfg>& cs, Tables<PB16>& t, const std::vector<int>
             if (hop_nq(flags) > 0)
                 DLMA_HIP(hipMemsetAsync(c.part.p, 0, sizeof(double) * (size_t)c.nrhs * hop_nq(flags) * c.thnsb, s));
         }
-        hipEvent_t a = nullptr;
-        if (pr.on) {
+        if (Profiler::get().on)
             for (size_t k = 0; k < cs.size(); ++k) bytes += frac * hop_bytes(PB16, kind, flags, cs[k].g->Vh, nact[k]);
-            pr.begin(kc, bytes, s, a);
-        }
-        DLMA_HIP(launch_tile_hop(kind, flags, jobs.as<TileHopJob>(), t.nk, nblk, tw0, twn, s));
-        if (pr.on) pr.end(a, kc, bytes, s);
-        return DLMA_OK;
+        return tile_launch(kind, flags, jobs, t.nk, nblk, tw0, twn, kc, bytes, s);
     };
     const TileVecJob* tv = t.dtv.as<TileVecJob>();
     const BiFinJob* bf = t.dbf.as<BiFinJob>();
@@ -1277,8 +1280,57 @@ extern "C" int dlma_solve(const dlma_gauge_t* gs, int ngauge, const dlma_rhs_set
 // ---------------------------------------------------------------- Schur benchmark
 
 namespace {
+// milliseconds per call of run(k), k = 0 .. napply - 1, after one of each parity
+template <class F> int time_applications(F run, int napply, double* ms_out, hipStream_t s) {
+    DLMA_TRY(run(0));
+    DLMA_TRY(run(1));
+    DLMA_HIP(hipStreamSynchronize(s));
+    if (Profiler::get().on) Profiler::get().collect();
+    struct Ev {  // released on every return path
+        hipEvent_t e = nullptr;
+        ~Ev() { if (e) (void)hipEventDestroy(e); }
+    } ev0, ev1;
+    DLMA_HIP(hipEventCreate(&ev0.e));
+    DLMA_HIP(hipEventCreate(&ev1.e));
+    DLMA_HIP(hipEventRecord(ev0.e, s));
+    for (int k = 0; k < napply; ++k) DLMA_TRY(run(k));
+    DLMA_HIP(hipEventRecord(ev1.e, s));
+    DLMA_HIP(hipEventSynchronize(ev1.e));
+    float ms = 0;
+    DLMA_HIP(hipEventElapsedTime(&ms, ev0.e, ev1.e));
+    DLMA_HIP(hipStreamSynchronize(s));
+    if (Profiler::get().on) Profiler::get().collect();
+    if (ms_out) *ms_out = ms / napply;
+    return DLMA_OK;
+}
+
+// Dhat on right-hand-side tiles, of the same vectors each time
+int bench_tiles(Gauge* g, int nrhs, int napply, double* ms_out, double* bytes_out, hipStream_t s) {
+    DLMA_TRY(gauge_prepare_tiles(g, s));
+    const int Vh = g->Vh, nt = tile_count(nrhs);
+    const size_t tw = (size_t)Vh * 192;  // words of a tile
+    Buf f[3], d1, d2;
+    for (Buf& b : f) DLMA_TRY(b.allocate(sizeof(uint32_t) * nt * tw));
+    for (int i = 0; i < nt; ++i) DLMA_HIP(launch_tile_random(f[0].as<uint32_t>() + i * tw, 16 * Vh, 11u + i, s));
+    TileHopJob j1 = tile_hop_job(g, 1, nrhs), j2 = tile_hop_job(g, 0, nrhs);
+    j1.in = f[0].as<uint32_t>(); j1.out = f[1].as<uint32_t>();
+    j2.x = f[0].as<uint32_t>(); j2.in = f[1].as<uint32_t>(); j2.out = f[2].as<uint32_t>();
+    DLMA_TRY(upload(d1, std::vector<TileHopJob>{j1}, s));
+    DLMA_TRY(upload(d2, std::vector<TileHopJob>{j2}, s));
+    const int nblk = tile_hop_blocks(j1, g->geo.T);
+    const double by1 = hop_bytes(PB16, K1, 0, Vh, nrhs), by2 = hop_bytes(PB16, K2, 0, Vh, nrhs);
+    auto run = [&](int) -> int {
+        DLMA_TRY(tile_launch(K1, 0, d1, 1, nblk, 0, 0, KC_K1, by1, s));
+        return tile_launch(K2, 0, d2, 1, nblk, 0, 0, KC_K2, by2, s);
+    };
+    if (bytes_out) *bytes_out = by1 + by2;
+    return time_applications(run, napply, ms_out, s);
+}
+
 template <int P>
 int bench_impl(Gauge* g, int nrhs, int nb, int napply, double* ms_out, double* bytes_out, hipStream_t s) {
+    if constexpr (P == PB16)  // the solver's stencils for this many right-hand sides
+        if (nb == 0 && tile_fill({{&g->geo, nrhs}})) return bench_tiles(g, nrhs, napply, ms_out, bytes_out, s);
     DLMA_TRY(gauge_prepare(g, P, s));
     int Vh = g->Vh;
     size_t halfP = pair_bytes(P) * (size_t)nrhs * 12 * Vh;
@@ -1327,28 +1379,8 @@ int bench_impl(Gauge* g, int nrhs, int nb, int napply, double* ms_out, double* b
         DLMA_TRY(hop_launch<P>(HopCfg{K2, fwd ? 0 : F_G5OUT, nb, j2.wn}, (fwd ? d2f : d2b).p, 1, b2, KC_K2, by2, s));
         return DLMA_OK;
     };
-    DLMA_TRY(run(0));
-    DLMA_TRY(run(1));
-    DLMA_HIP(hipStreamSynchronize(s));
-    if (Profiler::get().on) Profiler::get().collect();
-    struct Ev {  // released on every return path
-        hipEvent_t e = nullptr;
-        ~Ev() { if (e) (void)hipEventDestroy(e); }
-    } ev0, ev1;
-    DLMA_HIP(hipEventCreate(&ev0.e));
-    DLMA_HIP(hipEventCreate(&ev1.e));
-    hipEvent_t e0 = ev0.e, e1 = ev1.e;
-    DLMA_HIP(hipEventRecord(e0, s));
-    for (int k = 0; k < napply; ++k) DLMA_TRY(run(k));
-    DLMA_HIP(hipEventRecord(e1, s));
-    DLMA_HIP(hipEventSynchronize(e1));
-    float ms = 0;
-    DLMA_HIP(hipEventElapsedTime(&ms, e0, e1));
-    DLMA_HIP(hipStreamSynchronize(s));
-    if (Profiler::get().on) Profiler::get().collect();
-    if (ms_out) *ms_out = ms / napply;
     if (bytes_out) *bytes_out = by1 + by2;
-    return DLMA_OK;
+    return time_applications(run, napply, ms_out, s);
 }
 }  // namespace
 
