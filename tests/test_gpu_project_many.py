@@ -59,3 +59,26 @@ def test_correlators_of_many_modes_and_sources(D):
         ref = (f @ V[t].reshape(nev, 96).conj().T.contiguous()).abs().square().sum().item()
         d = (t - 5) % 32
         assert abs(got[d, 0] - ref) <= (192 + 16 * nev * nd) * 2.0**-52 * ref and abs(got[d, 1]) <= 1e-9 * ref, t
+
+
+# 16384 modes, the limit of the allocation-free entry: four right-hand sides per pass through its
+# array, one-launch coefficients (2^3) and two site chunks of the contraction (14^3); 5 modes on
+# 4^2 x 8: passes of 3272 (contraction) and 13104 (allocation-free array)
+@pytest.mark.parametrize("dims,nev,n", [((2, 2, 2, 2), 16384, 9), ((2, 14, 14, 14), 16384, 9), ((2, 4, 4, 8), 5, 13110)])
+def test_allocation_free_passes(D, dims, nev, n):
+    print("passes", dims, nev, n, flush=True)
+    g = D.dlma_load_gauge(torch.from_numpy(synth.gauge_field(dims, 0.2, 3)).cuda(), 0.121, 1.0)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    V = torch.randn((nev,) + dims[1:] + (3,), dtype=torch.complex128, device="cuda", generator=gen)
+    x = torch.randn((n,) + dims + (4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    out = torch.empty_like(x)
+    D.dlma_project_noalloc(g, 1, V, x, 1, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, D.dlma_project(g, 1, V, x, 1))
+    keep = sorted({0, 3, 4, n - 1} | ({3271, 3272, 13103, 13104} if n > 13104 else set()))
+    f = x[keep, 1].reshape(len(keep), -1, 4, 3).transpose(1, 2).reshape(4 * len(keep), -1)
+    v = V.reshape(nev, -1)
+    ref = f - (f @ v.conj().T.contiguous()) @ v
+    tol = (v.shape[1] + nev + 8) * 2.0**-52 * ((f.abs() @ v.abs().T.contiguous()) @ v.abs() + f.abs())
+    got = out[keep, 1].reshape(len(keep), -1, 4, 3).transpose(1, 2).reshape(4 * len(keep), -1)
+    assert bool(((got - ref).abs() <= tol).all())
