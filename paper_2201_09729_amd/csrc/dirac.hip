@@ -168,7 +168,6 @@ __global__ void __launch_bounds__(256) k_dirac(DiracArgs a) {
         const double2 give = bw ? up[e] : low, keep = bw ? low : up[e];
         const double2 got = quad_swap(give, 2);
         s[e] = make_double2(-0.5 * (keep.x + got.x), -0.5 * (keep.y + got.y));
-        add_re(s[e], dg[e], v[e]);
     }
     auto conj = [](double2 z) { return make_double2(z.x, -z.y); };
     add_mul(s[1], own[0], v[0]);
@@ -181,6 +180,7 @@ __global__ void __launch_bounds__(256) k_dirac(DiracArgs a) {
     for (int b = 0; b < 3; ++b) {
 #pragma unroll
         for (int e = 0; e < 3; ++e) add_mul(s[b], crs[b][e], q[e]);
+        add_re(s[b], dg[b], v[b]);  // the largest term last: fewest roundings at its size
         if (on) a.out[me + b] = s[b];
     }
 }
@@ -188,10 +188,10 @@ __global__ void __launch_bounds__(256) k_dirac(DiracArgs a) {
 // One lane per site, a wave 64 consecutive sites of a (t, z) plane and one right-hand side.
 // Each neighbour set (and the wave's own sites) is read as contiguous 1 KB pieces, passes
 // through the wave's LDS (sites 13 numbers apart: no bank conflicts), and the next one is
-// on its way while this one is worked on.
-// Bound: the vector memory path, 216 loads per wave that mostly miss L1, at two waves per
-// SIMD (228 registers; three waves spill and take twice as long).  24^3 x 48, D^dag: one right-hand
-// side 462 to 265 us, 12 3151 to 1702 us (3.5 TB/s of fields, links and clover once).
+// on its way while this one is worked on; the own sites come last, with the clover term.
+// Bound: the vector memory path, 216 loads per wave, at two waves per SIMD (236 registers; three
+// waves spill and take twice as long).  24^3 x 48, D^dag, per call: one right-hand side 462 to
+// 267 us, 12 3151 to 1680 us (3.8 GB of fields, links and clover once: 2.3 TB/s).
 constexpr int PAD = 13;
 
 // the same on native vectors
@@ -298,7 +298,7 @@ __device__ __forceinline__ void hop_step(const SiteWave& w, const DiracArgs& a, 
     // the link first, then the next neighbours: loads come back in order
     D2 m[9];
     link<D>(w, a, m);
-    if constexpr (D < 7) fetch<D + 1>(w, a.g, st);
+    fetch<D + 1>(w, a.g, st);  // (8: its own sites)
     __builtin_amdgcn_sched_barrier(0);
     hop_site<D>(w.buf + w.lane * PAD, m, a.sg, acc);
 }
@@ -348,37 +348,9 @@ __global__ void __launch_bounds__(256, 2) k_dirac_sites(DiracArgs a) {
 
     D2 st[12];
     D2 acc[12];
-    fetch<8>(w, g, st);
-    place(w, st);
+#pragma unroll
+    for (int e = 0; e < 12; ++e) acc[e] = (D2){0.0, 0.0};
     fetch<0>(w, g, st);
-    {   // clover; the hopping sum enters with -1/2
-        const double2* C = (w.par ? a.C1 : a.C0) + w.cb;
-        const D2* v0 = w.buf + w.lane * PAD;
-        const uint32_t Vh = (uint32_t)g.Vh;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            __builtin_amdgcn_sched_barrier(0);
-            D2 v[6];
-#pragma unroll
-            for (int e = 0; e < 6; ++e) v[e] = -2.0 * v0[b * 6 + e];
-#pragma unroll
-            for (int e = 0; e < 3; ++e) {
-                const double2 d = C[(uint32_t)(b * 18 + e) * Vh];
-                acc[b * 6 + 2 * e] = d.x * v[2 * e];
-                acc[b * 6 + 2 * e + 1] = d.y * v[2 * e + 1];
-            }
-#pragma unroll
-            for (int hi = 1; hi < 6; ++hi) {
-                if (hi > 3) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int lo = 0; lo < hi; ++lo) {
-                    const double2 m = C[(uint32_t)(b * 18 + 3 + hi * (hi - 1) / 2 + lo) * Vh];
-                    add_mul(acc[b * 6 + hi], m.x, m.y, v[lo]);
-                    add_mul(acc[b * 6 + lo], m.x, -m.y, v[hi]);
-                }
-            }
-        }
-    }
     hop_step<0>(w, a, st, acc);
     hop_step<1>(w, a, st, acc);
     hop_step<2>(w, a, st, acc);
@@ -387,10 +359,48 @@ __global__ void __launch_bounds__(256, 2) k_dirac_sites(DiracArgs a) {
     hop_step<5>(w, a, st, acc);
     hop_step<6>(w, a, st, acc);
     hop_step<7>(w, a, st, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    {   // clover, its diagonal, the largest term, last: fewest roundings at its size; the hopping
+        // sum enters with -1/2
+        const double2* C = (w.par ? a.C1 : a.C0) + w.cb;
+        const uint32_t Vh = (uint32_t)g.Vh;
+        double2 m[2][18];
+#pragma unroll
+        for (int e = 0; e < 18; ++e) m[0][e] = C[(uint32_t)e * Vh];
+        place(w, st);
+        const D2* v0 = w.buf + w.lane * PAD;
+#pragma unroll
+        for (int e = 0; e < 18; ++e) m[1][e] = C[(uint32_t)(18 + e) * Vh];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            D2 v[6];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                v[e] = v0[b * 6 + e];
+                acc[b * 6 + e] *= -0.5;
+            }
+#pragma unroll
+            for (int hi = 1; hi < 6; ++hi) {
+#pragma unroll
+                for (int lo = 0; lo < hi; ++lo) {
+                    const double2 u = m[b][3 + hi * (hi - 1) / 2 + lo];
+                    add_mul(acc[b * 6 + hi], u.x, u.y, v[lo]);
+                    add_mul(acc[b * 6 + lo], u.x, -u.y, v[hi]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                add_re(acc[b * 6 + 2 * e], m[b][e].x, v[2 * e]);
+                add_re(acc[b * 6 + 2 * e + 1], m[b][e].y, v[2 * e + 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     // out through the same buffer
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int e = 0; e < 12; ++e) w.buf[w.lane * PAD + e] = -0.5 * acc[e];
+    for (int e = 0; e < 12; ++e) w.buf[w.lane * PAD + e] = acc[e];
     __builtin_amdgcn_wave_barrier();
     double2* o = a.out + rs + ((long)(w.t * g.Z + w.z) * w.plane + s0) * 12;
 #pragma unroll
