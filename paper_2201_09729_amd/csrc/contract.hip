@@ -24,16 +24,39 @@ namespace dlma {
 // every field is read once for both results.  Two column sets per wave halve the reads
 // of V (L2 hits: the waves of a block take consecutive groups of one chunk, and each
 // XCD walks a contiguous range of chunks).
-// Bound: the matrix cores (64 cycles per instruction, 8 flop per complex product).  At
+// A step's twelve products are summed among themselves and then added: a rounding at the
+// size of the sum for every twelve terms.  The next step's numbers are loaded while one is
+// worked on.
+// Bound: the matrix cores (64 cycles per instruction, 8 flop per complex product; two waves
+// per SIMD at 220 registers with the Grams and 32 modes).  At
 // 16^3 x 32 with 32 modes, 128 distillation and 32 noise solutions the projections and
 // Grams took 23.8 ms as one block per field and four modes, every field read nev / 4
 // times for tau and 8 times for the Grams, and the sums over groups and spins 43 ms on
-// the host (67.2 ms per call); now 1.75 ms per call, 41 TFLOP/s of a 64 TFLOP/s FP64
-// matrix product.
+// the host (67.2 ms per call); now 1.64 ms per call, 89 GFLOP in matrix instructions: 54
+// TFLOP/s over the call, of a 64 TFLOP/s FP64 matrix product.  Without the next step's loads
+// under way 1.72 ms; 24x12^3 with 48 modes 1.26, 1.17.
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double2 cconjmul(double2 a, double2 b) { return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x); }
 __device__ __forceinline__ d4 mma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+// sums over four sites and three colours of conj(a) b: real or imaginary parts
+__device__ __forceinline__ d4 dot12(const double2 (&a)[3], const double2 (&b)[3], bool im) {
+    d4 r = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        r = mma64(a[c].x, im ? b[c].y : b[c].x, r);
+        r = mma64(im ? -a[c].y : a[c].y, im ? b[c].x : b[c].y, r);
+    }
+    return r;
+}
+// and of Re(a) Im(a)
+__device__ __forceinline__ d4 cross12(const double2 (&a)[3]) {
+    d4 r = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r = mma64(a[c].x, a[c].y, r);
+    return r;
+}
 
 // Result tile (re, im) of one wave into [16][16] complex numbers, rows limited to nrow
 __device__ __forceinline__ void store_tile(double2* o, int lane, int nrow, const d4& re, const d4& im) {
@@ -44,7 +67,7 @@ __device__ __forceinline__ void store_tile(double2* o, int lane, int nrow, const
 }
 
 template <bool NOISE, bool GRAM, int MT>
-__global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
+__global__ void __launch_bounds__(256, GRAM ? 2 : 1) k_contract(ContractArgs a) {
     // block -> (unit group fastest, site chunk, timeslice), contiguous per XCD
     const int per = gridDim.x >> 3;
     const int lb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -75,8 +98,8 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
     d4 tr[2][MT], tm[2][MT], g00r = z, g00x = z, g10r = z, g10i = z;
 #pragma unroll
     for (int b = 0; b < MT; ++b) { tr[0][b] = z; tr[1][b] = z; tm[0][b] = z; tm[1][b] = z; }
-    for (long x = x0; x < x1; x += 4) {
-        double2 f0[3], f1[3], v[MT][3];
+    double2 f0[3], f1[3], v[MT][3];
+    auto load = [&] {
 #pragma unroll
         for (int c = 0; c < 3; ++c) { f0[c] = p0[c]; f1[c] = p1[c]; }
 #pragma unroll
@@ -87,35 +110,36 @@ __global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
         p1 += 48;
 #pragma unroll
         for (int b = 0; b < MT; ++b) pv[b] += 12;
+    };
+    if (x0 < x1) load();
+    for (long x = x0; x < x1; x += 4) {
+        double2 c0[3], c1[3], cv[MT][3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
+        for (int c = 0; c < 3; ++c) { c0[c] = f0[c]; c1[c] = f1[c]; }
 #pragma unroll
-            for (int b = 0; b < MT; ++b) {
-                const double vr = v[b][c].x, vi = v[b][c].y, nvi = -vi;
-                tr[0][b] = mma64(vr, f0[c].x, tr[0][b]);
-                tm[0][b] = mma64(vr, f0[c].y, tm[0][b]);
-                tr[1][b] = mma64(vr, f1[c].x, tr[1][b]);
-                tm[1][b] = mma64(vr, f1[c].y, tm[1][b]);
-                tr[0][b] = mma64(vi, f0[c].y, tr[0][b]);
-                tm[0][b] = mma64(nvi, f0[c].x, tm[0][b]);
-                tr[1][b] = mma64(vi, f1[c].y, tr[1][b]);
-                tm[1][b] = mma64(nvi, f1[c].x, tm[1][b]);
-            }
-            if (GRAM) {
-                // (A, A): the imaginary part is X - X^T with X = Re(A)^T Im(A)
-                g00r = mma64(f0[c].x, f0[c].x, g00r);
-                g00x = mma64(f0[c].x, f0[c].y, g00x);
-                g00r = mma64(f0[c].y, f0[c].y, g00r);
-                if (NOISE) {
-                    g10r = mma64(f1[c].x, f0[c].x, g10r);
-                    g10i = mma64(f1[c].x, f0[c].y, g10i);
-                    g10r = mma64(f1[c].y, f0[c].y, g10r);
-                    g10i = mma64(-f1[c].y, f0[c].x, g10i);
-                } else if (two) {
-                    g00r = mma64(f1[c].x, f1[c].x, g00r);
-                    g00x = mma64(f1[c].x, f1[c].y, g00x);
-                    g00r = mma64(f1[c].y, f1[c].y, g00r);
-                }
+        for (int b = 0; b < MT; ++b)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) cv[b][c] = v[b][c];
+        if (x + 4 < x1) load();  // the next step's, while this one is worked on
+        // twelve products at a time are summed among themselves before they join the sum: a
+        // rounding at its size for every twelve terms
+#pragma unroll
+        for (int b = 0; b < MT; ++b) {
+            tr[0][b] += dot12(cv[b], c0, false);
+            tm[0][b] += dot12(cv[b], c0, true);
+            tr[1][b] += dot12(cv[b], c1, false);
+            tm[1][b] += dot12(cv[b], c1, true);
+        }
+        if (GRAM) {
+            // (A, A): the imaginary part is X - X^T with X = Re(A)^T Im(A)
+            g00r += dot12(c0, c0, false);
+            g00x += cross12(c0);
+            if (NOISE) {
+                g10r += dot12(c1, c0, false);
+                g10i += dot12(c1, c0, true);
+            } else if (two) {
+                g00r += dot12(c1, c1, false);
+                g00x += cross12(c1);
             }
         }
     }
@@ -184,14 +208,15 @@ __global__ void __launch_bounds__(256) k_sum_parts(const double2* __restrict__ p
         }
         sm[sl][e] = v;
         __syncthreads();
-        if (sl == 0) {
-            for (int k = 1; k < 16; ++k) {
-                v.x += sm[k][e].x;
-                v.y += sm[k][e].y;
+        for (int half = 8; half > 0; half >>= 1) {  // pairwise
+            if (sl < half) {
+                v.x += sm[sl + half][e].x;
+                v.y += sm[sl + half][e].y;
+                sm[sl][e] = v;
             }
-            o[i] = v;
+            __syncthreads();
         }
-        __syncthreads();
+        if (sl == 0) o[i] = v;
     }
 }
 
@@ -327,6 +352,14 @@ hipError_t launch_corr_pieces(const CorrPiecesArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// re + i im += x w over four columns, summed among themselves first: a rounding at the size of
+// the sum for every four terms
+__device__ __forceinline__ void mac4(d4& re, d4& im, double2 x, double2 w) {
+    const d4 z = {0.0, 0.0, 0.0, 0.0};
+    re += mma64(-x.y, w.y, mma64(x.x, w.x, z));
+    im += mma64(x.y, w.x, mma64(x.x, w.y, z));
+}
+
 // ---------------------------------------------------------------- projector
 //
 // box(t) in = sum_k v_k c_k with c = V^dag in on the contraction kernel (a right-hand side
@@ -334,12 +367,12 @@ hipError_t launch_corr_pieces(const CorrPiecesArgs& a, hipStream_t s) {
 // matrix product (32 rows (site, colour) and four or eight right-hand sides per wave) in one
 // launch with the zero fill of the other timeslices.  Bound: the fill, a stream of
 // stores.  With a thread per (site, spin) storing 48 bytes apart and a block per (mode,
-// right-hand side) for c, 32 modes and right-hand sides at 24^3 x 48 took 1.32 ms;
-// 0.77 ms so (6.3 TB/s of stores).
+// right-hand side) for c, 32 modes and right-hand sides at 24^3 x 48 took 1.32 ms; 0.78 ms so
+// (4.1 GB of stores: 5.3 TB/s over the call).
 constexpr int FILL_PER_BLOCK = 1024;
 
 template <int H>  // column sets per wave
-__global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long fs,
+__global__ void __launch_bounds__(256, 4) k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long fs,
                                                     int t, int nev, const double2* __restrict__ coef, int nrhs, int mode,
                                                     unsigned nab, unsigned nrb) {
     const long tofs = (long)t * L3 * 12;
@@ -375,23 +408,22 @@ __global__ void __launch_bounds__(256) k_proj_apply(const double2* __restrict__ 
         for (int b = 0; b < 2; ++b) re[h][b] = im[h][b] = z;
     const double2* v = Vt + (long)q * nrow;
     const double2* c = coef + ((long)ub * H * nev + q) * 16 + m;
-    const double2 zz = make_double2(0.0, 0.0);
     for (int k = 0; k < nev; k += 4) {
-        const bool ok = k + q < nev;
         double2 x[2], w[H];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) x[b] = ok ? v[(long)k * nrow + row[b]] : zz;
-        w[0] = ok ? c[(long)k * 16] : zz;
-        if (H == 2) w[H - 1] = ok && two ? c[((long)nev + k) * 16] : zz;
+        for (int b = 0; b < 2; ++b) x[b] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int h = 0; h < H; ++h) w[h] = make_double2(0.0, 0.0);
+        if (k + q < nev) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) x[b] = v[(long)k * nrow + row[b]];
+            w[0] = c[(long)k * 16];
+            if (two) w[H - 1] = c[((long)nev + k) * 16];
+        }
 #pragma unroll
         for (int h = 0; h < H; ++h)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                re[h][b] = mma64(x[b].x, w[h].x, re[h][b]);
-                im[h][b] = mma64(x[b].x, w[h].y, im[h][b]);
-                re[h][b] = mma64(-x[b].y, w[h].y, re[h][b]);
-                im[h][b] = mma64(x[b].y, w[h].x, im[h][b]);
-            }
+            for (int b = 0; b < 2; ++b) mac4(re[h][b], im[h][b], x[b], w[h]);
     }
 #pragma unroll
     for (int h = 0; h < H; ++h) {
@@ -559,95 +591,82 @@ hipError_t launch_tau_weights(const double2* tau, const double2* WP, const int* 
 // group's (field, spin) inputs, then over the modes, on FP64 matrix instructions.  Rows
 // are the A operand (of V: 256 contiguous bytes per mode), the 16 outputs (field, spin)
 // of each of the unit's two halves the columns, so V is read once for both halves.
-// Bound: the matrix cores and the field streams alike.  At 12^3 x 24 with 21 modes,
-// 13 distillation and 6 noise groups forward and backward together took 20.9 ms (tau and
-// tau' on the host, a VALU kernel here), 2.50 ms with the projections above, 1.85 ms so.
+// Bound: the matrix cores and the field streams alike, four waves per SIMD.  At 12^3 x 24 with 21
+// modes, 13 distillation and 6 noise groups forward and backward together took 20.9 ms (tau and
+// tau' on the host, a VALU kernel here), 2.50 ms with the projections above, 1.80 ms so.
 template <bool NOISE>
-__global__ void __launch_bounds__(256) k_corr_grad(CorrGradArgs a) {
+__global__ void __launch_bounds__(256, 4) k_corr_grad(CorrGradArgs a) {
     constexpr int NIN = NOISE ? 32 : 16;
     const int t = blockIdx.y, unit = blockIdx.z;
     const int g0 = NOISE ? unit : 2 * unit;
-    const bool two = NOISE || g0 + 1 < a.ndist;
+    const bool two = NOISE || g0 + 1 < a.ndist;  // a lone group is its own second half, not stored
     const int lane = (int)threadIdx.x & 63, q = lane >> 4, m = lane & 15;
     const long L3 = a.L3, nrow = L3 * 3;
     const long r0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
     if (r0 >= nrow) return;  // whole waves
     const int ta = a.tact[t];  // uniform: the timeslice carries weights or not
-    d4 re[2][2], im[2][2];  // [half][row tile]
     const d4 z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) re[h][b] = im[h][b] = z;
+    d4 re00 = z, im00 = z, re01 = z, im01 = z, re10 = z, im10 = z, re11 = z, im11 = z;  // half, row tile
     const long tofs = (long)t * L3 * 12;
     if (ta >= 0) {
         // operand rows of this lane (past the last row: the last one, not stored)
-        long row[2];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const long r = r0 + 16 * b + m;
-            row[b] = r < nrow ? r : nrow - 1;
-        }
-        auto mac = [&](int h, int b, double2 x, double2 w) {
-            re[h][b] = mma64(x.x, w.x, re[h][b]);
-            im[h][b] = mma64(x.x, w.y, im[h][b]);
-            re[h][b] = mma64(-x.y, w.y, re[h][b]);
-            im[h][b] = mma64(x.y, w.x, im[h][b]);
-        };
+        const long row0 = min(r0 + m, nrow - 1), row1 = min(r0 + 16 + m, nrow - 1);
         // W1 F: inputs (field j, spin q)
         const double2* W = (NOISE ? a.W1n : a.W1d) + (long)t * NIN * NIN + (long)m * NIN + q;
-        const long f0 = tofs + row[0] / 3 * 12 + row[0] % 3 + q * 3, f1 = tofs + row[1] / 3 * 12 + row[1] % 3 + q * 3;
-#pragma unroll
+        const long f0 = tofs + row0 / 3 * 12 + row0 % 3 + q * 3, f1 = tofs + row1 / 3 * 12 + row1 % 3 + q * 3;
+        const long half = two ? 4 * a.fs : 0;
+#pragma unroll 1
         for (int j = 0; j < NIN / 4; ++j) {
-            if (NOISE) {
-                const double2* f = (j < 4 ? a.phi : a.phibar) + ((long)g0 * 4 + (j & 3)) * a.fs;
-                const double2 x0 = f[f0], x1 = f[f1], w0 = W[j * 4], w1 = W[16 * NIN + j * 4];
-                mac(0, 0, x0, w0);
-                mac(0, 1, x1, w0);
-                mac(1, 0, x0, w1);
-                mac(1, 1, x1, w1);
-            } else {
-                const double2 w = W[j * 4];
-                const double2* f = a.dist + ((long)g0 * 4 + j) * a.fs;
-                mac(0, 0, f[f0], w);
-                mac(0, 1, f[f1], w);
-                if (two) {
-                    f += 4 * a.fs;
-                    mac(1, 0, f[f0], w);
-                    mac(1, 1, f[f1], w);
-                }
+            const double2* f = (NOISE ? (j < 4 ? a.phi : a.phibar) : a.dist) + ((long)g0 * 4 + (NOISE ? (j & 3) : j)) * a.fs;
+            const double2 x0 = f[f0], x1 = f[f1], w0 = W[j * 4];
+            mac4(re00, im00, x0, w0);
+            mac4(re01, im01, x1, w0);
+            if (NOISE) {  // the same inputs, the rows of phibar
+                const double2 w1 = W[16 * NIN + j * 4];
+                mac4(re10, im10, x0, w1);
+                mac4(re11, im11, x1, w1);
+            } else {  // the same weights, the second group
+                mac4(re10, im10, f[half + f0], w0);
+                mac4(re11, im11, f[half + f1], w0);
             }
         }
         // V tau': four modes at a time (past the last: zero)
         const double2* v = a.Vall + ((long)t * a.nev + q) * nrow;
-        const long ts = (long)a.nact * a.nev * 16;
         const double2* tp = NOISE ? a.taun + (((long)g0 * a.nact + ta) * a.nev + q) * 32 + m
                                   : a.taud + (((long)g0 * a.nact + ta) * a.nev + q) * 16 + m;
+        const long ts = NOISE ? 16 : (two ? (long)a.nact * a.nev * 16 : 0);
+#pragma unroll 1
         for (int k = 0; k < a.nev; k += 4) {
             const bool ok = k + q < a.nev;
-            const double2 zz = make_double2(0.0, 0.0);
-            const double2 x0 = ok ? v[(long)k * nrow + row[0]] : zz, x1 = ok ? v[(long)k * nrow + row[1]] : zz;
-            const double2 w0 = ok ? tp[(long)k * NIN] : zz;
-            const double2 w1 = ok && two ? (NOISE ? tp[(long)k * NIN + 16] : tp[(long)k * NIN + ts]) : zz;
-            mac(0, 0, x0, w0);
-            mac(0, 1, x1, w0);
-            mac(1, 0, x0, w1);
-            mac(1, 1, x1, w1);
+            double2 x0 = make_double2(0.0, 0.0), x1 = x0, w0 = x0, w1 = x0;
+            if (ok) {
+                x0 = v[(long)k * nrow + row0];
+                x1 = v[(long)k * nrow + row1];
+                w0 = tp[(long)k * NIN];
+                w1 = tp[(long)k * NIN + ts];
+            }
+            mac4(re00, im00, x0, w0);
+            mac4(re01, im01, x1, w0);
+            mac4(re10, im10, x0, w1);
+            mac4(re11, im11, x1, w1);
         }
     }
     // result register i of this lane: row 4 i + q, output m = (field, spin)
+    auto store = [&](double2* o, int b, d4 re, d4 im) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h == 1 && !two) break;
-        double2* o = (NOISE ? (h == 0 ? a.gphi : a.gphibar) + ((long)g0 * 4 + (m >> 2)) * a.fs
-                            : a.gdist + ((long)(g0 + h) * 4 + (m >> 2)) * a.fs) + tofs + (m & 3) * 3;
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const long r = r0 + 16 * b + 4 * i + q;
-                if (r < nrow) o[r / 3 * 12 + r % 3] = make_double2(re[h][b][i], im[h][b][i]);
-            }
+        for (int i = 0; i < 4; ++i) {
+            const long r = r0 + 16 * b + 4 * i + q;
+            if (r < nrow) o[r / 3 * 12 + r % 3] = make_double2(re[i], im[i]);
+        }
+    };
+    const long of = ((long)g0 * 4 + (m >> 2)) * a.fs + tofs + (m & 3) * 3;
+    double2* o0 = (NOISE ? a.gphi : a.gdist) + of;
+    store(o0, 0, re00, im00);
+    store(o0, 1, re01, im01);
+    if (two) {
+        double2* o1 = NOISE ? a.gphibar + of : o0 + 4 * a.fs;
+        store(o1, 0, re10, im10);
+        store(o1, 1, re11, im11);
     }
 }
 
