@@ -41,15 +41,8 @@ KCLASS = {0: "hop_k1 (odd sites: y = A_oo^-1 D_oe x)",
           3: "hop_k2_cg (even sites: q = A_ee w - D_eo y fused with r -= alpha q, x += alpha w, |r|^2)",
           4: "hop_k2 (even sites: z = A_ee x - D_eo y)",
           8: "hop_k2_dotr (even sites: v = A_ee p - D_eo y with (rh, v))",
-          9: "hop_k2_dotx (even sites: t = A_ee s - D_eo y with (t, s) and |t|^2)"}
-KTEMPLATE = {0: (0, 0), 1: (0, 1), 2: (1, 6), 3: (1, 8), 4: (1, 0), 8: (1, 512), 9: (1, 256)}
-
-
-def ktemplate(kc, prec):
-    """(kind, flags) of a class's hop_kernel: FP16 BiCGStab's K2 for t also forms (rh, t) (flag 1024)."""
-    if kc == 9 and prec == "mix_fp16":
-        return (1, 256 | 1024)
-    return KTEMPLATE[kc]
+          9: "hop_k2_dotx (even sites: t = A_ee s - D_eo y with (t, s), |t|^2 and (rh, t))"}
+KTEMPLATE = {0: (0, 0), 1: (0, 1), 2: (1, 6), 3: (1, 8), 4: (1, 0), 8: (1, 512), 9: (1, 256 | 1024)}
 PREC_ID = {"fp64": 0, "mix_fp32": 1, "mix_fp16": 2, "mix_bf16": 3}
 HOP_SOURCES = ["paper_2201_09729_amd/csrc/hop.h", "paper_2201_09729_amd/csrc/hop16.h", "paper_2201_09729_amd/csrc/common.h",
                "paper_2201_09729_amd/csrc/hop_inst.h"]
@@ -225,7 +218,7 @@ def main():
     # v = Dhat p and for t = Dhat s.
     kc = max(prof, key=lambda k: prof[k][1])
     n_l, ms_tot, by_all = prof[kc]
-    fixed, per_rhs = hop_bytes_split(args.prec, *ktemplate(kc, args.prec), DIMS)
+    fixed, per_rhs = hop_bytes_split(args.prec, *KTEMPLATE[kc], DIMS)
     per_iter = 2 if (args.inner_solver == 1 and kc == 0) else 1  # BiCGStab applies K1 twice per iteration
     rhs_launches = per_iter * sum(s["inner_iters"] for stp in pstats for s in stp)
     by_tot = n_l * fixed + rhs_launches * per_rhs
@@ -650,7 +643,7 @@ def summarize(args):
     stencil kernels, with FETCH_SIZE / WRITE_SIZE scaled by what the counters read for
     the 1 GiB device copy of --copy-probe (kernel __amd_rocclr_copyBuffer).  The
     per-class averages and counters cover the timed step only: the dispatches after
-    its gauge load (the last k_pack_links), so that the autotuner's and the warm-up's
+    its gauge load (the last k_ingest), so that the autotuner's and the warm-up's
     launches of the same kernels do not enter them."""
     import csv
     import collections
@@ -668,7 +661,7 @@ def summarize(args):
 
     def timed_step(rows):
         rows = sorted(rows, key=lambda r: int(r["Start_Timestamp"]))
-        starts = [i for i, r in enumerate(rows) if "k_pack_links" in r["Kernel_Name"]]
+        starts = [i for i, r in enumerate(rows) if "k_ingest" in r["Kernel_Name"]]
         return rows[starts[-1]:] if starts else rows
 
     step_ms = collections.defaultdict(list)
@@ -692,7 +685,7 @@ def summarize(args):
     def hop_name(kc, nb):
         """The full kernel name of the class as rocprofv3 prints it (matched on the
         template arguments, whatever the parameter list)."""
-        kind, fl = ktemplate(kc, prec)
+        kind, fl = KTEMPLATE[kc]
         head = "void dlma::hop_kernel<%d, %d, %d, %d, 128>(" % (pid, nb, kind, fl)
         for nm in step_ms:
             if nm.startswith(head):
@@ -724,7 +717,7 @@ def summarize(args):
         tb = (fk * scale["FETCH_SIZE"] + wk * scale["WRITE_SIZE"]) * 1024.0
         avg_ms = sum(step_ms[nm]) / len(step_ms[nm])
         lines.append("| %s | `hop_kernel<%d,%d,%d,%d>` | %d | %.0f | %.0f | %.3f | %.4f |"
-                     % (KCLASS[kc].split()[0], pid, nb, ktemplate(kc, prec)[0], ktemplate(kc, prec)[1], len(f), fk, wk,
+                     % (KCLASS[kc].split()[0], pid, nb, *KTEMPLATE[kc], len(f), fk, wk,
                         tb / 1e9, avg_ms))
         out[kc] = {"kernel": nm, "precision": prec, "rhs_block": nb, "source_sha": sources_sha(),
                    "fetch_kib_per_dispatch": fk, "write_kib_per_dispatch": wk, "copy_scale": scale,

@@ -105,7 +105,8 @@ int dlma_gauge_info(dlma_gauge_t g, int dims_out[4], double* kappa_out, double* 
 /*
  * out = D in (dagger = 0) or out = D^dag in = g5 D g5 in (dagger = 1), FP64,
  * for nrhs spinor fields in canonical layout.
- *   in, out  device, [nrhs][T][Z][Y][X][4][3] complex128; must not overlap.
+ *   in, out  device, [nrhs][T][Z][Y][X][4][3] complex128; out != in.  (Fields that
+ *            overlap in part cost a copy of in.)
  */
 int dlma_apply_dw(dlma_gauge_t g, const void* in, void* out, int nrhs, int dagger, void* stream);
 
@@ -121,8 +122,10 @@ int dlma_apply_dw(dlma_gauge_t g, const void* in, void* out, int nrhs, int dagge
  * precision, and the result is rounded once more before it is widened to FP64.
  *   in, out      device, [nrhs][T][Z][Y][X][4][3] complex128; must not overlap.
  *                Odd sites of in are ignored; odd sites of out are set to 0.
- *   rhs_block    right-hand sides per thread (1 .. 4), or 0 for the launch shape
- *                the solver's autotuner picks (super_group and lds_window ignored)
+ *   rhs_block    right-hand sides per thread (1 .. 4), or 0 for the kernels and launch
+ *                shape that dlma_solve takes (super_group and lds_window ignored):
+ *                the autotuner's, or, in BF16 without dagger and with well filled
+ *                tiles of 16 right-hand sides, the tile stencils
  *   super_group  right-hand-side groups per super-group of the block order (0 = all)
  *   lds_window   FP16 only: 1 = stage the +-x, +-y neighbours of each block through
  *                LDS when they fit, 0 = read every neighbour from memory
@@ -140,7 +143,10 @@ typedef struct {
     int prec;          /* DLMA_PREC_* */
     double inner_tol;  /* relative reduction of the inner residual per pass; 0 = default
                           (FP16 1e-3, BF16 1e-2, FP32 1e-5) */
-    int rhs_block;     /* right-hand sides per thread in the stencil kernels: 0 = autotune, or 1 .. 4 */
+    int rhs_block;     /* right-hand sides per thread in the stencil kernels: 0 = autotune, or 1 .. 4.
+                          BF16 BiCGStab solves with 0 and well filled tiles of 16 right-hand sides
+                          take the matrix-instruction stencils, which are not autotuned; 1 .. 4
+                          select the per-thread stencils */
     int use_x0;        /* 1: x holds the start vector on entry; 0: start from x = 0 */
     int graph_iters;   /* inner iterations captured in one hipGraph and replayed at the start of
                           each pass (replaces check_every); later convergence checks of the pass
@@ -343,7 +349,7 @@ int dlma_dot(const void* a, const void* b, long n, double* out, void* stream);
  *                   Rayleigh-Ritz step)
  * and the stencils of the BiCGStab inner solver (K1 of both applications is class 0):
  *   8 = hop_k2_dotr even sites, v = A_ee p - D_eo y, with (rh, v)
- *   9 = hop_k2_dotx even sites, t = A_ee s - D_eo y, with (t, s) and |t|^2
+ *   9 = hop_k2_dotx even sites, t = A_ee s - D_eo y, with (t, s), |t|^2 and (rh, t)
  * dlma_profile_read returns the launch count, total milliseconds and total
  * algorithmic bytes (compulsory HBM traffic of the launches, summed) per class.
  */

@@ -17,13 +17,14 @@
 // Block order: an XCD owns a contiguous range of timeslices (and of z, with few timeslices)
 // and walks strips of y rows outermost, then z, then its timeslices, so the +-t and +-z
 // neighbours of a strip stay in its L2.
-// Bound: latency and the misses of L2 (a site's 6 KB of neighbours come 1.6 to 2 times
-// over from the memory side); 75 to 85 registers keep six waves per SIMD.  48x24^3 with 96
-// right-hand sides: K1 1.29, K2 1.44 ms (1.9 and 2.1 ms with one thread per site and one to
-// four right-hand sides, FP32 arithmetic on the vector units); 24x12^3 with 72: 74 and 71 us (94
-// and 98).  Blocks of two to six tiles sharing a site's turned words were slower (1.45 to 1.8 ms):
-// the registers they need leave three waves per SIMD.  24 to 100 sites per block are alike, 256 are 10%
-// slower.
+// Bound: the texture address path (0.74 to 0.87 busy), L2 misses (hits 0.59 to 0.64; the fields
+// come 1.6 to 2 times over from the memory side) and LDS (the turned words are read a word per
+// lane, bank conflicts in 0.34 to 0.40 of the cycles), in three uneven configurations with 160
+// right-hand sides.  Waves per SIMD by registers: K1 six (78), K2 with (rh, v) five (91), K2 with
+// (t, s) four (100).  48x24^3 with 96 right-hand sides: K1 1.29, K2 1.44 ms (1.9 and 2.1 ms with
+// one thread per site and one to four right-hand sides, FP32 arithmetic on the vector units);
+// 24x12^3 with 72: 74 and 71 us (94 and 98).  Blocks of two to six tiles sharing a site's turned
+// words were slower (1.45 to 1.8 ms): the registers they need leave three waves per SIMD.
 #include "tile_dev.h"
 
 namespace dlma {
