@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) k_dirac(DiracArgs a) {
 // Each neighbour set (and the wave's own sites) is read as contiguous 1 KB pieces, passes
 // through the wave's LDS (sites 13 numbers apart: few bank conflicts), and the next one is
 // on its way while this one is worked on; the own sites come last, with the clover term.
-// Bound: the vector memory path (texture address unit 0.97 busy, 228 loads and stores per wave, 2.2
+// Bound: the vector memory path (texture address unit 0.97 busy, 228 loads and stores per wave, 3.8
 // times the compulsory reads from the memory side: 5.9 TB/s in all), at two waves per SIMD (236
 // registers; three waves spill and take twice as long).  24^3 x 48, D^dag, per call: one right-hand side 462 to
 // 267 us, 12 3151 to 1680 us (3.8 GB of fields, links and clover once: 2.3 TB/s).
