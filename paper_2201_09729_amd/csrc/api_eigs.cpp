@@ -841,9 +841,12 @@ extern "C" int dlma_project(dlma_gauge_t h, int t, int nev, const void* V_t, con
     Buf coef, part;
     const long per = 16L * std::max(1, nev), sets = std::min<long>((nrhs + 3L) / 4, 16384);
     const long nc = per * sets, np = per * sets * project_ks(g->geo, nev);
-    const long cap = std::max(std::min(np, 4 * PROJ_PART_CAP), per * project_ks(g->geo, nev));
+    const long least = per * project_ks(g->geo, nev);  // one column set's partials
+    long cap = std::max(std::min(np, 4 * PROJ_PART_CAP), least);
     DLMA_TRY(coef.allocate(sizeof(double2) * nc));
-    DLMA_TRY(part.allocate(sizeof(double2) * cap));
+    int rc = part.allocate(sizeof(double2) * cap);
+    if (rc == DLMA_ENOMEM) rc = part.allocate(sizeof(double2) * (cap = least));
+    DLMA_TRY(rc);
     DLMA_HIP(launch_project((const double2*)V_t, (const double2*)in, (double2*)out, g->geo, t, nev, nrhs, mode, coef.as<double2>(), nc,
                             part.as<double2>(), cap, s));
     DLMA_HIP(hipStreamSynchronize(s));
@@ -909,7 +912,7 @@ extern "C" int dlma_correlators(dlma_gauge_t h, int t_src, int nev, const void* 
     const long fs = g->V * 12;  // complex numbers per spinor field
     const long L3 = (long)g->dims[1] * g->dims[2] * g->dims[3];
     const int ud = (ndist + 1) / 2, un = nnoise;  // units of the contraction kernel
-    const int ksd = contract_ks(g->geo, T, ud), ksn = contract_ks(g->geo, T, un);
+    int ksd = contract_ks(g->geo, T, ud), ksn = contract_ks(g->geo, T, un);
     const size_t taud = (size_t)ndist * T * nev * 16, taun = (size_t)2 * nnoise * T * nev * 16;
     const size_t np = (size_t)T * proj_gram_parts() * 256;
     // spin weights: the piece <A_{s'}, M B_s> N_{s s'} takes entry (s', a), (s, b) of a Gram
@@ -929,15 +932,23 @@ extern "C" int dlma_correlators(dlma_gauge_t h, int t_src, int nev, const void* 
                             W[(size_t)gi * 256 + (sq * 4 + a) * 16 + sp * 4 + b] += N.m[sp][sq] * M.m[a][b] / (double)Gs.size();
         }
     }
-    // work buffers in one allocation: tau and its partials, Gram and projected partials, weights, result
-    size_t off = 0;
-    auto take = [&](size_t n) { const size_t o = off; off += n; return o; };
-    const size_t o_td = take(taud), o_tdp = take(ksd > 1 ? taud * ksd : 0), o_gd = take((size_t)T * ksd * ud * 256);
-    const size_t o_tn = take(taun), o_tnp = take(ksn > 1 ? taun * ksn : 0), o_gn = take((size_t)T * ksn * un * 512);
-    const size_t o_pd = take(np), o_pn = take(np), o_pq = take(np), o_w = take(W.size());
-    const size_t o_c = take((size_t)DLMA_NGAMMA * DLMA_NPARTS * T);
+    // work buffers in one allocation: tau and its partials, Gram and projected partials, weights,
+    // result; with fewer site chunks, so smaller partials, where they do not fit
+    size_t off, o_td, o_tdp, o_gd, o_tn, o_tnp, o_gn, o_pd, o_pn, o_pq, o_w, o_c;
     Buf ws;
-    DLMA_TRY(ws.allocate(sizeof(double2) * off));
+    for (;;) {
+        off = 0;
+        auto take = [&](size_t n) { const size_t o = off; off += n; return o; };
+        o_td = take(taud); o_tdp = take(ksd > 1 ? taud * ksd : 0); o_gd = take((size_t)T * ksd * ud * 256);
+        o_tn = take(taun); o_tnp = take(ksn > 1 ? taun * ksn : 0); o_gn = take((size_t)T * ksn * un * 512);
+        o_pd = take(np); o_pn = take(np); o_pq = take(np); o_w = take(W.size());
+        o_c = take((size_t)DLMA_NGAMMA * DLMA_NPARTS * T);
+        const int rc = ws.allocate(sizeof(double2) * off);
+        if (rc == DLMA_OK) break;
+        if (rc != DLMA_ENOMEM || (ksd == 1 && ksn == 1)) return rc;
+        ksd = (ksd + 1) / 2;
+        ksn = (ksn + 1) / 2;
+    }
     double2* w = ws.as<double2>();
     DLMA_HIP(hipMemcpyAsync(w + o_w, W.data(), sizeof(cplx) * W.size(), hipMemcpyHostToDevice, s));
     ContractArgs ca = {};
@@ -1068,7 +1079,7 @@ extern "C" int dlma_correlators_grad(dlma_gauge_t h, int t_src, int nev, const v
     Buf dW1n, dW1d, dWPn, dWPd, dTn, dTd, dTact, dtau, dtaup;
     DLMA_TRY(dTact.allocate(sizeof(int) * 2 * T));
     DLMA_HIP(hipMemcpyAsync(dTact.p, tact.data(), sizeof(int) * T, hipMemcpyHostToDevice, s));
-    const int ksd = contract_ks(g->geo, nact, (ndist + 1) / 2), ksn = contract_ks(g->geo, nact, nnoise);
+    int ksd = contract_ks(g->geo, nact, (ndist + 1) / 2), ksn = contract_ks(g->geo, nact, nnoise);
     const size_t taud = (size_t)ndist * nact * nev * 16, taun = (size_t)nnoise * nact * nev * 32;
     DLMA_TRY(dTn.allocate(sizeof(double2) * taun));
     DLMA_TRY(dTd.allocate(sizeof(double2) * taud));
@@ -1076,7 +1087,13 @@ extern "C" int dlma_correlators_grad(dlma_gauge_t h, int t_src, int nev, const v
         int* dtl = dTact.as<int>() + T;
         DLMA_HIP(hipMemcpyAsync(dtl, tlist.data(), sizeof(int) * nact, hipMemcpyHostToDevice, s));
         DLMA_TRY(dtau.allocate(sizeof(double2) * std::max(taud, taun)));
-        DLMA_TRY(dtaup.allocate(sizeof(double2) * std::max(taud * ksd, taun * ksn)));
+        for (;;) {  // partials of the site chunks, of fewer of them where they do not fit
+            const int rc = dtaup.allocate(sizeof(double2) * std::max(ksd > 1 ? taud * ksd : 0, ksn > 1 ? taun * ksn : 0));
+            if (rc == DLMA_OK) break;
+            if (rc != DLMA_ENOMEM || (ksd == 1 && ksn == 1)) return rc;
+            ksd = (ksd + 1) / 2;
+            ksn = (ksn + 1) / 2;
+        }
         ContractArgs ca = {};
         ca.Vall = (const double2*)V_all;
         ca.L3 = L3; ca.fs = fs; ca.tlist = dtl; ca.nt = nact; ca.nev = nev;
