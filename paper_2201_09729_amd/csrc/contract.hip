@@ -367,12 +367,12 @@ __device__ __forceinline__ void mac4(d4& re, d4& im, double2 x, double2 w) {
 // matrix product (32 rows (site, colour) and four or eight right-hand sides per wave) in one
 // launch with the zero fill of the other timeslices.  Bound: the fill, a stream of
 // stores.  With a thread per (site, spin) storing 48 bytes apart and a block per (mode,
-// right-hand side) for c, 32 modes and right-hand sides at 24^3 x 48 took 1.32 ms; 0.78 ms so
+// right-hand side) for c, 32 modes and right-hand sides at 24^3 x 48 took 1.32 ms; 0.77 ms so
 // (4.1 GB of stores: 5.3 TB/s over the call).
 constexpr int FILL_PER_BLOCK = 1024;
 
 template <int H>  // column sets per wave
-__global__ void __launch_bounds__(256, 4) k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long fs,
+__global__ void __launch_bounds__(256, H == 2 ? 1 : 4) k_proj_apply(const double2* __restrict__ Vt, const double2* in, double2* out, long L3, long fs,
                                                     int t, int nev, const double2* __restrict__ coef, int nrhs, int mode,
                                                     unsigned nab, unsigned nrb) {
     const long tofs = (long)t * L3 * 12;
@@ -408,8 +408,7 @@ __global__ void __launch_bounds__(256, 4) k_proj_apply(const double2* __restrict
         for (int b = 0; b < 2; ++b) re[h][b] = im[h][b] = z;
     const double2* v = Vt + (long)q * nrow;
     const double2* c = coef + ((long)ub * H * nev + q) * 16 + m;
-    for (int k = 0; k < nev; k += 4) {
-        double2 x[2], w[H];
+    auto load = [&](int k, double2 (&x)[2], double2 (&w)[H]) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) x[b] = make_double2(0.0, 0.0);
 #pragma unroll
@@ -420,10 +419,25 @@ __global__ void __launch_bounds__(256, 4) k_proj_apply(const double2* __restrict
             w[0] = c[(long)k * 16];
             if (two) w[H - 1] = c[((long)nev + k) * 16];
         }
+    };
+    double2 x[2], w[H];
+    if (H == 2) load(0, x, w);
+    for (int k = 0; k < nev; k += 4) {
+        // two column sets: the next four modes are on their way while these are worked on (24^3 x
+        // 48 with 32 modes and right-hand sides 766 us per call, 778 without; one set would lose 3%)
+        double2 nx[2], nw[H];
+        if (H == 2) load(k + 4, nx, nw);
+        else load(k, x, w);
 #pragma unroll
         for (int h = 0; h < H; ++h)
 #pragma unroll
             for (int b = 0; b < 2; ++b) mac4(re[h][b], im[h][b], x[b], w[h]);
+        if (H == 2) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) x[b] = nx[b];
+#pragma unroll
+            for (int h = 0; h < H; ++h) w[h] = nw[h];
+        }
     }
 #pragma unroll
     for (int h = 0; h < H; ++h) {
